@@ -48,49 +48,118 @@ struct EpiGeluGrad {
   }
 };
 
-// Output layer, one wave per row: y = A2 . w3 + b3; with a target also
-// dy = 2 (y - t) / n and the squared error (double) for the loss.
-__global__ void k_mlp_out(const float* A2, const float* w3, const float* b3, int64_t n,
-                          const float* t, float* y, float* dy, double* sq) {
+// Output layer, one wave per row: y = A2 . w3 + b3.
+__device__ __forceinline__ float mlp_row_out(float a0, float a1, float w0, float w1, float b3) {
+  float acc = a0 * w0 + a1 * w1;
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+  return acc + b3;  // (lane 0)
+}
+__global__ void k_mlp_out(const float* A2, const float* w3, const float* b3, int64_t n, float* y) {
   const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= n) return;
-  float acc = A2[row * kHid + lane] * w3[lane] + A2[row * kHid + lane + 64] * w3[lane + 64];
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+  const float out = mlp_row_out(A2[row * kHid + lane], A2[row * kHid + lane + 64], w3[lane],
+                                w3[lane + 64], b3[0]);
+  if (lane == 0) y[row] = out;
+}
+
+// Output layer of a training step and everything its rows feed in one pass
+// (each wave kOutRows / 4 rows, lane l columns l and l + 64):
+//   y = A2 . w3 + b3, dy = 2 (y - t) / n, dZ2[b][j] = dy[b] w3[j] gelu'(Z2[b][j]),
+// and this workgroup's share of the column sums, in FP64:
+//   part[g] = [ sum dZ2 (128) | sum A2 dy (128) | sum dy (1) | sum (y - t)^2 (1) ].
+// Bound by the launch and the row loads (6 MB at n = 4096).  32 rows a
+// workgroup put 128 of them on the chip at the training minibatch of 4096; with
+// one thread walking 1024 rows of a column the four column sums of a step took
+// 0.92 ms, this kernel with its k_sum_cols takes about 20 us.
+constexpr int kOutRows = 32;
+constexpr int kOutCols = 2 * kHid + 2;
+__global__ __launch_bounds__(256) void k_mlp_out_grad(const float* __restrict__ A2,
+                                                      const float* __restrict__ Z2,
+                                                      const float* __restrict__ w3,
+                                                      const float* __restrict__ b3, int64_t n,
+                                                      const float* __restrict__ t,
+                                                      float* __restrict__ dZ2,
+                                                      double* __restrict__ part) {
+  constexpr int RW = kOutRows / 4;
+  __shared__ double red[4][kOutCols];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t r0 = (int64_t)blockIdx.x * kOutRows + wave * RW;
+  const float w0 = w3[lane], w1 = w3[lane + 64], b = b3[0];
+  double s2[2] = {0.0, 0.0}, s3[2] = {0.0, 0.0}, sd = 0.0, sq = 0.0;
+#pragma unroll
+  for (int u = 0; u < RW; ++u) {
+    const int64_t row = r0 + u;
+    if (row >= n) break;  // (uniform over the wave)
+    const float a0 = A2[row * kHid + lane], a1 = A2[row * kHid + lane + 64];
+    const float z0 = Z2[row * kHid + lane], z1 = Z2[row * kHid + lane + 64];
+    const float r = __shfl(mlp_row_out(a0, a1, w0, w1, b), 0, 64) - t[row];
+    const float dy = 2.0f * r / (float)n;
+    const float d0 = dy * w0 * gelu_grad(z0), d1 = dy * w1 * gelu_grad(z1);
+    dZ2[row * kHid + lane] = d0;
+    dZ2[row * kHid + lane + 64] = d1;
+    s2[0] += (double)d0;
+    s2[1] += (double)d1;
+    s3[0] += (double)a0 * (double)dy;
+    s3[1] += (double)a1 * (double)dy;
+    sd += (double)dy;
+    sq += (double)r * (double)r;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    red[wave][lane + 64 * h] = s2[h];
+    red[wave][kHid + lane + 64 * h] = s3[h];
+  }
   if (lane == 0) {
-    const float out = acc + b3[0];
-    y[row] = out;
-    if (t) {
-      const float r = out - t[row];
-      dy[row] = 2.0f * r / (float)n;
-      sq[row] = (double)r * (double)r;
-    }
+    red[wave][2 * kHid] = sd;
+    red[wave][2 * kHid + 1] = sq;
   }
+  __syncthreads();
+  for (int c = threadIdx.x; c < kOutCols; c += 256)
+    part[(int64_t)blockIdx.x * kOutCols + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
 }
 
-// dZ2[b][j] = dy[b] w3[j] gelu'(Z2[b][j])
-__global__ void k_mlp_dz2(const float* Z2, const float* dy, const float* w3, int64_t n, float* dZ2) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * kHid) return;
-  const int64_t b = idx / kHid, j = idx - b * kHid;
-  dZ2[idx] = dy[b] * w3[j] * gelu_grad(Z2[idx]);
-}
-
-// Column sums of a [n][cols] matrix (rows optionally weighted by wrow[b]),
-// first stage: workgroup g sums rows [g*R, (g+1)*R) into part[g][col]
-// (double).  cols <= 256; thread c handles column c.
-__global__ void k_col_partial(const float* A, const float* wrow, int64_t n, int64_t cols,
-                              int64_t R, double* part) {
-  const int64_t g = blockIdx.x;
-  const int c = threadIdx.x;
-  if (c >= cols) return;
-  const int64_t r0 = g * R, r1 = (r0 + R) < n ? (r0 + R) : n;
+// Column sums of a [n][128] matrix over rows [g R, (g + 1) R): part[g][col]
+// (FP64), two row lanes per column.
+constexpr int kColRows = 32;
+__global__ __launch_bounds__(256) void k_col_partial(const float* __restrict__ A, int64_t n,
+                                                     double* __restrict__ part) {
+  __shared__ double red[kHid];
+  const int c = threadIdx.x & (kHid - 1), h = threadIdx.x / kHid;
+  const int64_t r0 = (int64_t)blockIdx.x * kColRows + h * (kColRows / 2);
   double s = 0.0;
-  for (int64_t b = r0; b < r1; ++b) {
-    const double a = A ? (double)A[b * cols + c] : 1.0;
-    s += wrow ? a * (double)wrow[b] : a;
+#pragma unroll
+  for (int u = 0; u < kColRows / 2; ++u)
+    if (r0 + u < n) s += (double)A[(r0 + u) * kHid + c];
+  if (h) red[c] = s;
+  __syncthreads();
+  if (!h) part[(int64_t)blockIdx.x * kHid + c] = s + red[c];
+}
+
+// out[i] (float) = sum_g part[g][i] of short rows and many groups (16 columns a
+// workgroup, 16 group lanes each, fixed order); with `loss`, column len holds
+// the squared errors and *loss = their sum / n.
+__global__ __launch_bounds__(256) void k_sum_cols(const double* __restrict__ part, int64_t ng,
+                                                  int ld, int len, float* __restrict__ out,
+                                                  int64_t n, double* __restrict__ loss) {
+  __shared__ double red[16][17];
+  const int cl = threadIdx.x & 15, gl = threadIdx.x >> 4;
+  const int i = blockIdx.x * 16 + cl;
+  double s = 0.0;
+  if (i < ld)
+#pragma unroll 8
+    for (int64_t g = gl; g < ng; g += 16) s += part[g * ld + i];
+  red[gl][cl] = s;
+  __syncthreads();
+  if (gl == 0 && i < ld) {
+    s = 0.0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += red[u][cl];
+    if (i < len)
+      out[i] = (float)s;
+    else if (loss)
+      *loss = s / (double)n;
   }
-  part[g * cols + c] = s;
 }
 
 // out[i] (float) = sum_z part[z][i] (fixed order)
@@ -98,16 +167,9 @@ __global__ void k_sum_parts(const double* part, int64_t nz, int64_t len, float* 
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= len) return;
   double s = 0.0;
+#pragma unroll 8
   for (int64_t z = 0; z < nz; ++z) s += part[z * len + i];
   out[i] = (float)s;
-}
-
-// loss = sum sq / n (one workgroup, fixed order)
-__global__ void k_loss(const double* sq, int64_t n, double* loss) {
-  double v[1] = {0.0};
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) v[0] += sq[i];
-  block_sum<1>(v);
-  if (threadIdx.x == 0) *loss = v[0] / (double)n;
 }
 
 // Adam (beta1 0.9, beta2 0.999, eps 1e-8) with bias correction for step t >= 1.
@@ -260,15 +322,17 @@ __global__ void k_warm_permute(int64_t nbf, const double* C0, const int64_t* per
 }
 
 struct MlpBuffers {
-  float *Z1, *A1, *Z2, *A2, *dZ2, *dZ1, *y, *dy, *grad;
-  double *sq, *part, *cpart;
+  float *Z1, *A1, *Z2, *A2, *dZ2, *dZ1, *grad;
+  double *part, *opart, *cpart;
 };
 
-int mlp_buffers(qsgw_ctx* c, int64_t n, int64_t nz, int64_t ngroups, MlpBuffers* b) {
+// nz = 0: inference buffers only.
+int mlp_buffers(qsgw_ctx* c, int64_t n, int64_t nz, MlpBuffers* b) {
   float* f = nullptr;
   double* d = nullptr;
-  const size_t nf = (size_t)(6 * n * kHid + 2 * n + kNParams + 64);
-  const size_t ndd = (size_t)(n + nz * (kHid * kHid + kHid * kIn) + ngroups * (3 * kHid + 2) + 64);
+  const int64_t og = (n + kOutRows - 1) / kOutRows, cg = (n + kColRows - 1) / kColRows;
+  const size_t nf = (size_t)(6 * n * kHid + kNParams + 64);
+  const size_t ndd = (size_t)(nz > 0 ? nz * kHid * kHid + og * kOutCols + cg * kHid : 1);
   CHECK(ws_get(c, W_MLP_F32, nf, &f));
   CHECK(ws_get(c, W_MLP_F64, ndd, &d));
   b->Z1 = f;
@@ -277,12 +341,10 @@ int mlp_buffers(qsgw_ctx* c, int64_t n, int64_t nz, int64_t ngroups, MlpBuffers*
   b->A2 = b->Z2 + n * kHid;
   b->dZ2 = b->A2 + n * kHid;
   b->dZ1 = b->dZ2 + n * kHid;
-  b->y = b->dZ1 + n * kHid;
-  b->dy = b->y + n;
-  b->grad = b->dy + n;
-  b->sq = d;
-  b->part = b->sq + n;
-  b->cpart = b->part + nz * (kHid * kHid + kHid * kIn);
+  b->grad = b->dZ1 + n * kHid;
+  b->part = d;  // (dW1 reuses it after dW2)
+  b->opart = b->part + nz * kHid * kHid;
+  b->cpart = b->opart + og * kOutCols;
   return QSGW_OK;
 }
 
@@ -315,11 +377,10 @@ int qsgw_mlp_forward(qsgw_ctx* c, const float* params, int64_t n, const float* X
   CHECK(check_finite(c, "qsgw_mlp_forward",
                      {fin32(params, kNParams, "params"), fin32(X, n * kIn, "X")}));
   MlpBuffers b;
-  CHECK(mlp_buffers(c, n, 1, 1, &b));
+  CHECK(mlp_buffers(c, n, 0, &b));
   CHECK(mlp_hidden(c, params, n, X, b, false));
   hipLaunchKernelGGL(k_mlp_out, dim3(blocks_for(n, 4)), dim3(256), 0, c->stream, b.A2,
-                     params + kOffW3, params + kOffB3, n, (const float*)nullptr, y, (float*)nullptr,
-                     (double*)nullptr);
+                     params + kOffW3, params + kOffB3, n, y);
   return launch_check(c, "k_mlp_out");
 }
 
@@ -347,43 +408,32 @@ int qsgw_mlp_train_step(qsgw_ctx* c, float* params, float* adam_m, float* adam_v
                      {fin32(params, kNParams, "params"), fin32(adam_m, kNParams, "adam_m"),
                       fin32(adam_v, kNParams, "adam_v"), fin32(X, n * kIn, "X"),
                       fin32(target, n, "target")}));
-  // weight gradients reduce over the batch: split K = n in chunks of 512
-  const SplitPlan sp = split_plan(n, (n + 511) / 512);
-  const int64_t R = 1024, ngroups = (n + R - 1) / R;
+  // weight gradients reduce over the batch: split K = n into 32 chunks (the
+  // two products have 4 and 2 output tiles), of 128 to 512 rows: below 128 the
+  // partial sums cost more than the chunk, above 512 the chunk is the chain
+  // (n = 4096, dW2: 27.9 us at 512 rows, 8 chunks)
+  const int64_t chunk = n <= 32 * 128 ? 128 : (n >= 32 * 512 ? 512 : (n + 31) / 32);
+  const SplitPlan sp = split_plan(n, (n + chunk - 1) / chunk);
+  const int64_t og = (n + kOutRows - 1) / kOutRows, cg = (n + kColRows - 1) / kColRows;
   MlpBuffers b;
-  CHECK(mlp_buffers(c, n, sp.nz, ngroups, &b));
+  CHECK(mlp_buffers(c, n, sp.nz, &b));
   CHECK(mlp_hidden(c, params, n, X, b, true));
-  hipLaunchKernelGGL(k_mlp_out, dim3(blocks_for(n, 4)), dim3(256), 0, c->stream, b.A2,
-                     params + kOffW3, params + kOffB3, n, target, b.y, b.dy, b.sq);
-  CHECK(launch_check(c, "k_mlp_out"));
-  hipLaunchKernelGGL(k_mlp_dz2, dim3(blocks_for(n * kHid)), dim3(256), 0, c->stream, b.Z2, b.dy,
-                     params + kOffW3, n, b.dZ2);
-  CHECK(launch_check(c, "k_mlp_dz2"));
   float* g = grad ? grad : b.grad;
-  // output layer: dw3 = A2^T dy, db3 = sum dy
-  double* cp = b.cpart;
-  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)ngroups), dim3(256), 0, c->stream, b.A2, b.dy, n,
-                     (int64_t)kHid, R, cp);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, c->stream, cp, ngroups, (int64_t)kHid,
-                     g + kOffW3);
-  cp += ngroups * kHid;
-  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)ngroups), dim3(256), 0, c->stream,
-                     (const float*)nullptr, b.dy, n, (int64_t)1, R, cp);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, c->stream, cp, ngroups, (int64_t)1,
-                     g + kOffB3);
-  cp += ngroups;
-  // layer 2: dW2[i][j] = sum_b dZ2[b][i] A1[b][j], db2 = colsum dZ2
+  // output layer: dZ2, and db2, dw3 = A2^T dy, db3 = sum dy (adjacent in the
+  // parameter layout) with the loss
+  static_assert(kOffW3 == kOffB2 + kHid && kOffB3 == kOffW3 + kHid, "parameter layout");
+  hipLaunchKernelGGL(k_mlp_out_grad, dim3((unsigned)og), dim3(256), 0, c->stream, b.A2, b.Z2,
+                     params + kOffW3, params + kOffB3, n, target, b.dZ2, b.opart);
+  CHECK(launch_check(c, "k_mlp_out_grad"));
+  hipLaunchKernelGGL(k_sum_cols, dim3((kOutCols + 15) / 16), dim3(256), 0, c->stream, b.opart, og,
+                     kOutCols, 2 * kHid + 1, g + kOffB2, n, loss);
+  // layer 2: dW2[i][j] = sum_b dZ2[b][i] A1[b][j]
   CHECK((gemm_t<float, 64, 64, false>(
       c, "mlp dW2", Strided<false, float>{b.dZ2, 1, kHid, 0, kHid},
       Strided<false, float>{b.A1, 1, kHid, 0, kHid},
       EpiStore{b.part, kHid, 0, kHid * kHid, 1.0}, kHid, kHid, n, 1, sp)));
   hipLaunchKernelGGL(k_sum_parts, dim3(blocks_for(kHid * kHid)), dim3(256), 0, c->stream, b.part,
                      sp.nz, (int64_t)(kHid * kHid), g + kOffW2);
-  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)ngroups), dim3(256), 0, c->stream, b.dZ2,
-                     (const float*)nullptr, n, (int64_t)kHid, R, cp);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, c->stream, cp, ngroups, (int64_t)kHid,
-                     g + kOffB2);
-  cp += ngroups * kHid;
   // dZ1 = (dZ2 W2) * gelu'(Z1)
   CHECK((gemm_t<float, 64, 64, false>(
       c, "mlp dA1", Strided<true, float>{b.dZ2, kHid, 1, 0, n},
@@ -396,15 +446,10 @@ int qsgw_mlp_train_step(qsgw_ctx* c, float* params, float* adam_m, float* adam_v
       kIn, n, 1, sp)));
   hipLaunchKernelGGL(k_sum_parts, dim3(blocks_for(kHid * kIn)), dim3(256), 0, c->stream, b.part,
                      sp.nz, (int64_t)(kHid * kIn), g + kOffW1);
-  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)ngroups), dim3(256), 0, c->stream, b.dZ1,
-                     (const float*)nullptr, n, (int64_t)kHid, R, cp);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, c->stream, cp, ngroups, (int64_t)kHid,
-                     g + kOffB1);
+  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)cg), dim3(256), 0, c->stream, b.dZ1, n, b.cpart);
+  hipLaunchKernelGGL(k_sum_cols, dim3((kHid + 15) / 16), dim3(256), 0, c->stream, b.cpart, cg,
+                     kHid, kHid, g + kOffB1, n, (double*)nullptr);
   CHECK(launch_check(c, "mlp gradient"));
-  if (loss) {
-    hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, c->stream, b.sq, n, loss);
-    CHECK(launch_check(c, "k_loss"));
-  }
   const float c1 = 1.0f - powf(0.9f, (float)step), c2 = 1.0f - powf(0.999f, (float)step);
   hipLaunchKernelGGL(k_adam, dim3(blocks_for(kNParams)), dim3(256), 0, c->stream, params, adam_m,
                      adam_v, g, kNParams, (float)lr, c1, c2);

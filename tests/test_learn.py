@@ -93,6 +93,13 @@ def test_train_step_gradient_loss_and_adam(env, n):
     np.testing.assert_allclose(V.cpu().numpy(), ve, rtol=1e-5, atol=1e-12)
 
 
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 4096, 16385])
+def test_train_step_row_group_edges(env, n):
+    """Batch sizes at the edges of the 32-row groups of the column sums and of
+    the weight gradients' chunk rule, to the bounds of the test above."""
+    test_train_step_gradient_loss_and_adam(env, n)
+
+
 def test_training_reduces_loss(env):
     """A smooth synthetic regression: 300 Adam steps cut the loss tenfold."""
     q, ctx = env
