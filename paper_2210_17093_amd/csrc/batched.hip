@@ -645,23 +645,19 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
     ni += tables[i].size();
   }
   {
-    // finite inputs of every molecule: one pass each, one read-back
-    int* flags = nullptr;
-    CHECK(ws_get(c, W_FLAGS, 8, &flags));
-    HIP_TRY(c, hipMemsetAsync(flags + 5, 0, sizeof(int), c->stream));
+    // finite inputs of every molecule: one pass each (kFinMax arrays a launch), one wait
+    for (int i = 0; i < kFinMax; ++i) c->hfin[i] = 0;
+    std::vector<FiniteArg> arr;
     for (int64_t i = 0; i < nmol; ++i) {
       const Mol& m = P.mols[i];
-      const double* arr[4] = {m.B_ao, m.h, m.C, m.eps};
-      const int64_t len[4] = {m.naux * m.nn, m.nn, m.nn, m.nbf};
-      for (int k = 0; k < 4; ++k) {
-        const int64_t nb = (len[k] + 255) / 256;
-        hipLaunchKernelGGL(k_check_finite, dim3((unsigned)(nb < 512 ? nb : 512)), dim3(256), 0,
-                           c->stream, arr[k], len[k], flags + 5, 1 << k);
-      }
+      arr.insert(arr.end(), {fin(m.B_ao, m.naux * m.nn, "B_ao"), fin(m.h, m.nn, "h"),
+                             fin(m.C, m.nn, "C"), fin(m.eps, m.nbf, "eps")});
     }
-    CHECK(launch_check(c, "k_check_finite"));
+    for (size_t i = 0; i < arr.size(); i += kFinMax)
+      CHECK(queue_finite(c, &arr[i], (int)std::min<size_t>(kFinMax, arr.size() - i)));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
     int bad = 0;
-    CHECK(read_flag(c, flags + 5, &bad));
+    for (int i = 0; i < kFinMax; ++i) bad |= c->hfin[i];
     if (bad) {
       for (int64_t i = 0; i < nmol; ++i) {
         const Mol& m = P.mols[i];

@@ -175,6 +175,9 @@ struct qsgw_ctx {
   // this device's copy of the allocation-free entry point's static scratch
   // array (noalloc.hip), null if the lookup failed
   double* scratch = nullptr;
+  // flag words of the finite-input scans (kFinMax ints, pinned host memory the
+  // kernels write and the host reads after a stream synchronization)
+  int* hfin = nullptr;
   // DIIS history of qsgw_iterate (W_DIIS_*): stored pairs, next slot, and
   // the (N_b, subspace size) it belongs to; diis_slots stages the slot order
   int64_t diis_n = 0, diis_next = 0, diis_nbf = -1, diis_m = 0;
@@ -568,35 +571,37 @@ struct FiniteArg {
 inline FiniteArg fin(const double* p, int64_t n, const char* name) { return {p, n, name, false}; }
 inline FiniteArg fin32(const float* p, int64_t n, const char* name) { return {p, n, name, true}; }
 
+// Queues the scans of args[0..n) (n <= kFinMax, null entries skipped) with the
+// flag words of c->hfin; a workgroup of a long array reads at least 16 KB.
+inline int queue_finite(qsgw_ctx* c, const FiniteArg* args, int n) {
+  FiniteTable t{};
+  t.n = n;
+  unsigned wg = 0;
+  for (int i = 0; i < n; ++i) {
+    const FiniteArg& a = args[i];
+    const int64_t len = a.p && a.n > 0 ? a.n : 0;
+    const int64_t nb = (len + 2047) / 2048;
+    t.p[i] = a.p;
+    t.len[i] = len;
+    t.first[i] = wg;
+    wg += (unsigned)(nb < 2048 ? nb : 2048);
+    if (a.f32) t.f32 |= 1u << i;
+  }
+  t.first[n] = wg;
+  if (wg == 0) return QSGW_OK;
+  hipLaunchKernelGGL(k_check_finite_table, dim3(wg), dim3(256), 0, c->stream, t, c->hfin);
+  return launch_check(c, "k_check_finite_table");
+}
+
 inline int check_finite(qsgw_ctx* c, const char* what, std::initializer_list<FiniteArg> args) {
-  int* flags = nullptr;
-  CHECK(ws_get(c, W_FLAGS, 8, &flags));
-  int* bad = flags + 5;
-  HIP_TRY(c, hipMemsetAsync(bad, 0, sizeof(int), c->stream));
-  int bit = 0;
-  for (const FiniteArg& a : args) {
-    if (a.p && a.n > 0) {
-      int64_t nb = (a.n + 255) / 256;
-      const unsigned grid = (unsigned)(nb < 2048 ? nb : 2048);
-      if (a.f32)
-        hipLaunchKernelGGL(k_check_finite_f32, dim3(grid), dim3(256), 0, c->stream,
-                           static_cast<const float*>(a.p), a.n, bad, 1 << bit);
-      else
-        hipLaunchKernelGGL(k_check_finite, dim3(grid), dim3(256), 0, c->stream,
-                           static_cast<const double*>(a.p), a.n, bad, 1 << bit);
-    }
-    ++bit;
-  }
-  CHECK(launch_check(c, "k_check_finite"));
-  int mask = 0;
-  CHECK(read_flag(c, bad, &mask));
-  if (mask) {
-    int i = 0;
-    for (const FiniteArg& a : args) {
-      if (mask & (1 << i)) return fail(c, QSGW_ERR_NONFINITE, "%s: non-finite value in %s", what, a.name);
-      ++i;
-    }
-  }
+  const int n = (int)args.size();
+  if (n > kFinMax) return fail(c, QSGW_ERR_INVALID_ARG, "%s: too many arrays to check", what);
+  for (int i = 0; i < kFinMax; ++i) c->hfin[i] = 0;  // (no scan is in flight between calls)
+  CHECK(queue_finite(c, args.begin(), n));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  for (int i = 0; i < n; ++i)
+    if (c->hfin[i])
+      return fail(c, QSGW_ERR_NONFINITE, "%s: non-finite value in %s", what, args.begin()[i].name);
   return QSGW_OK;
 }
 

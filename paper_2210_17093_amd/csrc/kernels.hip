@@ -387,25 +387,46 @@ __global__ void k_diis_combine(const double* F, int64_t len, const int* slots, i
   out[e] = s;
 }
 
-template <class T>
-__device__ __forceinline__ void check_finite_body(const T* x, int64_t len, int* bad, int mask) {
-  bool ok = true;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < len;
-       i += (int64_t)gridDim.x * blockDim.x)
-    ok = ok && isfinite(x[i]);
-  if (!ok) atomicOr(bad, mask);
-}
 __global__ void k_scale_rho(double* rho, int64_t naux, int64_t ntr, const double* Omega) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= naux * ntr) return;
   rho[idx] *= sqrt(2.0 / Omega[idx % ntr]);
 }
 
-__global__ void k_check_finite(const double* x, int64_t len, int* bad, int mask) {
-  check_finite_body(x, len, bad, mask);
+// Whether x[0..len) holds only finite values, as far as this thread of `nwg`
+// workgroups (this one `g`) looks.  Eight loads in flight per thread.
+template <class T>
+__device__ __forceinline__ bool finite_part(const T* x, int64_t len, int64_t g, int64_t nwg) {
+  constexpr int U = 8;
+  const int64_t step = nwg * blockDim.x;
+  int64_t i = g * blockDim.x + threadIdx.x;
+  bool ok = true;
+  for (; i + (U - 1) * step < len; i += U * step) {
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = x[i + u * step];
+#pragma unroll
+    for (int u = 0; u < U; ++u) ok = ok && isfinite(v[u]);
+  }
+  for (; i < len; i += step) ok = ok && isfinite(x[i]);
+  return ok;
 }
-__global__ void k_check_finite_f32(const float* x, int64_t len, int* bad, int mask) {
-  check_finite_body(x, len, bad, mask);
+__global__ void k_check_finite(const double* x, int64_t len, int* bad, int mask) {
+  if (!finite_part(x, len, blockIdx.x, gridDim.x)) atomicOr(bad, mask);
+}
+
+// Bound by reading each array once.  One launch for all arrays of a call and a
+// flag word per array in host memory: a call that works on a few kilobytes
+// spent most of its time in the launches of one scan per array, a fill and a
+// copy around them.
+__global__ void k_check_finite_table(FiniteTable t, int* bad) {
+  int i = 0;
+  while (i + 1 < t.n && blockIdx.x >= t.first[i + 1]) ++i;
+  const int64_t g = blockIdx.x - t.first[i], nwg = t.first[i + 1] - t.first[i];
+  const bool ok = (t.f32 >> i & 1)
+                      ? finite_part(static_cast<const float*>(t.p[i]), t.len[i], g, nwg)
+                      : finite_part(static_cast<const double*>(t.p[i]), t.len[i], g, nwg);
+  if (!ok) __hip_atomic_store(bad + i, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Order-independent fingerprint of an array's bit patterns:

@@ -487,10 +487,20 @@ __global__ void k_fix_column_signs(double* C, int64_t n);
 __global__ void k_max_abs_diff(const double* a, const double* b, int64_t n, double* out);
 // Non-finite scan: flags any NaN/Inf in x[0..len).
 __global__ void k_check_finite(const double* x, int64_t len, int* bad, int mask);
+// Non-finite scan of several arrays in one launch: array i owns the workgroups
+// [first[i], first[i + 1]); a NaN or infinity in it sets bad[i].
+constexpr int kFinMax = 32;
+struct FiniteTable {
+  const void* p[kFinMax];
+  int64_t len[kFinMax];
+  unsigned first[kFinMax + 1];
+  unsigned f32;  // bit i: array i is FP32
+  int n;
+};
+__global__ void k_check_finite_table(FiniteTable t, int* bad);
 // rho[P][s] *= sqrt(2 / Omega[s]) over a row-major [naux][ntr] array (the
 // factor of Eq. (18) with the normalisation (X+Y)^s = sqrt(Delta) Z^s / sqrt(Omega_s))
 __global__ void k_scale_rho(double* rho, int64_t naux, int64_t ntr, const double* Omega);
-__global__ void k_check_finite_f32(const float* x, int64_t len, int* bad, int mask);
 __global__ void k_bits_fingerprint(const double* x, int64_t len, unsigned long long* out);
 __global__ void k_fock_frozen(const double* hmo, const double* V, int64_t n, double* F);
 // Diagonal pole sum Sigma_mm(omega_l), Eq. (17), complex128 interleaved.

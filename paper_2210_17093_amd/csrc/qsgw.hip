@@ -668,6 +668,12 @@ int qsgw_ctx_create(qsgw_ctx** out, void* hip_stream) {
     delete c;
     return QSGW_ERR_SOLVER;
   }
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->hfin), kFinMax * sizeof(int)) != hipSuccess) {
+    (void)hipGetLastError();
+    rocblas_destroy_handle(c->blas);
+    delete c;
+    return QSGW_ERR_ALLOC;
+  }
   // the allocation-free entry point reports a failed lookup itself
   if (noalloc_setup(c) != QSGW_OK) c->scratch = nullptr;
   c->err.clear();
@@ -689,6 +695,7 @@ int qsgw_ctx_destroy(qsgw_ctx* c) {
     if (b.p) (void)hipFree(b.p);
   for (auto e : c->events) (void)hipEventDestroy(e);
   if (c->blas) rocblas_destroy_handle(c->blas);
+  if (c->hfin) (void)hipHostFree(c->hfin);
   delete c;
   return QSGW_OK;
 }

@@ -239,3 +239,38 @@ def test_iterate_fp64_streamed_blocks_match_oracle(q, ctx, s_block, with_diag):
             assert abs(d[m, 0] - s.real) <= 1e-9 * (abs(s) + 1e-3)
             assert abs(d[m, 1] - s.imag) <= 1e-9 * (abs(s) + 1e-3)
             assert abs(d[m, 2] - der.real) <= 1e-8 * (abs(der) + 1e-3)
+
+
+@pytest.mark.parametrize("rows", [1, 128, 129, 262144, 300007])
+def test_finite_scan_reaches_the_last_element(q, ctx, rows):
+    """One scan covers every array of a call: arrays at the edges of a scan
+    workgroup (2048 values) and of the largest launch (2048 workgroups, whose
+    threads then loop), the bad value in the last element, the array named."""
+    X = torch.zeros((rows, q.MLP_NFEAT), dtype=torch.float32, device="cuda")
+    P = torch.zeros(q.MLP_NPARAMS, dtype=torch.float32, device="cuda")
+    assert float(q.qsgw_mlp_forward_bf16(ctx, P, X).abs().max()) == 0.0
+    X[-1, -1] = float("inf")
+    with pytest.raises(q.QsgwError) as e:
+        q.qsgw_mlp_forward_bf16(ctx, P, X)
+    assert e.value.code == q.ERR_NONFINITE and "in X" in str(e.value)
+    X[-1, -1] = 0.0
+    P[-1] = float("nan")
+    with pytest.raises(q.QsgwError) as e:
+        q.qsgw_mlp_forward_bf16(ctx, P, X)
+    assert e.value.code == q.ERR_NONFINITE and "in params" in str(e.value)
+
+
+def test_finite_scan_of_many_molecules(q, ctx):
+    """Nine molecules are 36 arrays, more than one scan launch takes: the bad
+    value in the last array of the last molecule."""
+    mols = []
+    for i in range(9):
+        n = 10 + i
+        mols.append(dict(B_ao=torch.zeros((4, n, n), dtype=torch.float64, device="cuda"), nocc=2,
+                         h=torch.zeros((n, n), dtype=torch.float64, device="cuda"),
+                         C=torch.eye(n, dtype=torch.float64, device="cuda"),
+                         eps=torch.arange(n, dtype=torch.float64, device="cuda")))
+    mols[-1]["eps"][-1] = float("nan")
+    with pytest.raises(q.QsgwError) as e:
+        q.qsgw_iterate_batched(ctx, mols, 0.05)
+    assert e.value.code == q.ERR_NONFINITE and "molecule 8" in str(e.value) and "eps" in str(e.value)
