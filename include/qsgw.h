@@ -132,8 +132,13 @@ int qsgw_rpa_build(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc, const
 /* Solvers of the Casida eigenproblem M Z = Z Omega^2 (Eq. (12)), chosen per
  * context with qsgw_set_eigensolver.  They apply to qsgw_rpa_solve and to the
  * Casida eigensolves inside qsgw_iterate and qsgw_gw_unrestricted (the Fock
- * eigensolves and the batched path always use rocSOLVER dsyevd). */
-#define QSGW_EIG_AUTO 0      /* the two-stage solver for n >= 8192, dsyevd below (default) */
+ * eigensolves always take the automatic choice for their order, and so do
+ * both eigensolves of the batched path). */
+/* Default: up to n = 3072 the library's one-stage solver, which holds the
+ * matrix on the chip during its reduction; the two-stage solver for
+ * n >= 8192; rocSOLVER dsyevd between (and where the device has no
+ * cooperative launches). */
+#define QSGW_EIG_AUTO 0
 #define QSGW_EIG_ROCSOLVER 1 /* rocSOLVER dsyevd (one-stage tridiagonal reduction) */
 /* Two-stage reduction, all FP64: dense -> band of half-width 64 by blocked
  * Householder panels whose two-sided updates are matrix products, band ->
@@ -329,7 +334,7 @@ int qsgw_gw_unrestricted(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc_
  *   spins' correlation potentials in their current MO bases (qsgw_gw_unrestricted);
  * eps_a, eps_b: [nbf] device out; C_a, C_b: [nbf][nbf] device in/out.
  * Errors: 0 < nocc_a, nocc_b < nbf violated, naux < 1, NULL pointers,
- * QSGW_ERR_SOLVER if dsyevd fails.  Synchronizes the context stream; timed as
+ * QSGW_ERR_SOLVER if the eigensolve fails.  Synchronizes the context stream; timed as
  * the fock stage of qsgw_last_stage_ms.
  */
 int qsgw_fock_unrestricted(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc_a, int64_t nocc_b,

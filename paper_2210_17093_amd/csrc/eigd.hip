@@ -1,0 +1,1705 @@
+// Dense symmetric eigensolver for the orders where a one-stage reduction
+// holds its matrix on the chip (n <= kEigTeamMax), one problem or many of
+// different orders in the same launches.  Everything in FP64.
+//
+//   1. Reduction A = Q T Q^T (Householder, column j annihilates A[j+2.., j]):
+//      a team of workgroups keeps the rows of A in registers for the whole
+//      reduction, so a column costs its 3 m^2 multiply-adds and one exchange
+//      between the workgroups instead of a pass over the matrix in memory
+//      (k_tri_team).
+//   2. Eigenpairs of T by divide and conquer: blocks of up to 64 rows are
+//      solved in one workgroup (implicit QL on leaves of up to 16, then
+//      merges in LDS: k_dc_base), larger ones merged level by level with all
+//      nodes of a level in the same launches (k_dc_*), the eigenvectors of a
+//      merge as two grouped products (each half's rows use only the columns
+//      that are non-zero there).
+//   3. Z = Q E by blocks of 128 reflectors in compact WY form, as products.
+//
+// The merge theory (Cuppen's tearing, deflation of small weights and of close
+// poles by a rotation, the secular equation solved relative to the nearer
+// pole, Gu and Eisenstat's weights from the computed roots) is that of
+// eigdc.hip.
+#include "internal.hpp"
+
+#include <algorithm>
+
+namespace {
+
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kTeamThreads = 512;
+constexpr int kBase = 64;   // largest block of the tridiagonal solved in one workgroup
+constexpr int kLeaf = 16;   // largest QL leaf
+constexpr int kBk = 128;    // reflectors per WY block
+constexpr unsigned long long kEmpty = ~0ull;  // a slot not published yet
+
+// One eigenproblem on the device.
+struct EigDev {
+  double *A, *ev;      // matrix [n][ld] in, eigenvectors out; eigenvalues out
+  double *E, *B, *U;   // n x n work: eigenvectors; gathered columns and W = V^T X; merge
+                       // vectors and Y = V T (E and B: the exchange of the reduction)
+  double *d, *e, *tau; // tridiagonal (scaled after k_dc_scale), reflector factors
+  double* vec;         // merge vectors, kVec x n
+  int* idx;            // merge index maps, kIdx x n
+  double *G, *T;       // Gram matrices and T factors [blocks][128][128]
+  double* scale;       // power of two that T was divided by
+  int64_t ld;
+  int n, team, cfg, pad;
+};
+enum { V_DK = 0, V_ZK, V_LAM, V_MU, V_DOR, V_ZH, V_DFS, V_RC, V_RS, kVec };
+enum { I_COL = 0, I_P1, I_P2, I_DFC, I_DFF, I_POS, I_RA, I_RB, I_FLAG, kIdx };
+
+struct TeamWg {
+  int prob, g;
+};
+struct BaseNode {
+  int prob, off, m;
+};
+struct Node {
+  int prob, off, n1, n2;
+};
+// What a merge's deflation leaves for its later kernels.
+struct NodeRes {
+  double rho;
+  int K, ndf, K1, K2;
+};
+
+// ------------------------------------------------------------ wave tools --
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double x) {
+  const u32x2 b = __builtin_bit_cast(u32x2, x);
+  u32x2 r;
+  r[0] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b[0], CTRL, ROWS, 0xf, false);
+  r[1] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b[1], CTRL, ROWS, 0xf, false);
+  return x + __builtin_bit_cast(double, r);
+}
+__device__ __forceinline__ double read_lane(double x, int l) {
+  const u32x2 b = __builtin_bit_cast(u32x2, x);
+  u32x2 r;
+  r[0] = (unsigned)__builtin_amdgcn_readlane((int)b[0], l);
+  r[1] = (unsigned)__builtin_amdgcn_readlane((int)b[1], l);
+  return __builtin_bit_cast(double, r);
+}
+// Sum over the 64 lanes (row shifts by 1, 2, 4, 8, then the row broadcasts), the same in every lane.
+__device__ __forceinline__ double wave_total(double x) {
+  x = dpp_add<0x111, 0xf>(x);
+  x = dpp_add<0x112, 0xf>(x);
+  x = dpp_add<0x114, 0xf>(x);
+  x = dpp_add<0x118, 0xf>(x);
+  x = dpp_add<0x142, 0xa>(x);
+  x = dpp_add<0x143, 0xc>(x);
+  return read_lane(x, 63);
+}
+__device__ __forceinline__ double quad_total(double x) {
+  x = dpp_add<0xB1, 0xf>(x);
+  return dpp_add<0x4E, 0xf>(x);
+}
+__device__ __forceinline__ double wave_max(double x) {
+  for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
+  return x;
+}
+__device__ __forceinline__ double wave_prod(double x) {
+  for (int o = 32; o > 0; o >>= 1) x *= __shfl_xor(x, o);
+  return x;
+}
+// 1 / x and 1 / sqrt(x) to about one unit in the last place (two Newton steps).
+__device__ __forceinline__ double fast_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double fast_rsqrt(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+// Workgroup barrier for LDS traffic alone: global stores stay in flight (the
+// row that one team member publishes would otherwise hold up its y by a
+// store's round trip in every column).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+// x and y each summed over half of the lanes: lanes 0..31 hold x's sums, 32..63 y's.
+__device__ __forceinline__ double swap_add32(double x, double y) {
+  const u32x2 a = __builtin_bit_cast(u32x2, x), b = __builtin_bit_cast(u32x2, y);
+  const auto l = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+  return __builtin_bit_cast(double, u32x2{l[0], h[0]}) + __builtin_bit_cast(double, u32x2{l[1], h[1]});
+}
+// The same within each half: 16-lane rows 0 and 2 hold x's sums, 1 and 3 y's.
+__device__ __forceinline__ double swap_add16(double x, double y) {
+  const u32x2 a = __builtin_bit_cast(u32x2, x), b = __builtin_bit_cast(u32x2, y);
+  const auto l = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  return __builtin_bit_cast(double, u32x2{l[0], h[0]}) + __builtin_bit_cast(double, u32x2{l[1], h[1]});
+}
+// Sums of 4 values over the 64 lanes into out[0..4): the first two steps halve
+// the values as they halve the lanes (a swap of lane halves between two
+// values, one add), the last four run within 16-lane rows.
+__device__ __forceinline__ void reduce_rows4(const double (&s)[4], double* out) {
+  const int lane = threadIdx.x & 63;
+  double z = swap_add16(swap_add32(s[0], s[1]), swap_add32(s[2], s[3]));
+  z = dpp_add<0x128, 0xf>(z);
+  z = dpp_add<0x124, 0xf>(z);
+  z = dpp_add<0x122, 0xf>(z);
+  z = dpp_add<0x121, 0xf>(z);
+  const int q = lane >> 4;
+  if ((lane & 15) == 0) out[2 * (q & 1) + (q >> 1)] = z;
+}
+
+// ------------------------------------------------------------- reduction --
+// Shared memory of a team workgroup.
+struct TriSmem {
+  double v[2][kEigTeamMax], w[2][kEigTeamMax];
+  double y[128], r[128];   // single-workgroup teams
+  double part[8][64];
+  double red[2][4][8], al[2][4];
+};
+
+__device__ __forceinline__ void publish(double* p, double x) {
+  unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+  if (b == kEmpty) b = 0x7ff8000000000000ull;
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), b, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The 16-byte slots (y, r) of a thread's columns tc + TC u, u < CU, read past
+// the L2 of this XCD (the writers are anywhere on the chip); columns outside
+// (j, n) read the nearest one inside.  All loads are waited for here.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <int CU, int TC>
+__device__ __forceinline__ void load_slots(const double* at, int j, int n, int tc, u32x4 (&x)[CU]) {
+  const double* p[6];
+#pragma unroll
+  for (int u = 0; u < CU; ++u) {
+    const int c = tc + TC * u;
+    const int cc = c <= j ? j + 1 : (c < n ? c : n - 1);
+    p[u] = at + 2 * (int64_t)(cc - tc);
+  }
+  static_assert(CU >= 1 && CU <= 6, "columns per thread");
+  if constexpr (CU == 1)
+    asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(x[0])
+                 : "v"(p[0])
+                 : "memory");
+  else if constexpr (CU == 2)
+    asm volatile(
+        "global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(x[0]), "=&v"(x[1])
+        : "v"(p[0]), "v"(p[1])
+        : "memory");
+  else if constexpr (CU == 3)
+    asm volatile(
+        "global_load_dwordx4 %0, %3, off sc1\n\tglobal_load_dwordx4 %1, %4, off sc1\n\t"
+        "global_load_dwordx4 %2, %5, off sc1\n\ts_waitcnt vmcnt(0)"
+        : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2])
+        : "v"(p[0]), "v"(p[1]), "v"(p[2])
+        : "memory");
+  else if constexpr (CU == 4)
+    asm volatile(
+        "global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+        "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3])
+        : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3])
+        : "memory");
+  else if constexpr (CU == 5)
+    asm volatile(
+        "global_load_dwordx4 %0, %5, off sc1\n\tglobal_load_dwordx4 %1, %6, off sc1\n\t"
+        "global_load_dwordx4 %2, %7, off sc1\n\tglobal_load_dwordx4 %3, %8, off sc1\n\t"
+        "global_load_dwordx4 %4, %9, off sc1\n\ts_waitcnt vmcnt(0)"
+        : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4])
+        : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4])
+        : "memory");
+  else
+    asm volatile(
+        "global_load_dwordx4 %0, %6, off sc1\n\tglobal_load_dwordx4 %1, %7, off sc1\n\t"
+        "global_load_dwordx4 %2, %8, off sc1\n\tglobal_load_dwordx4 %3, %9, off sc1\n\t"
+        "global_load_dwordx4 %4, %10, off sc1\n\tglobal_load_dwordx4 %5, %11, off sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5])
+        : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5])
+        : "memory");
+}
+
+// Polls before a wait gives up (seconds; a team is resident as a whole, so its
+// waits end).
+constexpr int kTeamSpinMax = 1 << 21;
+
+// The reduction of one matrix by a team of P.team workgroups, this one g.
+// Rows are dealt cyclically to the team's VG = team * RG row groups (RG of TC
+// lanes a workgroup), RL per group; lane tc of a group holds the columns
+// tc + TC u, so A[i][c] is a[l][u] with i = l VG + vg.
+// Iteration j, from column j of the reduced matrix A_j (col, held by every row
+// group): v (v[j+1] = 1, zero up to j), tau, beta as in dlarfg; one pass over
+// the registers applies the previous iteration's update A -= v w^T + w v^T and
+// forms y = A_j v of the group's rows; y and row j + 1 of A_j are published
+// and every group picks both up whole, forms w = tau y - (tau^2 (y . v) / 2) v
+// and the next column A_j[j+1] - v w[j+1] - w.
+// The exchange has no flags: slot (j, i) = (y_i, A_j[j+1][i]) is written once,
+// each half by its owner, starts as kEmpty, and a reader polls the slots it needs.  Every group
+// computes the same scalars from the same values in the same order.
+// Row j of A takes v_j (every group has published y_j, so it has loaded its rows).
+template <int TC, int CU, int RL>
+__device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
+  constexpr int RG = kTeamThreads / TC, NW = TC / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int rg = __builtin_amdgcn_readfirstlane(tid / TC), tc = tid % TC;
+  const int wr = __builtin_amdgcn_readfirstlane(wave % NW);
+  const int n = P.n, G = P.team, VG = G * RG, vg = g * RG + rg;
+  const int64_t ld = P.ld;
+  double* A = P.A;
+  double* YR = P.E;  // [column j][entry c][y, row j + 1]
+  double a[RL][CU], v[CU], vp[CU], wp[CU], col[CU];
+#pragma unroll
+  for (int u = 0; u < CU; ++u) {
+    const int c = tc + TC * u;
+#pragma unroll
+    for (int l = 0; l < RL; ++l) {
+      const int i = l * VG + vg;
+      a[l][u] = (i < n && c < n) ? A[i * ld + c] : 0.0;
+    }
+    col[u] = c < n ? A[c] : 0.0;
+    v[u] = vp[u] = wp[u] = 0.0;
+    if (c < n && rg == 0) sm.v[1][c] = sm.w[1][c] = 0.0;
+  }
+  if (g == 0 && tid == 0) P.d[0] = col[0];
+  bool dead = false;
+  for (int j = 0; j + 1 < n; ++j) {
+    const int par = j & 1;
+    // ---- reflector of column j ----
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const int c = tc + TC * u;
+      if (c > j + 1) s += col[u] * col[u];
+      if (c == j + 1) sm.al[0][rg] = col[u];
+    }
+    s = wave_total(s);
+    if (lane == 0) sm.red[0][rg][wr] = s;
+    lds_barrier();
+    double sig = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) sig += sm.red[0][rg][q];
+    const double alpha = sm.al[0][rg];
+    // beta = -sign(alpha) r, tau = (beta - alpha) / beta = 1 + |alpha| / r,
+    // 1 / (alpha - beta) = sign(alpha) / (|alpha| + r)
+    double tau = 0.0, beta = alpha, scale = 0.0;
+    if (sig != 0.0) {
+      const double x = alpha * alpha + sig;
+      const double ir = fast_rsqrt(x), nr = x * ir;
+      const double r = fma(fma(-nr, nr, x), 0.5 * ir, nr);
+      beta = -copysign(r, alpha);
+      tau = fma(fabs(alpha), ir, 1.0);
+      scale = copysign(fast_rcp(fabs(alpha) + r), alpha);
+    }
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const int c = tc + TC * u;
+      v[u] = c > j + 1 ? col[u] * scale : (c == j + 1 ? 1.0 : 0.0);
+      if (rg == 0 && c < n) sm.v[par][c] = v[u];
+    }
+    if (g == 0 && tid == 0) {
+      P.e[j] = beta;
+      P.tau[j] = tau;
+    }
+    // ---- previous update and y = A v on this group's rows ----
+    double rv = 0.0, rw = 0.0;  // lane l: the previous v and w at row l
+    {
+      const int i = lane * VG + vg;
+      if (lane < RL && i < n) {
+        rv = sm.v[par ^ 1][i];
+        rw = sm.w[par ^ 1][i];
+      }
+    }
+    const int lr = (j + 1) % VG == vg ? (j + 1) / VG : -1;  // this group holds row j + 1
+#pragma unroll
+    for (int k = 0; k < RL / 4; ++k) {
+      if ((4 * k + 3) * VG + vg <= j) continue;  // (a group of rows all reduced already)
+      double s4[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int l = 4 * k + q;
+        const double bv = read_lane(rv, l), bw = read_lane(rw, l);
+        double t = 0.0;
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+          a[l][u] = fma(-bv, wp[u], a[l][u]);
+          a[l][u] = fma(-bw, vp[u], a[l][u]);
+          t = fma(a[l][u], v[u], t);
+        }
+        s4[q] = t;
+      }
+      reduce_rows4(s4, sm.part[wave] + 4 * k);
+      if (lr >> 2 == k) {
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+          const int c = tc + TC * u;
+          const int q = lr & 3;
+          const double x = q == 0 ? a[4 * k][u] : (q == 1 ? a[4 * k + 1][u]
+                                                           : (q == 2 ? a[4 * k + 2][u] : a[4 * k + 3][u]));
+          if (c > j && c < n) {
+            if (G > 1)
+              publish(YR + 2 * ((int64_t)j * n + c) + 1, x);
+            else
+              sm.r[c & 127] = x;
+          }
+        }
+      }
+    }
+    lds_barrier();
+    if (tc < RL) {
+      const int i = tc * VG + vg;
+      if (i > j && i < n) {
+        double y = 0.0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) y += sm.part[rg * NW + q][tc];
+        if (G > 1)
+          publish(YR + 2 * ((int64_t)j * n + i), y);
+        else
+          sm.y[i & 127] = y;
+      }
+    }
+    // ---- y and row j + 1, whole ----
+    double y[CU], r[CU];
+    if (G == 1) {
+      lds_barrier();
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int c = tc + TC * u;
+        y[u] = c > j && c < n ? sm.y[c & 127] : 0.0;
+        r[u] = c > j && c < n ? sm.r[c & 127] : 0.0;
+      }
+    } else {
+      // (a first poll sent at once would arrive before the slowest workgroup's
+      // stores and cost a second round trip: n = 1940, 14.1 -> 12.3 ms)
+      if (CU < 6) __builtin_amdgcn_s_sleep(6);
+      u32x4 x[CU];
+      const double* at = YR + 2 * ((int64_t)j * n + tc);
+      for (int spins = 0;; ++spins) {
+        load_slots<CU, TC>(at, j, n, tc, x);
+        bool all = true;
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+          const int c = tc + TC * u;
+          if (c > j && c < n) all = all && (x[u][0] & x[u][1]) != ~0u && (x[u][2] & x[u][3]) != ~0u;
+        }
+        if (all || dead) break;
+        if (spins > kTeamSpinMax) {
+          dead = true;
+          atomicOr(err, 1);
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int c = tc + TC * u;
+        const bool in = c > j && c < n;
+        y[u] = in ? __builtin_bit_cast(double, u32x2{x[u][0], x[u][1]}) : 0.0;
+        r[u] = in ? __builtin_bit_cast(double, u32x2{x[u][2], x[u][3]}) : 0.0;
+      }
+    }
+    if (j % G == g && rg == 0) {
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int c = tc + TC * u;
+        if (c < n) A[j * ld + c] = v[u];
+      }
+    }
+    // ---- w and the next column ----
+    double yv = 0.0;
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const int c = tc + TC * u;
+      yv += y[u] * v[u];
+      if (c == j + 1) sm.al[1][rg] = y[u];
+    }
+    yv = wave_total(yv);
+    if (lane == 0) sm.red[1][rg][wr] = yv;
+    lds_barrier();
+    yv = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) yv += sm.red[1][rg][q];
+    const double kap = 0.5 * tau * tau * yv;
+    const double w1 = tau * sm.al[1][rg] - kap;
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const int c = tc + TC * u;
+      const double w = c > j && c < n ? tau * y[u] - kap * v[u] : 0.0;
+      if (rg == 0 && c < n) sm.w[par][c] = w;
+      col[u] = c > j && c < n ? r[u] - v[u] * w1 - w : 0.0;
+      if (c == j + 1 && g == 0 && rg == 0) P.d[j + 1] = col[u];
+      vp[u] = v[u];
+      wp[u] = w;
+    }
+  }
+}
+
+// Row capacity of a workgroup and column capacity of each shape (RG RL rows,
+// TC CU columns).
+struct TeamShape {
+  int rows, cols;
+};
+constexpr TeamShape kTeamShapes[] = {
+    {128, 128}, {64, 256}, {16, 512}, {64, 512}, {16, 1024}, {40, 1024}, {12, 1536},
+    {28, 1536}, {8, 2048}, {20, 2048}, {12, 2560}, {12, 3072}, {16, 2048}, {12, 2048},
+};
+__global__ __launch_bounds__(kTeamThreads, 2) void k_tri_team(const EigDev* __restrict__ P,
+                                                              const TeamWg* __restrict__ wg,
+                                                              int* __restrict__ err) {
+  __shared__ TriSmem sm;
+  const TeamWg t = wg[blockIdx.x];
+  const EigDev p = P[t.prob];
+  switch (p.cfg) {
+    case 0: tri_team<128, 1, 32>(p, t.g, sm, err); break;
+    case 1: tri_team<256, 1, 32>(p, t.g, sm, err); break;
+    case 2: tri_team<512, 1, 16>(p, t.g, sm, err); break;
+    case 3: tri_team<512, 1, 64>(p, t.g, sm, err); break;
+    case 4: tri_team<512, 2, 16>(p, t.g, sm, err); break;
+    case 5: tri_team<512, 2, 40>(p, t.g, sm, err); break;
+    case 6: tri_team<512, 3, 12>(p, t.g, sm, err); break;
+    case 7: tri_team<512, 3, 28>(p, t.g, sm, err); break;
+    case 8: tri_team<512, 4, 8>(p, t.g, sm, err); break;
+    case 9: tri_team<512, 4, 20>(p, t.g, sm, err); break;
+    case 10: tri_team<512, 5, 12>(p, t.g, sm, err); break;
+    case 11: tri_team<512, 6, 12>(p, t.g, sm, err); break;
+    case 12: tri_team<512, 4, 16>(p, t.g, sm, err); break;
+    default: tri_team<512, 4, 12>(p, t.g, sm, err); break;
+  }
+}
+
+__global__ void k_eig_clear_err(int* err) {
+  if (threadIdx.x == 0) *err = 0;
+}
+
+// kEmpty into the exchange slots of every problem (blockIdx.y) solved by more than one workgroup.
+__global__ void k_tri_clear(const EigDev* __restrict__ P) {
+  const EigDev& p = P[blockIdx.y];
+  if (p.team <= 1) return;
+  const int64_t nn = (int64_t)p.n * p.n, step = (int64_t)gridDim.x * blockDim.x;
+  ulonglong2* x = reinterpret_cast<ulonglong2*>(p.E);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += step)
+    x[i] = ulonglong2{kEmpty, kEmpty};
+}
+
+// ------------------------------------------------------ divide and conquer --
+// T divided by the power of two of its largest entry (one workgroup a problem).
+__global__ __launch_bounds__(256) void k_dc_scale(const EigDev* __restrict__ P) {
+  __shared__ double red[4];
+  const EigDev& p = P[blockIdx.x];
+  double m = 0.0;
+  for (int i = threadIdx.x; i < p.n; i += 256) {
+    m = fmax(m, fabs(p.d[i]));
+    if (i + 1 < p.n) m = fmax(m, fabs(p.e[i]));
+  }
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  int ex = 0;
+  if (m > 0.0 && isfinite(m)) (void)frexp(m, &ex);
+  for (int i = threadIdx.x; i < p.n; i += 256) {
+    p.d[i] = ldexp(p.d[i], -ex);
+    if (i + 1 < p.n) p.e[i] = ldexp(p.e[i], -ex);
+  }
+  if (threadIdx.x == 0) *p.scale = ldexp(1.0, ex);
+}
+
+// Root of the secular equation j of K (poles d ascending, weights z), by W
+// lanes (4 or 64) that each sum every W-th term: the origin pole's index, mu
+// (the root less that pole).  `total` sums a value over the W lanes.
+template <int W, class F>
+__device__ __forceinline__ void secular_root(const double* d, const double* z, int K, double rho,
+                                             int j, int lane, F total, int& org, double& mu) {
+  double a, b;
+  int o;
+  if (j < K - 1) {
+    const double dj = d[j], half = 0.5 * (d[j + 1] - dj);
+    double s = 0.0;
+    for (int i = lane; i < K; i += W) s += z[i] * z[i] * fast_rcp((d[i] - dj) - half);
+    s = total(s);
+    if (1.0 + rho * s >= 0.0) {
+      o = j;
+      a = 0.0;
+      b = half;
+    } else {
+      o = j + 1;
+      a = -half;
+      b = 0.0;
+    }
+  } else {
+    o = j;
+    a = 0.0;
+    b = rho;
+  }
+  const double d_o = d[o], z_o2 = z[o] * z[o];
+  // f(mu) increases from -inf to +inf over the bracket; h(mu) = mu f(mu) has
+  // no pole at mu = 0
+  double m = 0.5 * (a + b);
+  for (int it = 0; it < 128; ++it) {
+    double S = 0.0, Sp = 0.0;
+    for (int i = lane; i < K; i += W) {
+      const double dl = d[i] - d_o;
+      const double r = i == o ? 0.0 : fast_rcp(dl - m);
+      const double q = z[i] * z[i] * r;
+      S += q;
+      Sp = fma(q * dl, r, Sp);
+    }
+    S = total(S);
+    Sp = total(Sp);
+    const double h = m * (1.0 + rho * S) - rho * z_o2;
+    const bool fneg = m > 0.0 ? h < 0.0 : h > 0.0;
+    if (fneg) a = m; else b = m;
+    double mn = m - h / (1.0 + rho * Sp);
+    if (!(mn > a && mn < b)) mn = 0.5 * (a + b);
+    const bool done = fabs(mn - m) <= 2.0 * __DBL_EPSILON__ * fabs(mn) ||
+                      !(b - a > 2.0 * __DBL_EPSILON__ * fmax(fabs(a), fabs(b)));
+    m = mn;
+    if (done) break;
+  }
+  org = o;
+  mu = m;
+}
+
+// Factor j of zh_i^2 (see eigdc.hip): lambda_j - d_i over the pole difference
+// that interlaces with it.
+__device__ __forceinline__ double zhat_factor(const double* d, int K, double rho, int i, int j,
+                                              double dor_j, double mu_j) {
+  const double di = d[i];
+  const double lj = (dor_j - di) + mu_j;
+  const double den = j < i ? d[j] - di : (j < K - 1 ? d[j + 1] - di : rho);
+  return lj / den;
+}
+
+// Number of entries of the ascending v[0..len) below x, or not above it.
+__device__ __forceinline__ int dc_count(const double* v, int len, double x, bool or_equal) {
+  int lo = 0, hi = len;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    const bool below = or_equal ? v[mid] <= x : v[mid] < x;
+    if (below) lo = mid + 1; else hi = mid;
+  }
+  return lo;
+}
+
+// Serial deflation of n sorted poles ds with unit weights zs (one thread): the
+// non-deflated positions nd[0..K) with values dk, zk, the deflated positions
+// df with values dfv, the rotations (ra, rb, rc, rs) in order.  Returns K.
+__device__ int dc_deflate_serial(const double* ds, const double* zs, int n, double rho, double tol,
+                                 int* nd, double* dk, double* zk, int* df, double* dfv, int* ra,
+                                 int* rb, double* rc, double* rs, int* nrot) {
+  int K = 0, ndf = 0, nr = 0, prev = -1;
+  double dp = 0.0, zp = 0.0;
+  for (int j = 0; j < n; ++j) {
+    const double dj = ds[j], zj = zs[j];
+    if (rho * fabs(zj) <= tol) {
+      df[ndf] = j;
+      dfv[ndf++] = dj;
+      continue;
+    }
+    if (prev >= 0) {
+      const double t = sqrt(zp * zp + zj * zj);
+      const double cc = zj / t, ss = zp / t;
+      if (fabs((dj - dp) * cc * ss) <= tol) {
+        ra[nr] = prev;
+        rb[nr] = j;
+        rc[nr] = cc;
+        rs[nr++] = ss;
+        df[ndf] = prev;
+        dfv[ndf++] = dp * cc * cc + dj * ss * ss;
+        prev = j;
+        dp = dp * ss * ss + dj * cc * cc;
+        zp = t;
+        continue;
+      }
+      nd[K] = prev;
+      dk[K] = dp;
+      zk[K++] = zp;
+    }
+    prev = j;
+    dp = dj;
+    zp = zj;
+  }
+  if (prev >= 0) {
+    nd[K] = prev;
+    dk[K] = dp;
+    zk[K++] = zp;
+  }
+  *nrot = nr;
+  return K;
+}
+
+// ---- blocks of up to 64 rows in one workgroup ----
+struct BaseSmem {
+  double E[kBase][kBase + 1], E2[kBase][kBase + 1], U[kBase][kBase + 1];  // [column][row]
+  double D[kBase], ds[kBase], zs[kBase], dk[kBase], zk[kBase], mu[kBase], dor[kBase], zh[kBase],
+      dfv[kBase], rc[kBase], rs[kBase], lam[kBase];
+  int src[kBase], nd[kBase], df[kBase], ra[kBase], rb[kBase], pos[kBase], K[4], nrot[4];
+  double rho[4];
+};
+
+// Implicit QL with eigenvectors of the tridiagonal leaf D[b..b+m), off-diagonals
+// eo (lane i: d_i, and e_i between i and i + 1) by one wave, lane r row r of
+// the leaf's block of E; eigenvalues ascending into D.  Returns false if an
+// eigenvalue does not converge.
+__device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
+  const int lane = threadIdx.x & 63;
+  bool ok = true;
+  for (int l = 0; l < m; ++l) {
+    for (int it = 0;; ++it) {
+      int q = l;
+      for (; q + 1 < m; ++q) {
+        const double dd = fabs(read_lane(d, q)) + fabs(read_lane(d, q + 1));
+        if (fabs(read_lane(e, q)) <= __DBL_EPSILON__ * dd) break;
+      }
+      if (q == l) break;
+      if (it >= 60) {
+        ok = false;
+        break;
+      }
+      const double dl = read_lane(d, l), el = read_lane(e, l);
+      double gg = (read_lane(d, l + 1) - dl) / (2.0 * el);
+      double r = sqrt(gg * gg + 1.0);
+      gg = read_lane(d, q) - dl + el / (gg + copysign(r, gg));
+      double s = 1.0, c = 1.0, p = 0.0;
+      int i = q - 1;
+      for (; i >= l; --i) {
+        const double ei = read_lane(e, i);
+        const double f = s * ei, bb = c * ei;
+        r = sqrt(f * f + gg * gg);
+        if (lane == i + 1) e = r;
+        if (r == 0.0) {
+          if (lane == i + 1) d -= p;
+          if (lane == q) e = 0.0;
+          break;
+        }
+        const double ri = 1.0 / r;
+        s = f * ri;
+        c = gg * ri;
+        gg = read_lane(d, i + 1) - p;
+        r = (read_lane(d, i) - gg) * s + 2.0 * c * bb;
+        p = s * r;
+        if (lane == i + 1) d = gg + p;
+        gg = c * r - bb;
+        if (lane < m) {
+          const double z1 = sm.E[b + i + 1][b + lane], z0 = sm.E[b + i][b + lane];
+          sm.E[b + i + 1][b + lane] = s * z0 + c * z1;
+          sm.E[b + i][b + lane] = c * z0 - s * z1;
+        }
+      }
+      if (r == 0.0 && i >= l) continue;
+      if (lane == l) {
+        d -= p;
+        e = gg;
+      }
+      if (lane == q) e = 0.0;
+    }
+  }
+  int rank = 0;
+  for (int k = 0; k < m; ++k) {
+    const double dk = read_lane(d, k);
+    rank += (dk < d || (dk == d && k < lane)) ? 1 : 0;
+  }
+  if (lane < m) sm.D[b + rank] = d;
+  for (int k = 0; k < m; ++k) {
+    const int rk = __builtin_amdgcn_readlane(rank, k);
+    if (lane < m) sm.E2[b + rk][b + lane] = sm.E[b + k][b + lane];
+  }
+  for (int k = 0; k < m; ++k)
+    if (lane < m) sm.E[b + k][b + lane] = sm.E2[b + k][b + lane];
+  return ok;
+}
+
+// Merge of D[o..o+m1) and D[o+m1..o+m1+m2) (each ascending, eigenvectors in
+// the columns of E) by the TS threads of a team, rank tr; `team` numbers the
+// teams of the workgroup, all of which call together.  m1 = 0: nothing to do.
+template <int TS>
+__device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2, double beta) {
+  const int m = m1 + m2;
+  if (tr < m) {
+    const double sg = beta < 0.0 ? -1.0 : 1.0;
+    const double val = sm.D[o + tr];
+    int pos;
+    double z;
+    if (tr < m1) {
+      pos = tr + dc_count(sm.D + o + m1, m2, val, false);
+      z = sm.E[o + tr][o + m1 - 1];
+    } else {
+      pos = tr - m1 + dc_count(sm.D + o, m1, val, true);
+      z = sg * sm.E[o + tr][o + m1];
+    }
+    sm.ds[o + pos] = val;
+    sm.zs[o + pos] = z;
+    sm.src[o + pos] = o + tr;
+  }
+  __syncthreads();
+  if (tr == 0) {
+    double s2 = 0.0, dm = 0.0;
+    for (int i = 0; i < m; ++i) {
+      s2 += sm.zs[o + i] * sm.zs[o + i];
+      dm = fmax(dm, fabs(sm.ds[o + i]));
+    }
+    const double zi = m > 0 ? 1.0 / sqrt(s2) : 0.0;
+    for (int i = 0; i < m; ++i) sm.zs[o + i] *= zi;
+    const double rho = fabs(beta) * s2;
+    const double tol = 8.0 * __DBL_EPSILON__ * fmax(dm, rho);
+    sm.rho[team] = rho;
+    sm.K[team] = dc_deflate_serial(sm.ds + o, sm.zs + o, m, rho, tol, sm.nd + o, sm.dk + o,
+                                   sm.zk + o, sm.df + o, sm.dfv + o, sm.ra + o, sm.rb + o,
+                                   sm.rc + o, sm.rs + o, &sm.nrot[team]);
+  }
+  __syncthreads();
+  const int K = sm.K[team], ndf = m - K, nrot = sm.nrot[team];
+  const double rho = sm.rho[team];
+  if (tr < m)
+    for (int q = 0; q < nrot; ++q) {
+      double* xa = &sm.E[sm.src[o + sm.ra[o + q]]][o + tr];
+      double* xb = &sm.E[sm.src[o + sm.rb[o + q]]][o + tr];
+      const double a = *xa, b = *xb, c = sm.rc[o + q], s = sm.rs[o + q];
+      *xa = c * a - s * b;
+      *xb = s * a + c * b;
+    }
+  // roots, four lanes each (TS >= 4 m)
+  const int j = tr >> 2, ql = tr & 3;
+  if (j < K) {
+    int org;
+    double mu;
+    secular_root<4>(sm.dk + o, sm.zk + o, K, rho, j, ql, [](double x) { return quad_total(x); },
+                    org, mu);
+    if (ql == 0) {
+      sm.mu[o + j] = mu;
+      sm.dor[o + j] = sm.dk[o + org];
+      sm.lam[o + j] = sm.dk[o + org] + mu;
+    }
+  }
+  __syncthreads();
+  if (j < K) {
+    double p = 1.0;
+    for (int q = ql; q < K; q += 4)
+      p *= zhat_factor(sm.dk + o, K, rho, j, q, sm.dor[o + q], sm.mu[o + q]);
+    p *= __shfl_xor(p, 1);
+    p *= __shfl_xor(p, 2);
+    if (ql == 0) sm.zh[o + j] = copysign(sqrt(p), sm.zk[o + j]);
+  }
+  __syncthreads();
+  if (j < K) {
+    const double dj = sm.dor[o + j], mu = sm.mu[o + j];
+    double s2 = 0.0;
+    for (int i = ql; i < K; i += 4) {
+      const double u = sm.zh[o + i] / ((sm.dk[o + i] - dj) - mu);
+      sm.U[o + j][o + i] = u;
+      s2 += u * u;
+    }
+    s2 = quad_total(s2);
+    const double inv = 1.0 / sqrt(s2);
+    for (int i = ql; i < K; i += 4) sm.U[o + j][o + i] *= inv;
+  }
+  // final positions: roots j < K, then deflated values (rank by counting)
+  if (tr < m) {
+    double val;
+    int pos;
+    if (tr < K) {
+      val = sm.lam[o + tr];
+      pos = tr;
+      for (int q = 0; q < ndf; ++q) pos += sm.dfv[o + q] < val ? 1 : 0;
+    } else {
+      const int q0 = tr - K;
+      val = sm.dfv[o + q0];
+      pos = dc_count(sm.lam + o, K, val, true);
+      for (int q = 0; q < ndf; ++q)
+        pos += (sm.dfv[o + q] < val || (sm.dfv[o + q] == val && q < q0)) ? 1 : 0;
+    }
+    sm.pos[o + tr] = o + pos;
+    sm.D[o + pos] = val;  // (the old values were last read before the secular step)
+  }
+  __syncthreads();
+  // E2[pos] = sum_i E[src(nd_i)] U[root][i]: a 4 x 4 block of (root, row) per
+  // thread for m = 64 and TS = 256 (rows tr % 16, + 16, ..)
+  {
+    constexpr int NR = 16, NJ = TS / NR;
+    const int r0 = tr % NR, j0 = tr / NR;
+    for (int jb = j0; jb < m; jb += NJ) {
+      const int at = sm.pos[o + jb];
+      if (jb < K) {
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int i = 0; i < K; ++i) {
+          const double u = sm.U[o + jb][o + i];
+          const double* ec = sm.E[sm.src[o + sm.nd[o + i]]] + o;
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (r0 + NR * q < m) acc[q] = fma(ec[r0 + NR * q], u, acc[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (r0 + NR * q < m) sm.E2[at][o + r0 + NR * q] = acc[q];
+      } else {
+        const double* ec = sm.E[sm.src[o + sm.df[o + jb - K]]] + o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (r0 + NR * q < m) sm.E2[at][o + r0 + NR * q] = ec[r0 + NR * q];
+      }
+    }
+  }
+  __syncthreads();
+  for (int e = tr; e < m * m; e += TS) {
+    const int c = e / m, r = e - c * m;
+    sm.E[o + c][o + r] = sm.E2[o + c][o + r];
+  }
+  __syncthreads();
+}
+
+// One workgroup per block of up to 64 rows: eigenvalues (ascending) over the
+// block of d, eigenvectors into the block of E.  Latency: the leaves' chain of
+// about 1.5 m^2 rotations (a square root and two divisions each) and two
+// merges; 16-row leaves keep that chain short, below them the merges' fixed
+// cost is larger than the rotations saved.
+__global__ __launch_bounds__(256) void k_dc_base(const EigDev* __restrict__ P,
+                                                 const BaseNode* __restrict__ nodes,
+                                                 int* __restrict__ err) {
+  __shared__ BaseSmem sm;
+  const BaseNode nd = nodes[blockIdx.x];
+  const EigDev& p = P[nd.prob];
+  const int n = p.n, off = nd.off, m = nd.m, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // leaf boundaries b[0..nl]
+  const int nl = m > 2 * kLeaf ? 4 : (m > kLeaf ? 2 : 1);
+  const int h = nl > 1 ? m / 2 : m;
+  const int q1 = nl == 4 ? h / 2 : h, q2 = nl == 4 ? h + (m - h) / 2 : m;
+  for (int e = tid; e < kBase * kBase; e += 256) sm.E[e / kBase][e % kBase] = e / kBase == e % kBase ? 1.0 : 0.0;
+  __syncthreads();
+  auto edge = [&](int r) -> double {  // |off-diagonal| between rows r - 1 and r of T
+    return r > 0 && r < n ? fabs(p.e[r - 1]) : 0.0;
+  };
+  if (wave < nl) {
+    // four leaves: [0,q1) [q1,h) [h,q2) [q2,m); two: [0,h) [h,m); one: [0,m)
+    int b0, b1;
+    if (nl == 4) {
+      b0 = wave == 0 ? 0 : (wave == 1 ? q1 : (wave == 2 ? h : q2));
+      b1 = wave == 0 ? q1 : (wave == 1 ? h : (wave == 2 ? q2 : m));
+    } else {
+      b0 = wave == 0 ? 0 : h;
+      b1 = wave == 0 && nl == 2 ? h : m;
+    }
+    const int lm = b1 - b0;
+    double d = 0.0, e = 0.0;
+    if (lane < lm) {
+      d = p.d[off + b0 + lane];
+      if (lane == 0) d -= edge(off + b0);
+      if (lane == lm - 1) d -= edge(off + b1);
+      if (lane + 1 < lm) e = p.e[off + b0 + lane];
+    }
+    if (!ql_leaf(sm, b0, lm, d, e) && lane == 0) atomicOr(err, 2);
+  }
+  __syncthreads();
+  if (nl == 4) {
+    const int team = tid >> 7, tr = tid & 127;
+    const int o = team ? h : 0, m1 = team ? q2 - h : q1, m2 = team ? m - q2 : h - q1;
+    base_merge<128>(sm, team, tr, o, m1, m2, p.e[off + o + m1 - 1]);
+  }
+  if (nl > 1) base_merge<256>(sm, 0, tid, 0, h, m - h, p.e[off + h - 1]);
+  for (int e = tid; e < m * m; e += 256) {
+    const int c = e / m, r = e - c * m;
+    p.E[(int64_t)(off + c) * n + off + r] = sm.E[c][r];
+  }
+  if (tid < m) p.d[off + tid] = sm.D[tid];
+}
+
+// ---- merges of larger blocks, every node of a level in the same launches ----
+// Node of global index q of the level (pre: first index of each node).
+__device__ __forceinline__ int node_of(const int* pre, int nn, int q) {
+  int lo = 0, hi = nn - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (pre[mid] <= q) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// E[off + pos[m]][off + n] (column-major columns): the new eigenvectors.
+struct EpiEigCols {
+  double* E;
+  int64_t ld;
+  const int* pos;
+  __device__ __forceinline__ void operator()(int64_t, int64_t, int64_t m, int64_t n, double v,
+                                             bool) const {
+    E[pos[m] * ld + n] = v;
+  }
+};
+typedef GemmJob<Strided<true>, Strided<false>, EpiEigCols> JobMerge;
+
+constexpr int kPrepThreads = 1024;
+struct PrepSmem {
+  double ds[kEigTeamMax], zs[kEigTeamMax];
+  int src[kEigTeamMax], S[kEigTeamMax];
+  double red[2][16];
+  int wsum[16], any, K, nrot;
+};
+// Exclusive sum of v over the workgroup's threads; *total the whole sum.
+__device__ int block_scan(int v, int* wsum, int* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  int x = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(x, o);
+    if (lane >= o) x += t;
+  }
+  __syncthreads();
+  if (lane == 63) wsum[w] = x;
+  __syncthreads();
+  int base = 0, all = 0;
+  for (int q = 0; q < nw; ++q) {
+    if (q < w) base += wsum[q];
+    all += wsum[q];
+  }
+  *total = all;
+  return base + x - v;
+}
+
+// Sorting and deflation of one node (one workgroup): the poles of both halves
+// merged, small weights and, where two neighbouring poles are close, rotated
+// ones deflated (the serial walk runs only then), the index maps of the later
+// kernels, and the sizes of the node's two products.
+__global__ __launch_bounds__(kPrepThreads) void k_dc_prep(const EigDev* __restrict__ P,
+                                                          const Node* __restrict__ nodes,
+                                                          NodeRes* __restrict__ res,
+                                                          JobMerge* __restrict__ jobs) {
+  __shared__ PrepSmem sm;
+  const Node nd = nodes[blockIdx.x];
+  const EigDev& p = P[nd.prob];
+  const int N = p.n, off = nd.off, n1 = nd.n1, n = nd.n1 + nd.n2;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const double* d = p.d + off;
+  double* vec = p.vec + off;
+  int* idx = p.idx + off;
+  const double beta = p.e[off + n1 - 1];
+  const double sg = beta < 0.0 ? -1.0 : 1.0;
+  double s2 = 0.0, dm = 0.0;
+  for (int t = tid; t < n; t += kPrepThreads) {
+    const double val = d[t];
+    const double* Ec = p.E + (int64_t)(off + t) * N + off;
+    int pos;
+    double z;
+    if (t < n1) {
+      pos = t + dc_count(d + n1, n - n1, val, false);
+      z = Ec[n1 - 1];
+    } else {
+      pos = t - n1 + dc_count(d, n1, val, true);
+      z = sg * Ec[n1];
+    }
+    sm.ds[pos] = val;
+    sm.zs[pos] = z;
+    sm.src[pos] = t;
+    s2 += z * z;
+    dm = fmax(dm, fabs(val));
+  }
+  s2 = wave_total(s2);
+  dm = wave_max(dm);
+  if (lane == 0) {
+    sm.red[0][w] = s2;
+    sm.red[1][w] = dm;
+  }
+  if (tid == 0) sm.any = 0;
+  __syncthreads();
+  s2 = 0.0;
+  for (int q = 0; q < kPrepThreads / 64; ++q) {
+    s2 += sm.red[0][q];
+    dm = fmax(dm, sm.red[1][q]);
+  }
+  const double zi = 1.0 / sqrt(s2);
+  const double rho = fabs(beta) * s2;
+  const double tol = 8.0 * __DBL_EPSILON__ * fmax(dm, rho);
+  // survivors of the weight test, in order
+  const int per = (n + kPrepThreads - 1) / kPrepThreads;
+  const int t0 = tid * per, t1 = min(t0 + per, n);
+  int cnt = 0;
+  for (int t = t0; t < t1; ++t) {
+    sm.zs[t] *= zi;
+    cnt += rho * fabs(sm.zs[t]) > tol ? 1 : 0;
+  }
+  int ns = 0;
+  int at = block_scan(cnt, sm.wsum, &ns);
+  for (int t = t0; t < t1; ++t) {
+    if (rho * fabs(sm.zs[t]) > tol)
+      sm.S[at++] = t;
+    else {
+      vec[V_DFS * N + t - at] = sm.ds[t];
+      idx[I_DFC * N + t - at] = sm.src[t];
+      idx[I_DFF * N + t - at] = sm.src[t] < n1 ? 1 : 2;
+    }
+    idx[I_FLAG * N + t] = t < n1 ? 1 : 2;
+  }
+  __syncthreads();
+  bool close = false;
+  for (int k = tid; k + 1 < ns; k += kPrepThreads) {
+    const int a = sm.S[k], b = sm.S[k + 1];
+    const double zp = sm.zs[a], zj = sm.zs[b];
+    const double t = sqrt(zp * zp + zj * zj);
+    if (fabs((sm.ds[b] - sm.ds[a]) * (zj / t) * (zp / t)) <= tol) close = true;
+  }
+  if (close) sm.any = 1;
+  __syncthreads();
+  int K = ns;
+  if (!sm.any) {
+    for (int k = tid; k < K; k += kPrepThreads) {
+      vec[V_DK * N + k] = sm.ds[sm.S[k]];
+      vec[V_ZK * N + k] = sm.zs[sm.S[k]];
+    }
+  } else {
+    // close poles: the serial walk, then its rotations on the columns of E
+    // (a column that meets one of the other half gets its missing half as zeros)
+    double *dfv = vec + V_LAM * N, *rc = vec + V_RC * N, *rs = vec + V_RS * N;
+    int *df = idx + I_POS * N, *ra = idx + I_RA * N, *rb = idx + I_RB * N;
+    if (tid == 0) {
+      int nrot = 0;
+      sm.K = dc_deflate_serial(sm.ds, sm.zs, n, rho, tol, sm.S, vec + V_DK * N, vec + V_ZK * N, df,
+                               dfv, ra, rb, rc, rs, &nrot);
+      sm.nrot = nrot;
+    }
+    __threadfence_block();
+    __syncthreads();
+    K = sm.K;
+    int* flag = idx + I_FLAG * N;
+    for (int q = 0; q < sm.nrot; ++q) {
+      const int ca = sm.src[ra[q]], cb = sm.src[rb[q]];
+      const int fa = flag[ca], fb = flag[cb];
+      double* xa = p.E + (int64_t)(off + ca) * N + off;
+      double* xb = p.E + (int64_t)(off + cb) * N + off;
+      const double c = rc[q], s = rs[q];
+      __syncthreads();
+      for (int r = tid; r < n; r += kPrepThreads) {
+        const int bit = r < n1 ? 1 : 2;
+        if (!((fa | fb) & bit)) continue;
+        const double a = fa & bit ? xa[r] : 0.0, b = fb & bit ? xb[r] : 0.0;
+        xa[r] = c * a - s * b;
+        xb[r] = s * a + c * b;
+      }
+      if (tid == 0) flag[ca] = flag[cb] = fa | fb;
+      __threadfence_block();
+      __syncthreads();
+    }
+    const int ndf = n - K;
+    for (int q = tid; q < ndf; q += kPrepThreads) {
+      const double val = dfv[q];
+      int r = 0;
+      for (int k = 0; k < ndf; ++k) r += (dfv[k] < val || (dfv[k] == val && k < q)) ? 1 : 0;
+      const int col = sm.src[df[q]];
+      vec[V_DFS * N + r] = val;
+      idx[I_DFC * N + r] = col;
+      idx[I_DFF * N + r] = flag[col];
+    }
+    __syncthreads();
+  }
+  // columns of the non-deflated poles, and their places among those with an
+  // upper and with a lower part
+  const int perk = (K + kPrepThreads - 1) / kPrepThreads;
+  const int k0 = tid * perk, k1 = min(k0 + perk, K);
+  int K1 = 0, K2 = 0;
+  for (int half = 1; half <= 2; ++half) {
+    int c2 = 0;
+    for (int k = k0; k < k1; ++k) c2 += idx[I_FLAG * N + sm.src[sm.S[k]]] & half ? 1 : 0;
+    int tot = 0;
+    int pos = block_scan(c2, sm.wsum, &tot);
+    for (int k = k0; k < k1; ++k) {
+      const int col = sm.src[sm.S[k]];
+      if (half == 1) idx[I_COL * N + k] = col;
+      idx[(half == 1 ? I_P1 : I_P2) * N + k] = idx[I_FLAG * N + col] & half ? pos++ : -1;
+    }
+    if (half == 1) K1 = tot; else K2 = tot;
+  }
+  if (tid == 0) {
+    res[blockIdx.x] = NodeRes{rho, K, n - K, K1, K2};
+    JobMerge& u = jobs[2 * blockIdx.x];
+    JobMerge& l = jobs[2 * blockIdx.x + 1];
+    u.M = u.a.rows = l.M = l.a.rows = K;
+    u.K = u.kchunk = K1;
+    l.K = l.kchunk = K2;
+    l.a.p = u.a.p + K1;
+  }
+}
+
+// Gathered columns (workgroups [0, cols), one per column of a node) and secular
+// roots (the others, four waves each one root).
+__global__ __launch_bounds__(256) void k_dc_roots(const EigDev* __restrict__ P,
+                                                  const Node* __restrict__ nodes, int nn,
+                                                  const int* __restrict__ pre,
+                                                  const int* __restrict__ preq, int cols,
+                                                  const NodeRes* __restrict__ res) {
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x < cols) {
+    const int ni = node_of(pre, nn, blockIdx.x);
+    const Node nd = nodes[ni];
+    const EigDev& p = P[nd.prob];
+    const int N = p.n, off = nd.off, n1 = nd.n1, n = nd.n1 + nd.n2, t = blockIdx.x - pre[ni];
+    const int K = res[ni].K;
+    const int* idx = p.idx + off;
+    double* Bc = p.B + (int64_t)off * N + off;
+    if (t < K) {
+      const double* Ec = p.E + (int64_t)(off + idx[I_COL * N + t]) * N + off;
+      const int a = idx[I_P1 * N + t], b = idx[I_P2 * N + t];
+      if (a >= 0)
+        for (int r = tid; r < n1; r += 256) Bc[(int64_t)a * N + r] = Ec[r];
+      if (b >= 0)
+        for (int r = n1 + tid; r < n; r += 256) Bc[(int64_t)b * N + r] = Ec[r];
+    } else {
+      const double* Ec = p.E + (int64_t)(off + idx[I_DFC * N + t - K]) * N + off;
+      const int f = idx[I_DFF * N + t - K];
+      for (int r = tid; r < n; r += 256) Bc[(int64_t)t * N + r] = f & (r < n1 ? 1 : 2) ? Ec[r] : 0.0;
+    }
+    return;
+  }
+  const int q = blockIdx.x - cols;
+  const int ni = node_of(preq, nn, q);
+  const Node nd = nodes[ni];
+  const EigDev& p = P[nd.prob];
+  const int j = 4 * (q - preq[ni]) + (tid >> 6), K = res[ni].K, N = p.n;
+  if (j >= K) return;
+  double* vec = p.vec + nd.off;
+  int org;
+  double mu;
+  secular_root<64>(vec + V_DK * N, vec + V_ZK * N, K, res[ni].rho, j, tid & 63,
+                   [](double x) { return wave_total(x); }, org, mu);
+  if ((tid & 63) == 0) {
+    const double dor = vec[V_DK * N + org];
+    vec[V_MU * N + j] = mu;
+    vec[V_DOR * N + j] = dor;
+    vec[V_LAM * N + j] = dor + mu;
+  }
+}
+
+// Recomputed weights, one wave each.
+__global__ __launch_bounds__(256) void k_dc_weights(const EigDev* __restrict__ P,
+                                                    const Node* __restrict__ nodes, int nn,
+                                                    const int* __restrict__ preq,
+                                                    const NodeRes* __restrict__ res) {
+  const int ni = node_of(preq, nn, blockIdx.x);
+  const Node nd = nodes[ni];
+  const EigDev& p = P[nd.prob];
+  const int i = 4 * ((int)blockIdx.x - preq[ni]) + (threadIdx.x >> 6), K = res[ni].K, N = p.n;
+  if (i >= K) return;
+  double* vec = p.vec + nd.off;
+  double q = 1.0;
+  for (int j = threadIdx.x & 63; j < K; j += 64)
+    q *= zhat_factor(vec + V_DK * N, K, res[ni].rho, i, j, vec[V_DOR * N + j], vec[V_MU * N + j]);
+  q = wave_prod(q);
+  if ((threadIdx.x & 63) == 0) vec[V_ZH * N + i] = copysign(sqrt(q), vec[V_ZK * N + i]);
+}
+
+// Eigenvectors of the merged matrix, one workgroup per column of a node: the
+// unit vector of root t split into its parts on the upper and the lower
+// columns (rows of U), or the deflated column copied to its place; the
+// eigenvalue into the node's d.
+__global__ __launch_bounds__(256) void k_dc_vecs(const EigDev* __restrict__ P,
+                                                 const Node* __restrict__ nodes, int nn,
+                                                 const int* __restrict__ pre,
+                                                 const NodeRes* __restrict__ res) {
+  __shared__ double red[4];
+  const int ni = node_of(pre, nn, blockIdx.x);
+  const Node nd = nodes[ni];
+  const EigDev& p = P[nd.prob];
+  const int N = p.n, off = nd.off, n = nd.n1 + nd.n2, t = blockIdx.x - pre[ni], tid = threadIdx.x;
+  const int K = res[ni].K, ndf = res[ni].ndf, K1 = res[ni].K1;
+  double* vec = p.vec + off;
+  int* idx = p.idx + off;
+  if (t < K) {
+    const double dor = vec[V_DOR * N + t], mu = vec[V_MU * N + t];
+    const double *dk = vec + V_DK * N, *zh = vec + V_ZH * N;
+    double s2 = 0.0;
+    for (int i = tid; i < K; i += 256) {
+      const double u = zh[i] / ((dk[i] - dor) - mu);
+      s2 += u * u;
+    }
+    s2 = wave_total(s2);
+    if ((tid & 63) == 0) red[tid >> 6] = s2;
+    __syncthreads();
+    const double inv = 1.0 / sqrt(red[0] + red[1] + red[2] + red[3]);
+    double* Ur = p.U + (int64_t)off * N + (int64_t)t * n;
+    for (int i = tid; i < K; i += 256) {
+      const double u = zh[i] / ((dk[i] - dor) - mu) * inv;
+      const int a = idx[I_P1 * N + i], b = idx[I_P2 * N + i];
+      if (a >= 0) Ur[a] = u;
+      if (b >= 0) Ur[K1 + b] = u;
+    }
+    if (tid == 0) {
+      const double lam = vec[V_LAM * N + t];
+      const int pos = t + dc_count(vec + V_DFS * N, ndf, lam, false);
+      idx[I_POS * N + t] = pos;
+      p.d[off + pos] = lam;
+    }
+  } else {
+    const int r0 = t - K;
+    const double val = vec[V_DFS * N + r0];
+    const int pos = r0 + dc_count(vec + V_LAM * N, K, val, true);
+    const double* Bc = p.B + (int64_t)(off + t) * N + off;
+    double* Ec = p.E + (int64_t)(off + pos) * N + off;
+    for (int r = tid; r < n; r += 256) Ec[r] = Bc[r];
+    if (tid == 0) p.d[off + pos] = val;
+  }
+}
+
+__global__ void k_dc_finish(const EigDev* __restrict__ P) {
+  const EigDev& p = P[blockIdx.x];
+  const double s = *p.scale;
+  for (int i = threadIdx.x; i < p.n; i += blockDim.x) p.ev[i] = p.d[i] * s;
+}
+
+// ---------------------------------------------------- back-transformation --
+// T of each block of kBk reflectors, H_0 H_1 .. = I - V T V^T, from the Gram
+// matrix G = V^T V and tau (one workgroup a block): the two 64-column halves
+// by columns, T[0:j, j] = -tau_j T[0:j, 0:j] G[0:j, j] (four lanes a row, a
+// fixed trip over the zero-filled row), then T12 = -T11 G12 T22.
+struct TBlock {
+  const double* G;
+  const double* tau;
+  double* T;
+  int kb;
+};
+__global__ __launch_bounds__(256) void k_wy_t(const TBlock* __restrict__ blocks) {
+  constexpr int H = kBk / 2;
+  __shared__ double Gs[H][H + 1], Ta[H][H + 1], Tb[H][H + 1], X[H][H + 1];
+  const TBlock b = blocks[blockIdx.x];
+  const int tid = threadIdx.x;
+  for (int half = 0; half < 2; ++half) {
+    double (*T)[H + 1] = half ? Tb : Ta;
+    const int o = half * H;
+    for (int e = tid; e < H * H; e += 256) {
+      const int i = e / H, l = e % H;
+      Gs[i][l] = (o + i < b.kb && o + l < b.kb) ? b.G[(o + i) * kBk + o + l] : 0.0;
+      T[i][l] = 0.0;
+    }
+    __syncthreads();
+    for (int j = 0; j < H; ++j) {
+      const int i = tid >> 2, q = tid & 3;
+      const double tj = o + j < b.kb ? b.tau[o + j] : 0.0;
+      double s = 0.0;
+#pragma unroll
+      for (int u = 0; u < H / 4; ++u) s += T[i][q + 4 * u] * Gs[q + 4 * u][j];
+      s = quad_total(s);
+      __syncthreads();
+      if (q == 0 && i <= j) T[i][j] = i == j ? tj : -tj * s;
+      __syncthreads();
+    }
+  }
+  for (int e = tid; e < H * H; e += 256) {
+    const int i = e / H, l = e % H;
+    Gs[i][l] = (i < b.kb && H + l < b.kb) ? b.G[i * kBk + H + l] : 0.0;
+  }
+  __syncthreads();
+  const int r0 = (tid >> 4) * 4, c0 = (tid & 15);  // 4 rows, columns c0 + 16 q
+  auto product = [&](double (*L)[H + 1], double (*R)[H + 1], double (&acc)[4][4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[i][q] = 0.0;
+    for (int l = 0; l < H; ++l) {
+      double x[4], y[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = L[r0 + i][l];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] = R[l][c0 + 16 * q];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[i][q] = fma(x[i], y[q], acc[i][q]);
+    }
+  };
+  double acc[4][4];
+  product(Gs, Tb, acc);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) X[r0 + i][c0 + 16 * q] = acc[i][q];
+  __syncthreads();
+  product(Ta, X, acc);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) b.T[(r0 + i) * kBk + H + c0 + 16 * q] = -acc[i][q];
+  for (int e = tid; e < H * H; e += 256) {
+    const int i = e / H, l = e % H;
+    b.T[i * kBk + l] = Ta[i][l];
+    b.T[(H + i) * kBk + l] = 0.0;
+    b.T[(H + i) * kBk + H + l] = Tb[i][l];
+  }
+}
+
+// X[m][n] -= v
+struct EpiMinus {
+  double* X;
+  int64_t ld;
+  __device__ __forceinline__ void operator()(int64_t, int64_t, int64_t m, int64_t n, double v,
+                                             bool) const {
+    X[m * ld + n] -= v;
+  }
+};
+typedef GemmJob<Strided<true>, Strided<true>, EpiStore> JobGW;    // Gram matrices, W = V^T X
+typedef GemmJob<Strided<false>, Strided<false>, EpiStore> JobY;   // Y = V T
+typedef GemmJob<Strided<false>, Strided<false>, EpiMinus> JobX;   // X -= Y W
+
+__global__ void k_eig_out(const EigDev* __restrict__ P) {
+  const EigDev& p = P[blockIdx.y];
+  const int64_t nn = (int64_t)p.n * p.n, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += step) {
+    const int64_t s = i / p.n;
+    p.A[s * p.ld + (i - s * p.n)] = p.E[i];
+  }
+}
+
+// ------------------------------------------------------------- host side --
+template <class J, class OA, class OB, class EPI>
+void add_job(std::vector<J>& v, int64_t& wg, OA a, OB b, EPI e, int64_t M, int64_t N, int64_t K) {
+  v.push_back(J{a, b, e, M, N, K, K > 0 ? K : 1, (M + 63) / 64, (N + 63) / 64, 1, wg});
+  wg += ((M + 63) / 64) * ((N + 63) / 64);
+}
+
+// Appends a table to the upload image; returns its offset.
+template <class T>
+size_t put(std::vector<char>& img, const std::vector<T>& v) {
+  const size_t at = (img.size() + 255) / 256 * 256;
+  img.resize(at + v.size() * sizeof(T));
+  if (!v.empty()) memcpy(img.data() + at, v.data(), v.size() * sizeof(T));
+  return at;
+}
+
+// Team of a problem: the smallest workgroup count whose rows hold it, in the
+// shape with few rows per workgroup (`wide`: the columns of a single problem
+// cost least) or with many (several problems share the chip).
+void pick_team(int n, bool wide, int* cfg, int* team) {
+  int c;
+  if (n <= 128) c = 0;
+  else if (n <= 256) c = 1;
+  else if (n <= 512) c = wide ? 2 : 3;
+  else if (n <= 1024) c = wide ? 4 : 5;
+  else if (n <= 1536) c = wide ? 6 : 7;
+  else if (n <= 2048) c = wide ? 8 : 9;
+  else if (n <= 2560) c = 10;
+  else c = 11;
+  *cfg = c;
+  *team = (n + kTeamShapes[c].rows - 1) / kTeamShapes[c].rows;
+}
+
+}  // namespace
+
+struct EigPlan {
+  struct Round {
+    size_t at;
+    unsigned wgs;
+    bool coop;
+  };
+  struct Level {
+    size_t nodes, pre, preq, res, jobs;
+    int nn, cols, qblk;
+    int64_t njobs, nwg;
+  };
+  struct Products {
+    size_t at;
+    int64_t n, nwg;
+  };
+  struct Step {
+    Products w, x;
+  };
+  std::vector<char> img;  // host image of the device tables (alive until the run's last wait)
+  char* dev = nullptr;
+  int* err = nullptr;
+  size_t probs = 0, base = 0, tblocks = 0;
+  unsigned count = 0, nbase = 0, ntb = 0;
+  bool clear = false;
+  std::vector<Round> rounds;
+  std::vector<Level> levels;
+  Products gram{}, y{};
+  std::vector<Step> steps;
+};
+
+EigPlan* eig_plan_new() { return new (std::nothrow) EigPlan(); }
+void eig_plan_free(EigPlan* p) { delete p; }
+
+// Workgroups of k_tri_team the device holds at once (0: cooperative launches are not available).
+static int team_budget(qsgw_ctx* c) {
+  if (c->team_wgs < 0) {
+    int coop = 0, cus = 0, per = 0;
+    c->team_wgs = 0;
+    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, c->device) == hipSuccess &&
+        coop &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(&k_tri_team),
+                                                     kTeamThreads, 0) == hipSuccess)
+      c->team_wgs = cus * per;
+    (void)hipGetLastError();
+  }
+  return c->team_wgs;
+}
+
+bool eig_team_fits(qsgw_ctx* c, int64_t n) {
+  if (n < 1 || n > kEigTeamMax) return false;
+  int cfg, team;
+  pick_team((int)n, false, &cfg, &team);
+  return team <= 1 || team <= team_budget(c);
+}
+
+int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, int set) {
+  pl->count = (unsigned)count;
+  std::vector<EigDev> P((size_t)count);
+  // ---- sizes and teams ----
+  int64_t wide_wgs = 0;
+  for (int64_t i = 0; i < count; ++i) {
+    int cfg, team;
+    pick_team((int)prob[i].n, true, &cfg, &team);
+    wide_wgs += team;
+  }
+  const int budget = team_budget(c);
+  const bool wide = wide_wgs <= budget;
+  size_t nd = 8, ni = 64;
+  for (int64_t i = 0; i < count; ++i) {
+    const int64_t n = prob[i].n, nb = (n - 1 + kBk - 1) / kBk;
+    nd += (size_t)(3 * n * n + (3 + kVec) * n + 2 + 2 * nb * kBk * kBk + 8);
+    ni += (size_t)(kIdx * n);
+  }
+  double* D = nullptr;
+  int* I = nullptr;
+  CHECK(ws_get(c, W_EIGD_F + 3 * set, nd, &D));
+  CHECK(ws_get(c, W_EIGD_I + 3 * set, ni, &I));
+  pl->err = I;
+  I += 64;
+  for (int64_t i = 0; i < count; ++i) {
+    const int64_t n = prob[i].n, nb = (n - 1 + kBk - 1) / kBk;
+    EigDev& p = P[(size_t)i];
+    p.A = prob[i].A;
+    p.ev = prob[i].evals;
+    p.ld = prob[i].ld;
+    p.n = (int)n;
+    p.pad = 0;
+    pick_team((int)n, wide, &p.cfg, &p.team);
+    p.E = D;
+    p.B = D + n * n;
+    p.U = D + 2 * n * n;
+    D += (3 * n * n + 1) / 2 * 2;  // (16-byte slots of the exchange)
+    p.d = D;
+    p.e = D + n;
+    p.tau = D + 2 * n;
+    p.vec = D + 3 * n;
+    D += ((3 + kVec) * n + 1) / 2 * 2;
+    p.G = D;
+    p.T = D + nb * kBk * kBk;
+    D += 2 * nb * kBk * kBk;
+    p.scale = D;
+    D += 8;
+    p.idx = I;
+    I += kIdx * n;
+    pl->clear = pl->clear || p.team > 1;
+  }
+  pl->probs = put(pl->img, P);
+  // ---- reduction rounds: largest first, each round filled up with what still fits ----
+  std::vector<int> order((size_t)count);
+  for (int64_t i = 0; i < count; ++i) order[(size_t)i] = (int)i;
+  std::sort(order.begin(), order.end(), [&](int a, int b) {
+    return P[(size_t)a].n != P[(size_t)b].n ? P[(size_t)a].n > P[(size_t)b].n : a < b;
+  });
+  std::vector<char> done((size_t)count, 0);
+  size_t left = (size_t)count;
+  while (left > 0) {
+    std::vector<TeamWg> wg;
+    bool coop = false;
+    for (int i : order) {
+      const EigDev& p = P[(size_t)i];
+      if (done[(size_t)i]) continue;
+      // (a problem in one workgroup needs no co-resident partner)
+      if ((int64_t)wg.size() + p.team > (budget > 0 ? budget : 1)) continue;
+      for (int g = 0; g < p.team; ++g) wg.push_back({i, g});
+      coop = coop || p.team > 1;
+      done[(size_t)i] = 1;
+      --left;
+    }
+    if (wg.empty()) return fail(c, QSGW_ERR_UNSUPPORTED, "eigensolver: a team exceeds the device");
+    pl->rounds.push_back({put(pl->img, wg), (unsigned)wg.size(), coop});
+  }
+  // ---- divide and conquer tree ----
+  std::vector<BaseNode> base;
+  std::vector<std::vector<Node>> lev;
+  struct Rec {
+    int prob, off, n, depth;
+  };
+  std::vector<Rec> stack;
+  for (int64_t i = 0; i < count; ++i) stack.push_back({(int)i, 0, P[(size_t)i].n, 0});
+  while (!stack.empty()) {
+    const Rec r = stack.back();
+    stack.pop_back();
+    if (r.n <= kBase) {
+      base.push_back({r.prob, r.off, r.n});
+      continue;
+    }
+    if ((int)lev.size() <= r.depth) lev.resize((size_t)r.depth + 1);
+    const int n1 = r.n / 2;
+    lev[(size_t)r.depth].push_back({r.prob, r.off, n1, r.n - n1});
+    stack.push_back({r.prob, r.off, n1, r.depth + 1});
+    stack.push_back({r.prob, r.off + n1, r.n - n1, r.depth + 1});
+  }
+  pl->base = put(pl->img, base);
+  pl->nbase = (unsigned)base.size();
+  for (size_t dep = lev.size(); dep-- > 0;) {
+    std::vector<int> pre, preq;
+    std::vector<JobMerge> jobs;
+    std::vector<NodeRes> res(lev[dep].size());
+    int cols = 0, qb = 0;
+    int64_t wg = 0;
+    for (const Node& nd2 : lev[dep]) {
+      const EigDev& p = P[(size_t)nd2.prob];
+      const int64_t N = p.n, n = nd2.n1 + nd2.n2, off = nd2.off;
+      pre.push_back(cols);
+      preq.push_back(qb);
+      cols += (int)n;
+      qb += (int)((n + 3) / 4);
+      const double* Ub = p.U + off * N;
+      const double* Bb = p.B + off * N + off;
+      const int* pos = p.idx + I_POS * N + off;
+      double* Eb = p.E + off * N + off;
+      add_job(jobs, wg, Strided<true>{Ub, n, 1, 0, n}, Strided<false>{Bb, 1, N, 0, nd2.n1},
+              EpiEigCols{Eb, N, pos}, n, nd2.n1, n);
+      add_job(jobs, wg, Strided<true>{Ub, n, 1, 0, n}, Strided<false>{Bb + nd2.n1, 1, N, 0, nd2.n2},
+              EpiEigCols{Eb + nd2.n1, N, pos}, n, nd2.n2, n);
+    }
+    EigPlan::Level L;
+    L.nodes = put(pl->img, lev[dep]);
+    L.pre = put(pl->img, pre);
+    L.preq = put(pl->img, preq);
+    L.res = put(pl->img, res);
+    L.jobs = put(pl->img, jobs);
+    L.nn = (int)lev[dep].size();
+    L.cols = cols;
+    L.qblk = qb;
+    L.njobs = (int64_t)jobs.size();
+    L.nwg = wg;
+    pl->levels.push_back(L);
+  }
+  // ---- back-transformation ----
+  std::vector<JobGW> gram;
+  std::vector<JobY> yj;
+  std::vector<TBlock> tb;
+  int64_t gwg = 0, ywg = 0, maxb = 0;
+  auto blocks = [](int64_t n) { return (n - 1 + kBk - 1) / kBk; };
+  for (const EigDev& p : P) {
+    const int64_t n = p.n, nb = blocks(n);
+    maxb = std::max(maxb, nb);
+    for (int64_t b = 0; b < nb; ++b) {
+      const int64_t j0 = b * kBk, kb = std::min<int64_t>(kBk, n - 1 - j0), len = n - 1 - j0;
+      const double* V = p.A + j0 * p.ld + j0 + 1;
+      double *G = p.G + b * kBk * kBk, *T = p.T + b * kBk * kBk;
+      add_job(gram, gwg, Strided<true>{V, p.ld, 1, 0, kb}, Strided<true>{V, p.ld, 1, 0, kb},
+              EpiStore{G, kBk, 0, 0, 1.0}, kb, kb, len);
+      tb.push_back({G, p.tau + j0, T, (int)kb});
+      add_job(yj, ywg, Strided<false>{T, 1, kBk, 0, kb}, Strided<false>{V, 1, p.ld, 0, len},
+              EpiStore{p.U + j0 * n + j0 + 1, n, 0, 0, 1.0}, kb, len, kb);
+    }
+  }
+  pl->gram = {put(pl->img, gram), (int64_t)gram.size(), gwg};
+  pl->y = {put(pl->img, yj), (int64_t)yj.size(), ywg};
+  pl->tblocks = put(pl->img, tb);
+  pl->ntb = (unsigned)tb.size();
+  for (int64_t s = 0; s < maxb; ++s) {
+    std::vector<JobGW> wj;
+    std::vector<JobX> xj;
+    int64_t wwg = 0, xwg = 0;
+    for (const EigDev& p : P) {
+      const int64_t n = p.n, b = blocks(n) - 1 - s;
+      if (b < 0) continue;
+      const int64_t j0 = b * kBk, kb = std::min<int64_t>(kBk, n - 1 - j0), len = n - 1 - j0;
+      const double* V = p.A + j0 * p.ld + j0 + 1;
+      add_job(wj, wwg, Strided<true>{V, p.ld, 1, 0, kb}, Strided<true>{p.E + j0 + 1, n, 1, 0, n},
+              EpiStore{p.B, n, 0, 0, 1.0}, kb, n, len);
+      add_job(xj, xwg, Strided<false>{p.B, 1, n, 0, n},
+              Strided<false>{p.U + j0 * n + j0 + 1, 1, n, 0, len}, EpiMinus{p.E + j0 + 1, n}, n, len,
+              kb);
+    }
+    EigPlan::Step st;
+    st.w = {put(pl->img, wj), (int64_t)wj.size(), wwg};
+    st.x = {put(pl->img, xj), (int64_t)xj.size(), xwg};
+    pl->steps.push_back(st);
+  }
+  CHECK(ws_get(c, W_EIGD_T + 3 * set, pl->img.size() + 256, &pl->dev));
+  HIP_TRY(c, hipMemcpyAsync(pl->dev, pl->img.data(), pl->img.size(), hipMemcpyHostToDevice,
+                            c->stream));
+  return QSGW_OK;
+}
+
+template <class J>
+static int run_products(qsgw_ctx* c, const EigPlan* pl, const EigPlan::Products& g, const J*,
+                        const char* what) {
+  if (g.nwg <= 0) return QSGW_OK;
+  if (g.nwg > 0x7fffffffLL) return fail(c, QSGW_ERR_INVALID_ARG, "%s: launch too large", what);
+  const J* jobs = reinterpret_cast<const J*>(pl->dev + g.at);
+  typedef decltype(jobs->a) OA;
+  typedef decltype(jobs->b) OB;
+  typedef decltype(jobs->e) EP;
+  hipLaunchKernelGGL((gemm_grouped_kernel<64, 64, OA, OB, EP, false>), dim3((unsigned)g.nwg),
+                     dim3(256), 0, c->stream, jobs, g.n, g.nwg);
+  return launch_check(c, what);
+}
+
+int eig_run(qsgw_ctx* c, const EigPlan* pl) {
+  const EigDev* P = reinterpret_cast<const EigDev*>(pl->dev + pl->probs);
+  const dim3 per_prob(pl->count > 8 ? 64 : 512, pl->count);
+  hipLaunchKernelGGL(k_eig_clear_err, dim3(1), dim3(64), 0, c->stream, pl->err);
+  if (pl->clear) hipLaunchKernelGGL(k_tri_clear, per_prob, dim3(256), 0, c->stream, P);
+  CHECK(launch_check(c, "k_tri_clear"));
+  for (const auto& r : pl->rounds) {
+    const TeamWg* wg = reinterpret_cast<const TeamWg*>(pl->dev + r.at);
+    int* err = pl->err;
+    if (r.coop) {
+      void* args[] = {&P, &wg, &err};
+      HIP_TRY(c, hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_tri_team), dim3(r.wgs),
+                                            dim3(kTeamThreads), args, 0, c->stream));
+    } else {
+      hipLaunchKernelGGL(k_tri_team, dim3(r.wgs), dim3(kTeamThreads), 0, c->stream, P, wg, err);
+    }
+    CHECK(launch_check(c, "k_tri_team"));
+  }
+  hipLaunchKernelGGL(k_dc_scale, dim3(pl->count), dim3(256), 0, c->stream, P);
+  hipLaunchKernelGGL(k_dc_base, dim3(pl->nbase), dim3(256), 0, c->stream, P,
+                     reinterpret_cast<const BaseNode*>(pl->dev + pl->base), pl->err);
+  CHECK(launch_check(c, "k_dc_base"));
+  for (const auto& L : pl->levels) {
+    const Node* nodes = reinterpret_cast<const Node*>(pl->dev + L.nodes);
+    const int* pre = reinterpret_cast<const int*>(pl->dev + L.pre);
+    const int* preq = reinterpret_cast<const int*>(pl->dev + L.preq);
+    NodeRes* res = reinterpret_cast<NodeRes*>(pl->dev + L.res);
+    JobMerge* jobs = reinterpret_cast<JobMerge*>(pl->dev + L.jobs);
+    hipLaunchKernelGGL(k_dc_prep, dim3((unsigned)L.nn), dim3(kPrepThreads), 0, c->stream, P, nodes,
+                       res, jobs);
+    hipLaunchKernelGGL(k_dc_roots, dim3((unsigned)(L.cols + L.qblk)), dim3(256), 0, c->stream, P,
+                       nodes, L.nn, pre, preq, L.cols, res);
+    hipLaunchKernelGGL(k_dc_weights, dim3((unsigned)L.qblk), dim3(256), 0, c->stream, P, nodes, L.nn,
+                       preq, res);
+    hipLaunchKernelGGL(k_dc_vecs, dim3((unsigned)L.cols), dim3(256), 0, c->stream, P, nodes, L.nn,
+                       pre, res);
+    CHECK(launch_check(c, "k_dc_vecs"));
+    CHECK(run_products(c, pl, EigPlan::Products{L.jobs, L.njobs, L.nwg}, (const JobMerge*)nullptr,
+                       "eig merge"));
+  }
+  hipLaunchKernelGGL(k_dc_finish, dim3(pl->count), dim3(256), 0, c->stream, P);
+  CHECK(run_products(c, pl, pl->gram, (const JobGW*)nullptr, "eig Gram"));
+  if (pl->ntb > 0)
+    hipLaunchKernelGGL(k_wy_t, dim3(pl->ntb), dim3(256), 0, c->stream,
+                       reinterpret_cast<const TBlock*>(pl->dev + pl->tblocks));
+  CHECK(launch_check(c, "k_wy_t"));
+  CHECK(run_products(c, pl, pl->y, (const JobY*)nullptr, "eig V T"));
+  for (const auto& s : pl->steps) {
+    CHECK(run_products(c, pl, s.w, (const JobGW*)nullptr, "eig V^T X"));
+    CHECK(run_products(c, pl, s.x, (const JobX*)nullptr, "eig X update"));
+  }
+  hipLaunchKernelGGL(k_eig_out, per_prob, dim3(256), 0, c->stream, P);
+  return launch_check(c, "k_eig_out");
+}
+
+int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what) {
+  int e = 0;
+  CHECK(read_flag(c, pl->err, &e));
+  if (e & 1) return fail(c, QSGW_ERR_SOLVER, "%s: reduction wait exceeded its bound", what);
+  if (e & 2) return fail(c, QSGW_ERR_SOLVER, "%s: a tridiagonal block did not converge", what);
+  return QSGW_OK;
+}
+
+int eig_team(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what) {
+  EigPlan pl;
+  const EigProblem p{n, n, A, evals};
+  CHECK(eig_plan(c, &pl, &p, 1, 0));
+  CHECK(eig_run(c, &pl));
+  return eig_check(c, &pl, what);
+}

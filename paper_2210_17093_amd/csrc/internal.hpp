@@ -107,6 +107,12 @@ enum Slot {
   W_RHOFULL32,   // ... and its FP32 copy (FP32 products)          [naux][ntr] float
   W_BMO_B,       // open-shell iteration: beta-spin MO tensor     [naux][nbf][nbf]
   W_VB,          // open-shell iteration: beta-spin potential     [nbf][nbf]
+  W_EIGD_F,      // dense eigensolver: work matrices and vectors of every problem
+  W_EIGD_I,      // dense eigensolver: error flag, index maps
+  W_EIGD_T,      // dense eigensolver: problem, node and product tables
+  W_EIGD1_F,     // the same for the batched iteration's second plan (Fock)
+  W_EIGD1_I,
+  W_EIGD1_T,
   W_NSLOTS
 };
 
@@ -178,6 +184,8 @@ struct qsgw_ctx {
   // flag words of the finite-input scans (kFinMax ints, pinned host memory the
   // kernels write and the host reads after a stream synchronization)
   int* hfin = nullptr;
+  // workgroups of the dense eigensolver's reduction the device holds at once (-1: not asked yet)
+  int team_wgs = -1;
   // DIIS history of qsgw_iterate (W_DIIS_*): stored pairs, next slot, and
   // the (N_b, subspace size) it belongs to; diis_slots stages the slot order
   int64_t diis_n = 0, diis_next = 0, diis_nbf = -1, diis_m = 0;
@@ -187,6 +195,26 @@ struct qsgw_ctx {
 // Looks up the device address of the static scratch array of the
 // allocation-free entry point for the context's device (noalloc.hip).
 int noalloc_setup(qsgw_ctx* c);
+
+// Dense symmetric eigensolver (eigd.hip) for problems of order up to
+// kEigTeamMax: A [n][ld] symmetric in, row s of A the eigenvector of evals[s]
+// (ascending) out.  A plan lays out any number of problems of different orders
+// in the workspace slots of `set` (0 or 1) and may be run again; eig_check
+// reads the run's error flag (synchronizes).
+constexpr int kEigTeamMax = 3072;
+struct EigProblem {
+  int64_t n, ld;
+  double *A, *evals;
+};
+struct EigPlan;
+EigPlan* eig_plan_new();
+void eig_plan_free(EigPlan* p);
+bool eig_team_fits(qsgw_ctx* c, int64_t n);
+int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, int set);
+int eig_run(qsgw_ctx* c, const EigPlan* pl);
+int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what);
+// One problem with ld = n, checked.
+int eig_team(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what);
 
 // Two-stage dense symmetric eigensolver (eig2s.hip): A [n][n] in, its
 // eigenvectors column-major out, eigenvalues ascending.
@@ -534,9 +562,16 @@ inline bool eig_two_stage_for(const qsgw_ctx* c, int64_t n) {
   return c->eig_solver == QSGW_EIG_TWO_STAGE ||
          (c->eig_solver == QSGW_EIG_AUTO && n >= kEigTwoStageMin);
 }
+// Dense symmetric eigensolve of the orders the team solver holds on the chip;
+// rocSOLVER above.
+inline int eig_dense(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what) {
+  if (eig_team_fits(c, n)) return eig_team(c, n, A, evals, what);
+  return syevd(c, n, A, evals, what);
+}
 inline int eig_casida(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what) {
   if (eig_two_stage_for(c, n)) return eig_two_stage(c, n, A, evals, what);
-  return syevd(c, n, A, evals, what);
+  if (c->eig_solver == QSGW_EIG_ROCSOLVER) return syevd(c, n, A, evals, what);
+  return eig_dense(c, n, A, evals, what);
 }
 
 // V (+)= 1/2 (G + G^T), G = sum of the nz partial slices of part.  Long sums

@@ -429,6 +429,18 @@ __global__ void k_check_finite_table(FiniteTable t, int* bad) {
   if (!ok) __hip_atomic_store(bad + i, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+__global__ void k_mirror_lower(double* A, int64_t n) {
+  __shared__ double t[32][33];
+  if (blockIdx.x > blockIdx.y) return;  // tile (row y, column x) of the lower triangle
+  const int64_t r0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int q = ty; q < 32; q += 8)
+    if (r0 + q < n && c0 + tx < n) t[q][tx] = A[(r0 + q) * n + c0 + tx];
+  __syncthreads();
+  for (int q = ty; q < 32; q += 8)
+    if (c0 + q < n && r0 + tx < n && r0 + tx > c0 + q) A[(c0 + q) * n + r0 + tx] = t[tx][q];
+}
+
 // Order-independent fingerprint of an array's bit patterns:
 // sum_i bits(x_i) * (2 i + 1) mod 2^64.  Integer sums wrap and commute, so
 // the result does not depend on the reduction order.

@@ -501,6 +501,9 @@ __global__ void k_check_finite_table(FiniteTable t, int* bad);
 // rho[P][s] *= sqrt(2 / Omega[s]) over a row-major [naux][ntr] array (the
 // factor of Eq. (18) with the normalisation (X+Y)^s = sqrt(Delta) Z^s / sqrt(Omega_s))
 __global__ void k_scale_rho(double* rho, int64_t naux, int64_t ntr, const double* Omega);
+// Upper triangle of a row-major n x n matrix from its lower one (one
+// workgroup of 256 per 32 x 32 tile, transposed through LDS).
+__global__ void k_mirror_lower(double* A, int64_t n);
 __global__ void k_bits_fingerprint(const double* x, int64_t len, unsigned long long* out);
 __global__ void k_fock_frozen(const double* hmo, const double* V, int64_t n, double* F);
 // Diagonal pole sum Sigma_mm(omega_l), Eq. (17), complex128 interleaved.

@@ -756,6 +756,12 @@ int qsgw_rpa_solve(qsgw_ctx* c, int64_t ntr, double* M_to_Z, double* Omega) {
   if (ntr < 1 || !M_to_Z || !Omega) return fail(c, QSGW_ERR_INVALID_ARG, "bad arguments");
   CHECK(check_finite(c, "qsgw_rpa_solve", {fin(M_to_Z, ntr * ntr, "M")}));
   CHECK(single_begin(c, kStageEigRpa));
+  if (!eig_two_stage_for(c, ntr)) {
+    // a caller's matrix counts by its lower triangle (row-major), whichever solver takes it
+    hipLaunchKernelGGL(k_mirror_lower, dim3(blocks_for(ntr, 32), blocks_for(ntr, 32)), dim3(256), 0,
+                       c->stream, M_to_Z, ntr);
+    CHECK(launch_check(c, "k_mirror_lower"));
+  }
   CHECK(stage_rpa_solve(c, ntr, M_to_Z, Omega));
   return single_end(c);
 }
@@ -1249,7 +1255,7 @@ int iterate_impl(qsgw_ctx* c, const qsgw_problem* p, qsgw_state* st, const qsgw_
     CHECK(sp.close());
     CHECK(sp.close());
     CHECK(sp.open(kStageEigFock));
-    CHECK(syevd(c, nbf, F, epsn, "eig_fock"));
+    CHECK(eig_dense(c, nbf, F, epsn, "eig_fock"));
     CHECK(sp.close());
     // C' = C U (U column-major in F), sign convention, max |d eps|
     {
@@ -1508,7 +1514,7 @@ int qsgw_fock_unrestricted(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc_
     hipLaunchKernelGGL(k_fock_assemble, dim3(blocks_for(nn)), dim3(256), 0, c->stream, hmo, J,
                        Kpart, spl.nz, Vs[sp], nbf, F);
     CHECK(launch_check(c, "k_fock_assemble"));
-    CHECK(syevd(c, nbf, F, epsn, "fock_u/eig"));
+    CHECK(eig_dense(c, nbf, F, epsn, "fock_u/eig"));
     {  // C' = C U (U column-major in F)
       Strided<true> A{Cs[sp], nbf, 1, 0, nbf};
       Strided<true> B{F, nbf, 1, 0, nbf};

@@ -1,0 +1,117 @@
+"""The dense eigensolver of the orders that fit on the chip (qsgw_rpa_solve with
+the automatic solver, and with it the Fock and batched eigensolves): the edges
+of its team shapes, base blocks and reflector blocks, and the spectra that
+exercise deflation, against LAPACK (numpy) in FP64.
+
+Bounds: a backward-stable solver leaves |A z - l z| and |Z^T Z - 1| within a
+small multiple of n eps |A|; 1e-13 n^(1/2) max|A|-scaled bounds (n eps = 7e-13
+at n = 3072) hold LAPACK's own results here and are what is asserted.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2210_17093_amd.qsgw as q
+    return q
+
+
+@pytest.fixture(scope="module")
+def ctx(q):
+    c = q.Context()
+    yield c
+    c.close()
+
+
+def solve(q, ctx, M):
+    A = torch.from_numpy(np.ascontiguousarray(M)).cuda()
+    Z, Om = q.qsgw_rpa_solve(ctx, A)
+    torch.cuda.synchronize()
+    return Z, Om
+
+
+def check(q, ctx, M):
+    n = M.shape[0]
+    lam_ref = np.linalg.eigvalsh(M)
+    Z, Om = solve(q, ctx, M)
+    norm = np.abs(lam_ref).max()
+    bound = 1e-13 * max(4.0, np.sqrt(n))
+    lam = Om.cpu().numpy() ** 2
+    assert np.max(np.abs(lam - lam_ref)) <= bound * norm
+    A = torch.from_numpy(np.ascontiguousarray(M)).cuda()
+    assert float((Z @ Z.T - torch.eye(n, dtype=torch.float64, device="cuda")).abs().max()) <= bound
+    assert float((Z @ A - (Om ** 2)[:, None] * Z).abs().max()) <= bound * norm
+
+
+def spd(n, seed):
+    """A Casida-like matrix: a spread diagonal in (0, 2500] plus a smooth coupling."""
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((n, max(2, n // 4))) * 0.3
+    return np.diag(rng.uniform(0.1, 2500.0, n)) + X @ X.T
+
+
+SIZES = [1, 2, 3, 15, 16, 17, 32, 33, 63, 64, 65, 95, 127, 128, 129, 130, 200, 256, 257, 258, 511,
+         512, 513, 1000, 1024, 1025, 1536, 1537, 1940, 2048, 2049, 2560, 2561, 3072]
+
+
+@pytest.mark.parametrize("n", SIZES)
+def test_orders(q, ctx, n):
+    print("dense eigensolve", n, flush=True)
+    check(q, ctx, spd(n, n))
+
+
+@pytest.mark.parametrize("n", [24, 64, 100, 300, 700])
+@pytest.mark.parametrize("kind", ["identity", "diagonal", "rank_one", "multiplets", "graded",
+                                  "toeplitz", "block"])
+def test_spectra(q, ctx, n, kind):
+    """Deflation of every sort: all of it, close and equal poles, tiny weights."""
+    print("dense eigensolve", kind, n, flush=True)
+    rng = np.random.default_rng(n)
+    if kind == "identity":
+        M = np.eye(n) * 3.0
+    elif kind == "diagonal":
+        M = np.diag(rng.uniform(1.0, 9.0, n))
+    elif kind == "rank_one":
+        u = rng.standard_normal(n)
+        M = np.eye(n) + np.outer(u, u)
+    elif kind == "multiplets":
+        Q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+        M = (Q * np.repeat([1.0, 2.0, 2.0 + 1e-13, 5.0], -(-n // 4))[:n]) @ Q.T
+        M = 0.5 * (M + M.T)
+    elif kind == "graded":
+        s = 10.0 ** np.linspace(0.0, -7.0, n)
+        X = rng.standard_normal((n, n))
+        M = s[:, None] * (X @ X.T + n * np.eye(n)) * s[None, :]
+        M = M + 1e-3 * np.eye(n)
+    elif kind == "toeplitz":
+        M = 2.5 * np.eye(n) - np.eye(n, k=1) - np.eye(n, k=-1)
+    else:
+        B = spd(n // 2, 7)
+        M = np.zeros((n, n))
+        M[:n // 2, :n // 2] = B
+        M[n - n // 2:, n - n // 2:] = B
+        if n % 2:
+            M[n // 2, n // 2] = 2.0
+    check(q, ctx, M)
+
+
+def test_lower_triangle_counts(q, ctx):
+    """The caller's matrix is read by its lower triangle, as rocSOLVER reads it."""
+    M = spd(77, 5)
+    L = np.tril(M) + np.triu(np.full((77, 77), 123.0), 1)
+    Z0, Om0 = solve(q, ctx, M)
+    Z1, Om1 = solve(q, ctx, L)
+    assert torch.equal(Om0, Om1) and torch.equal(Z0, Z1)
+
+
+def test_runs_are_reproducible(q, ctx):
+    M = spd(1200, 1)
+    Z0, Om0 = solve(q, ctx, M)
+    Z1, Om1 = solve(q, ctx, M)
+    assert torch.equal(Om0, Om1) and torch.equal(Z0, Z1)
