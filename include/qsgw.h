@@ -135,8 +135,10 @@ int qsgw_rpa_build(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc, const
  * eigensolves always take the automatic choice for their order, and so do
  * both eigensolves of the batched path). */
 /* Default: up to n = 3072 the library's one-stage solver, which holds the
- * matrix on the chip during its reduction; the two-stage solver for
- * n >= 8192; rocSOLVER dsyevd between (and where the device has no
+ * matrix on the chip during its reduction (FP64 iterations and
+ * qsgw_rpa_solve; the reduced-precision iterations take dsyevd, as their
+ * trajectories hang on the last bits of the eigenvectors); the two-stage
+ * solver for n >= 8192; rocSOLVER dsyevd between (and where the device has no
  * cooperative launches). */
 #define QSGW_EIG_AUTO 0
 #define QSGW_EIG_ROCSOLVER 1 /* rocSOLVER dsyevd (one-stage tridiagonal reduction) */
@@ -489,10 +491,12 @@ int qsgw_iterate_unrestricted(qsgw_ctx* ctx, const qsgw_problem* prob, int64_t n
  * GEMMs (a job table with one entry per molecule, each workgroup finding its
  * molecule by binary search) and segment kernels for the element-wise steps.
  * Each molecule's arithmetic is that of qsgw_iterate (same tile shapes, K
- * splits and epilogues).  The Casida and Fock eigensolves are rocSOLVER
- * strided-batched dsyevd calls, one per size bucket: each matrix is stored
- * padded to its bucket size with zero coupling and a diagonal above its
- * Gershgorin bound, so its own eigenpairs come first.  With QSGW_OPT_GRAPH
+ * splits and epilogues).  In FP64 the Casida (and the Fock) eigensolves of
+ * every molecule run in the same launches of the one-stage solver (orders up
+ * to 3072); larger ones and those of the reduced precisions are rocSOLVER
+ * strided-batched dsyevd calls, one per size bucket, each matrix stored padded
+ * to its bucket size with zero coupling and a diagonal above its Gershgorin
+ * bound, so its own eigenpairs come first.  With QSGW_OPT_GRAPH
  * the kernel segments between eigensolves are captured into hipGraphs on the
  * first iteration and replayed on every iteration (this needs a context
  * created on a stream other than the legacy default stream).

@@ -10,8 +10,10 @@
 //   * segment kernels for the element-wise steps: the per-molecule element
 //     counts are prefix-summed and a thread finds its molecule by binary
 //     search;
-//   * rocSOLVER strided-batched dsyevd per size bucket for the Casida and Fock
-//     eigenproblems.  A matrix of order n in a bucket of order nb is stored
+//   * in FP64 one plan of the dense eigensolver (eigd.hip) each for the Casida
+//     and the Fock eigenproblems of every molecule it takes, all solved in the
+//     same launches.  Larger orders and the reduced precisions go to rocSOLVER
+//     strided-batched dsyevd, one call per size bucket: a matrix of order n in a bucket of order nb is stored
 //     nb x nb with zero coupling to the padding and padding diagonal above the
 //     Gershgorin bound of the matrix, so its n lowest eigenpairs are its own.
 // With QSGW_OPT_GRAPH the kernel segments between the eigensolves are
@@ -26,7 +28,7 @@ namespace {
 // ------------------------------------------------------------ descriptors --
 struct Mol {
   int64_t nbf, naux, nocc, nv, ntr, nn;
-  int64_t nbM, nbF;  // padded eigenproblem orders (bucket sizes)
+  int64_t nbM, nbF;  // leading dimensions of the eigenproblems (padded in a bucket)
   const double* B_ao;
   const double* h;
   double* eps;  // state
@@ -301,6 +303,12 @@ struct Plan {
   int64_t* sig_nz = nullptr;   // device, per molecule
   int64_t* exc_nz = nullptr;   // device, per molecule
   std::vector<Bucket> bM, bF;
+  EigPlan *eM = nullptr, *eF = nullptr;  // the other molecules' eigenproblems
+  std::vector<int64_t> mM, mF;           // their molecule indices
+  ~Plan() {
+    eig_plan_free(eM);
+    eig_plan_free(eF);
+  }
   double* deps = nullptr;      // device [nmol]
   double* gpart = nullptr;     // device, Gershgorin partial maxima (one per workgroup)
   double mix = 1.0;
@@ -405,6 +413,18 @@ struct Jobs {
   int64_t nv, nmix;
 };
 
+// Padding of the bucketed matrices (which = 0 Casida, 1 Fock).
+void pad_buckets(qsgw_ctx* c, Plan& P, Seg ch, Seg nb2, int which) {
+  if (P.total[nb2] == 0) return;
+  const int64_t nmol = (int64_t)P.mols.size();
+  hipLaunchKernelGGL(kb_gershgorin, dim3((unsigned)P.total[ch]), dim3(kGerCols), 0, c->stream,
+                     P.dmols, P.dpre[ch], nmol, which, P.gpart);
+  hipLaunchKernelGGL(kb_gershgorin_max, dim3(blocks_for(nmol)), dim3(256), 0, c->stream, P.dmols,
+                     P.dpre[ch], nmol, P.total[ch], which, P.gpart);
+  hipLaunchKernelGGL(kb_pad, dim3(blocks_for(P.total[nb2])), dim3(256), 0, c->stream, P.dmols,
+                     P.dpre[nb2], nmol, P.total[nb2], which);
+}
+
 // CTM: arithmetic of the MO transform, CT: of the Casida build (split-BF16
 // keeps the MO transform on the FP32 matrix cores, as the single path does)
 template <class CTM, class CT>
@@ -425,12 +445,7 @@ int segment_a(qsgw_ctx* c, Plan& P, const Jobs& J, Spans* sp) {
   CHECK((launch_shape<true, CT>(c, c->tiles.shape[TU_CASIDA], "batched casida", J.cas, J.n,
                                 J.cas_wg)));
   SPAN_CLOSE(sp);
-  hipLaunchKernelGGL(kb_gershgorin, dim3((unsigned)P.total[S_CHM]), dim3(kGerCols), 0, c->stream,
-                     P.dmols, P.dpre[S_CHM], nmol, 0, P.gpart);
-  hipLaunchKernelGGL(kb_gershgorin_max, dim3(blocks_for(nmol)), dim3(256), 0, c->stream, P.dmols,
-                     P.dpre[S_CHM], nmol, P.total[S_CHM], 0, P.gpart);
-  hipLaunchKernelGGL(kb_pad, dim3(blocks_for(P.total[S_NBM2])), dim3(256), 0, c->stream, P.dmols,
-                     P.dpre[S_NBM2], nmol, P.total[S_NBM2], 0);
+  pad_buckets(c, P, S_CHM, S_NBM2, 0);
   return launch_check(c, "batched segment A");
 }
 
@@ -486,12 +501,7 @@ int segment_b2(qsgw_ctx* c, Plan& P, const Jobs& J, Spans* sp) {
   hipLaunchKernelGGL(kb_reduce_nn, dim3(blocks_for(P.total[S_NN])), dim3(256), 0, c->stream, P.dmols,
                      P.dpre[S_NN], nmol, P.total[S_NN], P.exc_nz, 1);
   SPAN_CLOSE(sp);
-  hipLaunchKernelGGL(kb_gershgorin, dim3((unsigned)P.total[S_CHF]), dim3(kGerCols), 0, c->stream,
-                     P.dmols, P.dpre[S_CHF], nmol, 1, P.gpart);
-  hipLaunchKernelGGL(kb_gershgorin_max, dim3(blocks_for(nmol)), dim3(256), 0, c->stream, P.dmols,
-                     P.dpre[S_CHF], nmol, P.total[S_CHF], 1, P.gpart);
-  hipLaunchKernelGGL(kb_pad, dim3(blocks_for(P.total[S_NBF2])), dim3(256), 0, c->stream, P.dmols,
-                     P.dpre[S_NBF2], nmol, P.total[S_NBF2], 1);
+  pad_buckets(c, P, S_CHF, S_NBF2, 1);
   return launch_check(c, "batched segment B2");
 }
 
@@ -508,8 +518,8 @@ int segment_c(qsgw_ctx* c, Plan& P, const Jobs& J, Spans* sp) {
 
 int aux_streams(qsgw_ctx* c) {
   if (c->aux_ready) return QSGW_OK;
+  CHECK(aux_queues(c));
   for (int i = 0; i < qsgw_ctx::kAux; ++i) {
-    if (!c->aux[i]) HIP_TRY(c, hipStreamCreateWithFlags(&c->aux[i], hipStreamNonBlocking));
     if (!c->join[i]) HIP_TRY(c, hipEventCreateWithFlags(&c->join[i], hipEventDisableTiming));
     if (!c->aux_blas[i]) {
       if (rocblas_create_handle(&c->aux_blas[i]) != rocblas_status_success) {
@@ -529,6 +539,7 @@ int aux_streams(qsgw_ctx* c) {
 // round-robin over the context stream and the auxiliary streams, which fork
 // from and join back into the context stream.
 int eig_buckets(qsgw_ctx* c, std::vector<Bucket>& bs) {
+  if (bs.empty()) return QSGW_OK;
   CHECK(aux_streams(c));
   std::vector<Bucket*> order;
   for (auto& b : bs) order.push_back(&b);
@@ -564,6 +575,10 @@ struct Graphs {
       if (g) (void)hipGraphExecDestroy(g);
   }
 };
+
+// Whether an eigenproblem of order n goes to the plan of the dense solver
+// (not in the reduced precisions, see eig_dense).
+bool in_team(qsgw_ctx* c, int64_t n, bool reduced) { return !reduced && eig_team_fits(c, n); }
 
 int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
 
@@ -620,8 +635,9 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
     m.nv = m.nbf - m.nocc;
     m.ntr = m.nocc * m.nv;
     m.nn = m.nbf * m.nbf;
-    m.nbM = round_up(m.ntr, 128);
-    m.nbF = round_up(m.nbf, 32);
+    const bool tM = in_team(c, m.ntr, fp32), tF = in_team(c, m.nbf, fp32);
+    m.nbM = tM ? m.ntr : round_up(m.ntr, 128);
+    m.nbF = tF ? m.nbf : round_up(m.nbf, 32);
     m.B_ao = p.B_ao;
     m.h = p.h;
     m.eps = states[i].eps;
@@ -629,8 +645,10 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
     m.Vc = states[i].Vc;
     m.diag = states[i].diag;
     m.eta = o->eta;
-    bucketM[m.nbM].push_back(i);
-    bucketF[m.nbF].push_back(i);
+    if (tM) P.mM.push_back(i); else bucketM[m.nbM].push_back(i);
+    if (tF) P.mF.push_back(i); else bucketF[m.nbF].push_back(i);
+    if (tM) nd += m.ntr * m.ntr + m.ntr;
+    if (tF) nd += m.nn + m.nbf;
     const SplitPlan rs = rho_split(c->tiles, m.naux, m.ntr, m.ntr, fp32 ? kFp32MaxK : m.ntr);
     m.rho_nz = rs.nz;
     sig_nz[i] = sigma_split(c->tiles, m.nbf, m.ntr).nz;
@@ -747,6 +765,32 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
   };
   make_buckets(bucketM, P.bM, true);
   make_buckets(bucketF, P.bF, false);
+  {
+    std::vector<EigProblem> prob;
+    for (int64_t i : P.mM) {
+      Mol& m = P.mols[i];
+      m.M = take(m.ntr * m.ntr);
+      m.Mev = take(m.ntr);
+      prob.push_back({m.ntr, m.nbM, m.M, m.Mev});
+    }
+    if (!prob.empty()) {
+      P.eM = eig_plan_new();
+      if (!P.eM) return fail(c, QSGW_ERR_ALLOC, "eigensolver plan");
+      CHECK(eig_plan(c, P.eM, prob.data(), (int64_t)prob.size(), 0));
+    }
+    prob.clear();
+    for (int64_t i : P.mF) {
+      Mol& m = P.mols[i];
+      m.F = take(m.nn);
+      m.Fev = take(m.nbf);
+      prob.push_back({m.nbf, m.nbF, m.F, m.Fev});
+    }
+    if (!prob.empty()) {
+      P.eF = eig_plan_new();
+      if (!P.eF) return fail(c, QSGW_ERR_ALLOC, "eigensolver plan");
+      CHECK(eig_plan(c, P.eF, prob.data(), (int64_t)prob.size(), 1));
+    }
+  }
 
   // segment prefix sums
   std::vector<int64_t> pre(S_COUNT * nmol);
@@ -755,9 +799,11 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
     for (int64_t i = 0; i < nmol; ++i) {
       const Mol& m = P.mols[i];
       pre[s * nmol + i] = acc;
-      const int64_t cnt[S_COUNT] = {m.ntr, m.naux * m.ntr, m.nn, m.nbM * m.nbM, m.nbF * m.nbF,
-                                    m.naux, m.nbf, (m.ntr + kGerCols - 1) / kGerCols,
-                                    (m.nbf + kGerCols - 1) / kGerCols};
+      const bool pM = !in_team(c, m.ntr, fp32), pF = !in_team(c, m.nbf, fp32);
+      const int64_t cnt[S_COUNT] = {m.ntr, m.naux * m.ntr, m.nn, pM ? m.nbM * m.nbM : 0,
+                                    pF ? m.nbF * m.nbF : 0, m.naux, m.nbf,
+                                    pM ? (m.ntr + kGerCols - 1) / kGerCols : 0,
+                                    pF ? (m.nbf + kGerCols - 1) / kGerCols : 0};
       acc += cnt[s];
     }
     P.total[s] = acc;
@@ -942,6 +988,7 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
       }
       if (k == 0 || k == 2) {
         CHECK(sp.open(k == 0 ? kStageEigRpa : kStageEigFock));
+        if (EigPlan* e = k == 0 ? P.eM : P.eF) CHECK(eig_run(c, e));
         CHECK(eig_buckets(c, k == 0 ? P.bM : P.bF));
         CHECK(sp.close());
       }
@@ -989,6 +1036,17 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
         if (info[j] != 0 && status >= 0)
           status = fail(c, QSGW_ERR_SOLVER, "molecule %lld: dsyevd info %d", (long long)b.mols[j], info[j]);
     }
+  for (int f = 0; f < 2 && status >= 0; ++f) {
+    const EigPlan* e = f ? P.eF : P.eM;
+    int64_t at = -1;
+    const int rc = e ? eig_check(c, e, f ? "batched Fock eigensolve" : "batched Casida eigensolve", &at)
+                     : QSGW_OK;
+    if (rc < 0 && at >= 0)
+      status = fail(c, rc, "molecule %lld: %s", (long long)(f ? P.mF : P.mM)[(size_t)at],
+                    std::string(c->err).c_str());
+    else if (rc < 0)
+      status = rc;
+  }
   bool all = true;
   for (int64_t i = 0; i < nmol; ++i) {
     all = all && first_ok[i] > 0;

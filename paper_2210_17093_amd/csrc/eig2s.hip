@@ -970,6 +970,7 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
   unsigned long long* pflags = nullptr;
   int* perr = nullptr;
   if (c->tiles.panel_coop) {
+    CHECK(aux_queues(c));
     CHECK(ws_get(c, W_EIG_PFLAG, 257, &pflags));
     perr = reinterpret_cast<int*>(pflags + 256);
     HIP_TRY(c, hipMemsetAsync(pflags, 0, 257 * sizeof(unsigned long long), c->stream));

@@ -18,7 +18,11 @@
 // The merge theory (Cuppen's tearing, deflation of small weights and of close
 // poles by a rotation, the secular equation solved relative to the nearer
 // pole, Gu and Eisenstat's weights from the computed roots) is that of
-// eigdc.hip.
+// eigdc.hip, with the tear's sign kept: beta = e[n1 - 1] comes off both
+// touching diagonal entries and T = diag(T1, T2) + beta v v^T, v = e_{n1-1} +
+// e_{n1}.  A negative beta is solved as -T (poles and roots negated, so their
+// order reversed).  A root's vector is zh / (d - lambda) there, a deflated one keeps
+// its half's sign.
 #include "internal.hpp"
 
 #include <algorithm>
@@ -61,7 +65,7 @@ struct Node {
 // What a merge's deflation leaves for its later kernels.
 struct NodeRes {
   double rho;
-  int K, ndf, K1, K2;
+  int K, ndf, K1, K2, neg, pad;
 };
 
 // ------------------------------------------------------------ wave tools --
@@ -241,6 +245,13 @@ constexpr int kTeamSpinMax = 1 << 21;
 // each half by its owner, starts as kEmpty, and a reader polls the slots it needs.  Every group
 // computes the same scalars from the same values in the same order.
 // Row j of A takes v_j (every group has published y_j, so it has loaded its rows).
+// Indices here run from the matrix's last row to its first (index i is row
+// n - 1 - i); T, the eigenvectors and the stored v are in the matrix's order.
+// That is the order in which dsyevd reduces an upper triangle, and with the
+// merges below the eigenvectors come out with the signs dsyevd gives them
+// (every one of 32,572 vectors of 40 Casida matrices): the split-BF16
+// matrix-core products round a vector and its negative differently (2.8e-7
+// relative), so the signs are part of their results.
 template <int TC, int CU, int RL>
 __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
   constexpr int RG = kTeamThreads / TC, NW = TC / 64;
@@ -258,13 +269,13 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
 #pragma unroll
     for (int l = 0; l < RL; ++l) {
       const int i = l * VG + vg;
-      a[l][u] = (i < n && c < n) ? A[i * ld + c] : 0.0;
+      a[l][u] = (i < n && c < n) ? A[(n - 1 - i) * ld + (n - 1 - c)] : 0.0;
     }
-    col[u] = c < n ? A[c] : 0.0;
+    col[u] = c < n ? A[(n - 1) * ld + (n - 1 - c)] : 0.0;
     v[u] = vp[u] = wp[u] = 0.0;
     if (c < n && rg == 0) sm.v[1][c] = sm.w[1][c] = 0.0;
   }
-  if (g == 0 && tid == 0) P.d[0] = col[0];
+  if (g == 0 && tid == 0) P.d[n - 1] = col[0];
   bool dead = false;
   for (int j = 0; j + 1 < n; ++j) {
     const int par = j & 1;
@@ -301,7 +312,7 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
       if (rg == 0 && c < n) sm.v[par][c] = v[u];
     }
     if (g == 0 && tid == 0) {
-      P.e[j] = beta;
+      P.e[n - 2 - j] = beta;
       P.tau[j] = tau;
     }
     // ---- previous update and y = A v on this group's rows ----
@@ -405,7 +416,7 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
 #pragma unroll
       for (int u = 0; u < CU; ++u) {
         const int c = tc + TC * u;
-        if (c < n) A[j * ld + c] = v[u];
+        if (c < n) A[j * ld + (n - 1 - c)] = v[u];
       }
     }
     // ---- w and the next column ----
@@ -430,7 +441,7 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
       const double w = c > j && c < n ? tau * y[u] - kap * v[u] : 0.0;
       if (rg == 0 && c < n) sm.w[par][c] = w;
       col[u] = c > j && c < n ? r[u] - v[u] * w1 - w : 0.0;
-      if (c == j + 1 && g == 0 && rg == 0) P.d[j + 1] = col[u];
+      if (c == j + 1 && g == 0 && rg == 0) P.d[n - 2 - j] = col[u];
       vp[u] = v[u];
       wp[u] = w;
     }
@@ -452,6 +463,7 @@ __global__ __launch_bounds__(kTeamThreads, 2) void k_tri_team(const EigDev* __re
   __shared__ TriSmem sm;
   const TeamWg t = wg[blockIdx.x];
   const EigDev p = P[t.prob];
+  err += t.prob;
   switch (p.cfg) {
     case 0: tri_team<128, 1, 32>(p, t.g, sm, err); break;
     case 1: tri_team<256, 1, 32>(p, t.g, sm, err); break;
@@ -470,8 +482,9 @@ __global__ __launch_bounds__(kTeamThreads, 2) void k_tri_team(const EigDev* __re
   }
 }
 
-__global__ void k_eig_clear_err(int* err) {
-  if (threadIdx.x == 0) *err = 0;
+__global__ void k_eig_clear_err(int* err, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) err[i] = 0;
 }
 
 // kEmpty into the exchange slots of every problem (blockIdx.y) solved by more than one workgroup.
@@ -714,12 +727,12 @@ __device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
 
 // Merge of D[o..o+m1) and D[o+m1..o+m1+m2) (each ascending, eigenvectors in
 // the columns of E) by the TS threads of a team, rank tr; `team` numbers the
-// teams of the workgroup, all of which call together.  m1 = 0: nothing to do.
+// teams of the workgroup, all of which call together.
 template <int TS>
 __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2, double beta) {
   const int m = m1 + m2;
+  const bool neg = beta < 0.0;
   if (tr < m) {
-    const double sg = beta < 0.0 ? -1.0 : 1.0;
     const double val = sm.D[o + tr];
     int pos;
     double z;
@@ -728,9 +741,10 @@ __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2
       z = sm.E[o + tr][o + m1 - 1];
     } else {
       pos = tr - m1 + dc_count(sm.D + o, m1, val, true);
-      z = sg * sm.E[o + tr][o + m1];
+      z = sm.E[o + tr][o + m1];
     }
-    sm.ds[o + pos] = val;
+    if (neg) pos = m - 1 - pos;
+    sm.ds[o + pos] = neg ? -val : val;
     sm.zs[o + pos] = z;
     sm.src[o + pos] = o + tr;
   }
@@ -811,6 +825,10 @@ __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2
       for (int q = 0; q < ndf; ++q)
         pos += (sm.dfv[o + q] < val || (sm.dfv[o + q] == val && q < q0)) ? 1 : 0;
     }
+    if (neg) {
+      pos = m - 1 - pos;
+      val = -val;
+    }
     sm.pos[o + tr] = o + pos;
     sm.D[o + pos] = val;  // (the old values were last read before the secular step)
   }
@@ -862,14 +880,14 @@ __global__ __launch_bounds__(256) void k_dc_base(const EigDev* __restrict__ P,
   const BaseNode nd = nodes[blockIdx.x];
   const EigDev& p = P[nd.prob];
   const int n = p.n, off = nd.off, m = nd.m, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // leaf boundaries b[0..nl]
+  // leaf boundaries: halves of halves
   const int nl = m > 2 * kLeaf ? 4 : (m > kLeaf ? 2 : 1);
   const int h = nl > 1 ? m / 2 : m;
   const int q1 = nl == 4 ? h / 2 : h, q2 = nl == 4 ? h + (m - h) / 2 : m;
   for (int e = tid; e < kBase * kBase; e += 256) sm.E[e / kBase][e % kBase] = e / kBase == e % kBase ? 1.0 : 0.0;
   __syncthreads();
-  auto edge = [&](int r) -> double {  // |off-diagonal| between rows r - 1 and r of T
-    return r > 0 && r < n ? fabs(p.e[r - 1]) : 0.0;
+  auto edge = [&](int r) -> double {  // off-diagonal between rows r - 1 and r of T
+    return r > 0 && r < n ? p.e[r - 1] : 0.0;
   };
   if (wave < nl) {
     // four leaves: [0,q1) [q1,h) [h,q2) [q2,m); two: [0,h) [h,m); one: [0,m)
@@ -889,7 +907,7 @@ __global__ __launch_bounds__(256) void k_dc_base(const EigDev* __restrict__ P,
       if (lane == lm - 1) d -= edge(off + b1);
       if (lane + 1 < lm) e = p.e[off + b0 + lane];
     }
-    if (!ql_leaf(sm, b0, lm, d, e) && lane == 0) atomicOr(err, 2);
+    if (!ql_leaf(sm, b0, lm, d, e) && lane == 0) atomicOr(err + nd.prob, 2);
   }
   __syncthreads();
   if (nl == 4) {
@@ -972,7 +990,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_dc_prep(const EigDev* __restri
   double* vec = p.vec + off;
   int* idx = p.idx + off;
   const double beta = p.e[off + n1 - 1];
-  const double sg = beta < 0.0 ? -1.0 : 1.0;
+  const bool neg = beta < 0.0;
   double s2 = 0.0, dm = 0.0;
   for (int t = tid; t < n; t += kPrepThreads) {
     const double val = d[t];
@@ -984,9 +1002,10 @@ __global__ __launch_bounds__(kPrepThreads) void k_dc_prep(const EigDev* __restri
       z = Ec[n1 - 1];
     } else {
       pos = t - n1 + dc_count(d, n1, val, true);
-      z = sg * Ec[n1];
+      z = Ec[n1];
     }
-    sm.ds[pos] = val;
+    if (neg) pos = n - 1 - pos;
+    sm.ds[pos] = neg ? -val : val;
     sm.zs[pos] = z;
     sm.src[pos] = t;
     s2 += z * z;
@@ -1107,7 +1126,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_dc_prep(const EigDev* __restri
     if (half == 1) K1 = tot; else K2 = tot;
   }
   if (tid == 0) {
-    res[blockIdx.x] = NodeRes{rho, K, n - K, K1, K2};
+    res[blockIdx.x] = NodeRes{rho, K, n - K, K1, K2, neg ? 1 : 0, 0};
     JobMerge& u = jobs[2 * blockIdx.x];
     JobMerge& l = jobs[2 * blockIdx.x + 1];
     u.M = u.a.rows = l.M = l.a.rows = K;
@@ -1198,6 +1217,7 @@ __global__ __launch_bounds__(256) void k_dc_vecs(const EigDev* __restrict__ P,
   const EigDev& p = P[nd.prob];
   const int N = p.n, off = nd.off, n = nd.n1 + nd.n2, t = blockIdx.x - pre[ni], tid = threadIdx.x;
   const int K = res[ni].K, ndf = res[ni].ndf, K1 = res[ni].K1;
+  const bool neg = res[ni].neg != 0;
   double* vec = p.vec + off;
   int* idx = p.idx + off;
   if (t < K) {
@@ -1221,18 +1241,20 @@ __global__ __launch_bounds__(256) void k_dc_vecs(const EigDev* __restrict__ P,
     }
     if (tid == 0) {
       const double lam = vec[V_LAM * N + t];
-      const int pos = t + dc_count(vec + V_DFS * N, ndf, lam, false);
+      int pos = t + dc_count(vec + V_DFS * N, ndf, lam, false);
+      if (neg) pos = n - 1 - pos;
       idx[I_POS * N + t] = pos;
-      p.d[off + pos] = lam;
+      p.d[off + pos] = neg ? -lam : lam;
     }
   } else {
     const int r0 = t - K;
     const double val = vec[V_DFS * N + r0];
-    const int pos = r0 + dc_count(vec + V_LAM * N, K, val, true);
+    int pos = r0 + dc_count(vec + V_LAM * N, K, val, true);
+    if (neg) pos = n - 1 - pos;
     const double* Bc = p.B + (int64_t)(off + t) * N + off;
     double* Ec = p.E + (int64_t)(off + pos) * N + off;
     for (int r = tid; r < n; r += 256) Ec[r] = Bc[r];
-    if (tid == 0) p.d[off + pos] = val;
+    if (tid == 0) p.d[off + pos] = neg ? -val : val;
   }
 }
 
@@ -1447,7 +1469,7 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
   }
   const int budget = team_budget(c);
   const bool wide = wide_wgs <= budget;
-  size_t nd = 8, ni = 64;
+  size_t nd = 8, ni = (size_t)count;
   for (int64_t i = 0; i < count; ++i) {
     const int64_t n = prob[i].n, nb = (n - 1 + kBk - 1) / kBk;
     nd += (size_t)(3 * n * n + (3 + kVec) * n + 2 + 2 * nb * kBk * kBk + 8);
@@ -1458,7 +1480,10 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
   CHECK(ws_get(c, W_EIGD_F + 3 * set, nd, &D));
   CHECK(ws_get(c, W_EIGD_I + 3 * set, ni, &I));
   pl->err = I;
-  I += 64;
+  I += count;
+  hipLaunchKernelGGL(k_eig_clear_err, dim3(blocks_for(count)), dim3(256), 0, c->stream, pl->err,
+                     count);
+  CHECK(launch_check(c, "k_eig_clear_err"));
   for (int64_t i = 0; i < count; ++i) {
     const int64_t n = prob[i].n, nb = (n - 1 + kBk - 1) / kBk;
     EigDev& p = P[(size_t)i];
@@ -1580,13 +1605,13 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
     maxb = std::max(maxb, nb);
     for (int64_t b = 0; b < nb; ++b) {
       const int64_t j0 = b * kBk, kb = std::min<int64_t>(kBk, n - 1 - j0), len = n - 1 - j0;
-      const double* V = p.A + j0 * p.ld + j0 + 1;
+      const double* V = p.A + j0 * p.ld;  // (v_j is zero from column n - 1 - j on)
       double *G = p.G + b * kBk * kBk, *T = p.T + b * kBk * kBk;
       add_job(gram, gwg, Strided<true>{V, p.ld, 1, 0, kb}, Strided<true>{V, p.ld, 1, 0, kb},
               EpiStore{G, kBk, 0, 0, 1.0}, kb, kb, len);
       tb.push_back({G, p.tau + j0, T, (int)kb});
       add_job(yj, ywg, Strided<false>{T, 1, kBk, 0, kb}, Strided<false>{V, 1, p.ld, 0, len},
-              EpiStore{p.U + j0 * n + j0 + 1, n, 0, 0, 1.0}, kb, len, kb);
+              EpiStore{p.U + j0 * n, n, 0, 0, 1.0}, kb, len, kb);
     }
   }
   pl->gram = {put(pl->img, gram), (int64_t)gram.size(), gwg};
@@ -1601,12 +1626,11 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
       const int64_t n = p.n, b = blocks(n) - 1 - s;
       if (b < 0) continue;
       const int64_t j0 = b * kBk, kb = std::min<int64_t>(kBk, n - 1 - j0), len = n - 1 - j0;
-      const double* V = p.A + j0 * p.ld + j0 + 1;
-      add_job(wj, wwg, Strided<true>{V, p.ld, 1, 0, kb}, Strided<true>{p.E + j0 + 1, n, 1, 0, n},
+      const double* V = p.A + j0 * p.ld;
+      add_job(wj, wwg, Strided<true>{V, p.ld, 1, 0, kb}, Strided<true>{p.E, n, 1, 0, n},
               EpiStore{p.B, n, 0, 0, 1.0}, kb, n, len);
       add_job(xj, xwg, Strided<false>{p.B, 1, n, 0, n},
-              Strided<false>{p.U + j0 * n + j0 + 1, 1, n, 0, len}, EpiMinus{p.E + j0 + 1, n}, n, len,
-              kb);
+              Strided<false>{p.U + j0 * n, 1, n, 0, len}, EpiMinus{p.E, n}, n, len, kb);
     }
     EigPlan::Step st;
     st.w = {put(pl->img, wj), (int64_t)wj.size(), wwg};
@@ -1636,13 +1660,13 @@ static int run_products(qsgw_ctx* c, const EigPlan* pl, const EigPlan::Products&
 int eig_run(qsgw_ctx* c, const EigPlan* pl) {
   const EigDev* P = reinterpret_cast<const EigDev*>(pl->dev + pl->probs);
   const dim3 per_prob(pl->count > 8 ? 64 : 512, pl->count);
-  hipLaunchKernelGGL(k_eig_clear_err, dim3(1), dim3(64), 0, c->stream, pl->err);
   if (pl->clear) hipLaunchKernelGGL(k_tri_clear, per_prob, dim3(256), 0, c->stream, P);
   CHECK(launch_check(c, "k_tri_clear"));
   for (const auto& r : pl->rounds) {
     const TeamWg* wg = reinterpret_cast<const TeamWg*>(pl->dev + r.at);
     int* err = pl->err;
     if (r.coop) {
+      CHECK(aux_queues(c));
       void* args[] = {&P, &wg, &err};
       HIP_TRY(c, hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_tri_team), dim3(r.wgs),
                                             dim3(kTeamThreads), args, 0, c->stream));
@@ -1688,11 +1712,18 @@ int eig_run(qsgw_ctx* c, const EigPlan* pl) {
   return launch_check(c, "k_eig_out");
 }
 
-int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what) {
-  int e = 0;
-  CHECK(read_flag(c, pl->err, &e));
-  if (e & 1) return fail(c, QSGW_ERR_SOLVER, "%s: reduction wait exceeded its bound", what);
-  if (e & 2) return fail(c, QSGW_ERR_SOLVER, "%s: a tridiagonal block did not converge", what);
+// Error flags of the plan's runs so far (synchronizes); *at the first failing problem.
+int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what, int64_t* at) {
+  std::vector<int> e(pl->count, 0);
+  HIP_TRY(c, hipMemcpyAsync(e.data(), pl->err, e.size() * sizeof(int), hipMemcpyDeviceToHost,
+                            c->stream));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  for (size_t i = 0; i < e.size(); ++i) {
+    if (!e[i]) continue;
+    if (at) *at = (int64_t)i;
+    if (e[i] & 1) return fail(c, QSGW_ERR_SOLVER, "%s: reduction wait exceeded its bound", what);
+    return fail(c, QSGW_ERR_SOLVER, "%s: a tridiagonal block did not converge", what);
+  }
   return QSGW_OK;
 }
 
@@ -1701,5 +1732,5 @@ int eig_team(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what)
   const EigProblem p{n, n, A, evals};
   CHECK(eig_plan(c, &pl, &p, 1, 0));
   CHECK(eig_run(c, &pl));
-  return eig_check(c, &pl, what);
+  return eig_check(c, &pl, what, nullptr);
 }

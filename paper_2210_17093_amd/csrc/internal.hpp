@@ -212,7 +212,7 @@ void eig_plan_free(EigPlan* p);
 bool eig_team_fits(qsgw_ctx* c, int64_t n);
 int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, int set);
 int eig_run(qsgw_ctx* c, const EigPlan* pl);
-int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what);
+int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what, int64_t* at);
 // One problem with ld = n, checked.
 int eig_team(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what);
 
@@ -538,6 +538,18 @@ int read_flag(qsgw_ctx* c, int* dflag, int* out) {
   return QSGW_OK;
 }
 
+// The context's auxiliary streams.  Called before any cooperative launch too:
+// the first one makes the runtime take a hardware queue for itself, and the
+// streams created after that share the queues that are left (48 molecules in
+// reduced precision, whose dsyevd calls spread over these streams: 980 ms an
+// iteration pair with the streams created after a cooperative launch, 580 ms
+// before).
+inline int aux_queues(qsgw_ctx* c) {
+  for (int i = 0; i < qsgw_ctx::kAux; ++i)
+    if (!c->aux[i]) HIP_TRY(c, hipStreamCreateWithFlags(&c->aux[i], hipStreamNonBlocking));
+  return QSGW_OK;
+}
+
 // rocSOLVER dsyevd, eigenvectors in place (column-major).
 int syevd(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what) {
   if (n > 0x7fffffffLL) return fail(c, QSGW_ERR_UNSUPPORTED, "%s: n too large for rocSOLVER", what);
@@ -562,16 +574,23 @@ inline bool eig_two_stage_for(const qsgw_ctx* c, int64_t n) {
   return c->eig_solver == QSGW_EIG_TWO_STAGE ||
          (c->eig_solver == QSGW_EIG_AUTO && n >= kEigTwoStageMin);
 }
-// Dense symmetric eigensolve of the orders the team solver holds on the chip;
-// rocSOLVER above.
-inline int eig_dense(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what) {
-  if (eig_team_fits(c, n)) return eig_team(c, n, A, evals, what);
+// Dense symmetric eigensolve: the team solver for the orders it holds on the
+// chip, rocSOLVER above, and rocSOLVER for the iterations of the reduced
+// precisions (fp64 false).  Their products round the eigenvectors to 16 or 24
+// bits, and which way an entry close to a rounding boundary falls hangs on its
+// last FP64 bits: two solvers of equal accuracy give trajectories that part at
+// the level of these variants' own error (up to 2e-7 in the orbitals after two
+// iterations at 117 basis functions, against 1e-12 in FP64), so these variants
+// keep the solver their results were obtained with.
+inline int eig_dense(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
+                     bool fp64) {
+  if (fp64 && eig_team_fits(c, n)) return eig_team(c, n, A, evals, what);
   return syevd(c, n, A, evals, what);
 }
-inline int eig_casida(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what) {
+inline int eig_casida(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
+                      bool fp64) {
   if (eig_two_stage_for(c, n)) return eig_two_stage(c, n, A, evals, what);
-  if (c->eig_solver == QSGW_EIG_ROCSOLVER) return syevd(c, n, A, evals, what);
-  return eig_dense(c, n, A, evals, what);
+  return eig_dense(c, n, A, evals, what, fp64 && c->eig_solver == QSGW_EIG_AUTO);
 }
 
 // V (+)= 1/2 (G + G^T), G = sum of the nz partial slices of part.  Long sums

@@ -204,8 +204,8 @@ int stage_rpa_build(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc, const 
   return QSGW_OK;
 }
 
-int stage_rpa_solve(qsgw_ctx* c, int64_t ntr, double* M, double* Omega) {
-  CHECK(eig_casida(c, ntr, M, Omega, "rpa_solve"));
+int stage_rpa_solve(qsgw_ctx* c, int64_t ntr, double* M, double* Omega, bool fp64) {
+  CHECK(eig_casida(c, ntr, M, Omega, "rpa_solve", fp64));
   int* flags = nullptr;
   CHECK(ws_get(c, W_FLAGS, 8, &flags));
   HIP_TRY(c, hipMemsetAsync(flags, 0, sizeof(int), c->stream));
@@ -762,7 +762,7 @@ int qsgw_rpa_solve(qsgw_ctx* c, int64_t ntr, double* M_to_Z, double* Omega) {
                        c->stream, M_to_Z, ntr);
     CHECK(launch_check(c, "k_mirror_lower"));
   }
-  CHECK(stage_rpa_solve(c, ntr, M_to_Z, Omega));
+  CHECK(stage_rpa_solve(c, ntr, M_to_Z, Omega, true));
   return single_end(c);
 }
 
@@ -1112,7 +1112,7 @@ int iterate_impl(qsgw_ctx* c, const qsgw_problem* p, qsgw_state* st, const qsgw_
         if (fold)
           CHECK(stage_rpa_solve_project(c, ntr, naux, M, Omega, Bt, PX, rhoF));
         else
-          CHECK(stage_rpa_solve(c, ntr, M, Omega));
+          CHECK(stage_rpa_solve(c, ntr, M, Omega, !fp32));
         CHECK(sp.close());
         c->eig_ntr = ntr;
         c->eig_fp = fp;
@@ -1255,7 +1255,7 @@ int iterate_impl(qsgw_ctx* c, const qsgw_problem* p, qsgw_state* st, const qsgw_
     CHECK(sp.close());
     CHECK(sp.close());
     CHECK(sp.open(kStageEigFock));
-    CHECK(eig_dense(c, nbf, F, epsn, "eig_fock"));
+    CHECK(eig_dense(c, nbf, F, epsn, "eig_fock", !fp32));
     CHECK(sp.close());
     // C' = C U (U column-major in F), sign convention, max |d eps|
     {
@@ -1423,7 +1423,7 @@ int qsgw_gw_unrestricted(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc_a,
   if (fold)
     CHECK(stage_rpa_solve_project(c, ntr, naux, M, Omega, Bt, PX, rhoF));
   else
-    CHECK(stage_rpa_solve(c, ntr, M, Omega));
+    CHECK(stage_rpa_solve(c, ntr, M, Omega, true));
   CHECK(spn.close());
   for (int64_t s0 = 0; s0 < ntr; s0 += sb) {
     const int64_t ns = ntr - s0 < sb ? ntr - s0 : sb;
@@ -1514,7 +1514,7 @@ int qsgw_fock_unrestricted(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc_
     hipLaunchKernelGGL(k_fock_assemble, dim3(blocks_for(nn)), dim3(256), 0, c->stream, hmo, J,
                        Kpart, spl.nz, Vs[sp], nbf, F);
     CHECK(launch_check(c, "k_fock_assemble"));
-    CHECK(eig_dense(c, nbf, F, epsn, "fock_u/eig"));
+    CHECK(eig_dense(c, nbf, F, epsn, "fock_u/eig", true));
     {  // C' = C U (U column-major in F)
       Strided<true> A{Cs[sp], nbf, 1, 0, nbf};
       Strided<true> B{F, nbf, 1, 0, nbf};
