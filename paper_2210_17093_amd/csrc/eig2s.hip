@@ -14,8 +14,10 @@
 //      rows [i+1+kb, i+(k+1)b] it fills, annihilates that block's first
 //      column and applies the new reflector to the diagonal block.  Step k
 //      of sweep i runs at time 2i + k: the steps sharing a time touch
-//      disjoint rows of the band, so each time is one launch with one
-//      workgroup per step, and the result equals the sweep-by-sweep order;
+//      disjoint rows of the band, so the result equals the sweep-by-sweep
+//      order.  One launch for all sweeps, a workgroup per k
+//      (k_bulge_chase); orders with more steps a sweep than the device holds
+//      workgroups take one launch per time (k_bulge);
 //   3. tridiagonal eigenproblem: rocSOLVER divide and conquer (dstedc),
 //      eigenvectors E of the tridiagonal matrix;
 //   4. back-transformations Z = Q1 Q2 E: the bulge-chasing reflectors in
@@ -27,6 +29,7 @@
 // All arrays are column-major; a symmetric row-major matrix is its own
 // column-major view.  Everything runs in FP64.
 #include "internal.hpp"
+#include "wave.hpp"
 
 namespace {
 
@@ -663,7 +666,8 @@ __device__ void bulge_step(double* __restrict__ AB, int64_t ldab, int64_t n, int
 // the sequential reduction is kept (checked on the CPU entry by entry).
 constexpr int64_t kLag = 2;
 
-// Step k = t - kLag i of every sweep i of time t, one workgroup each (one launch per time).
+// Step k = t - kLag i of every sweep i of time t, one workgroup each (one launch
+// per time): for orders whose windows k_bulge_chase cannot hold all at once.
 __global__ __launch_bounds__(256) void k_bulge(double* __restrict__ AB, int64_t ldab, int64_t n,
                                                int b, double* __restrict__ V2,
                                                double* __restrict__ tau2, int64_t t,
@@ -675,6 +679,275 @@ __global__ __launch_bounds__(256) void k_bulge(double* __restrict__ AB, int64_t 
   if (k >= K) return;
   __shared__ BulgeSmem sm;
   bulge_step(AB, ldab, n, b, V2, tau2, i, k, sm);
+}
+
+// ---- bulge chasing in one launch ----
+// One workgroup per step index k keeps the two blocks of its window, the
+// off-diagonal O and the diagonal D (all of it), in registers for all sweeps:
+// lane = row, 16 columns per wave.  From one sweep to the next the window moves
+// by one row and column, so with row and column r kept at r mod 64 nothing
+// moves but what crosses a window's edge.  Per sweep a workgroup takes
+//   - the reflector of step (i, k - 1) from the workgroup before it (read from
+//     V2, where the back-transformation needs it anyway: every entry starts
+//     empty and is its own arrival), and
+//   - row r1 + 1 of the band from the workgroup after it, when that has done
+//     step (i - 1, k + 1): a slot pair per workgroup, emptied by its reader
+//     (the writer of a slot has the reader's reflector of a later sweep, which
+//     is sent after the emptying store was acknowledged), and the row's
+//     diagonal entry, which is ready later and needed later, from DN.
+// The chain of a sweep is two exchanges, two reflectors with the product O v
+// before each and one row of the updated O; the rest of the two blocks is
+// updated off it.  Row sums (O v, D v) meet across the waves in LDS, column
+// sums (O^T v) within a wave, and a wave's column values reach its lanes by
+// readlane: LDS broadcasts would share one pipe between the four waves.  The
+// band is read once, d and e leave from workgroup 0.
+// Bound by the instructions of a sweep (about 8,000 cycles a workgroup, of them
+// 1,300 waiting for the neighbours).  n = 10,400, kernel time: 20,795 launches
+// of k_bulge 228 ms, this one 34.4 ms; with the blocks in LDS 64 ms.
+struct alignas(16) BulgePos {
+  double zero[kBand];
+  double oc[kBand], row[kBand];         // the column to annihilate next, the window's first row of O
+  double vp[4][kBand], m[4][kBand];     // what the neighbours sent, a copy per wave
+  double yo4[4][kBand], y4[4][kBand];   // row sums of each wave's columns
+};
+constexpr int kBulgeSpinMax = 1 << 21;  // polls before the wait is given up
+
+__global__ void k_empty(unsigned long long* __restrict__ p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = kEmpty;
+}
+
+// Sums over the 64 lanes of 16 values: lane 16 h + t gets value t % 4 + 4 (h % 2) + 8 (h / 2).
+__device__ __forceinline__ double wave_total16(const double (&x)[16]) {
+  double a[8], c[4];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) a[u] = swap_add32(x[u], x[u + 8]);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    c[u] = swap_add16(a[u], a[u + 4]);
+    c[u] = dpp_add<0x128, 0xf>(c[u]);
+    c[u] = dpp_add<0x124, 0xf>(c[u]);
+    c[u] = dpp_add<0x122, 0xf>(c[u]);
+    c[u] = dpp_add<0x121, 0xf>(c[u]);
+  }
+  const int t = threadIdx.x & 3;
+  const double lo = t & 1 ? c[1] : c[0], hi = t & 1 ? c[3] : c[2];
+  return t & 2 ? hi : lo;
+}
+
+// A row's 16 columns: a vector, so that an index that is the same in every lane
+// becomes a register move.
+typedef double d16 __attribute__((ext_vector_type(16)));
+
+__global__ __launch_bounds__(256, 2) void k_bulge_chase(const double* __restrict__ AB, int64_t ldab,
+                                                        int64_t n, double* V2, double* tau2,
+                                                        double* UP, double* DN,
+                                                        double* __restrict__ dd,
+                                                        double* __restrict__ ee,
+                                                        int* __restrict__ err) {
+  constexpr int b = kBand, W = kBand - 1;
+  __shared__ BulgePos sm;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c0 = 16 * wave;  // this wave's columns c0 .. c0 + 15
+  // the column of this wave that wave_total16 leaves in this lane
+  const int cz = c0 + (lane & 3) + 4 * ((lane >> 4) & 1) + 8 * (lane >> 5);
+  const int64_t k = blockIdx.x;
+  d16 O, D;  // row `lane`
+  // sweep 0's window: rows 1 + k b .. (k + 1) b
+  {
+    const int64_t R = 1 + k * b;
+    const int s = (int)(R & W);
+    const int a = (lane - s) & W;  // logical row, column
+    const bool in = R + a < n;
+    const int ca = k > 0 ? s : 0;  // the column that sweep 0 annihilates
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int c = (c0 + u - s) & W;
+      const int hi = a > c ? a : c, lo = a > c ? c : a;
+      D[u] = R + hi < n ? AB[(R + lo) * ldab + (hi - lo)] : 0.0;
+      O[u] = in && k > 0 && a <= c ? AB[(R - b + c) * ldab + (b + a - c)] : 0.0;
+      if (c0 + u == ca) sm.oc[lane] = k > 0 ? O[u] : (in ? AB[1 + a] : 0.0);
+      if (lane == s) sm.row[c0 + u] = O[u];
+    }
+    if (tid < b) sm.zero[tid] = 0.0;
+    if (k == 0 && tid == 0) dd[0] = AB[0];
+  }
+  __syncthreads();
+  bool dead = false;
+  int64_t f = 0, fp = 0;  // first step of this sweep and of the one before
+  const int64_t sweeps = min(n - 2, n - 1 - k * b);
+  for (int64_t i = 0; i < sweeps; ++i) {
+    const int64_t r0 = i + 1 + k * b;
+    const int par = (int)(i & 1);
+    const int s = (int)(r0 & W);    // slot of the window's first row
+    const int sp = (s + W) & W;     // slot of the row that entered it, r0 + b - 1
+    const bool up = i > 0 && r0 + b - 1 < n;
+    // ---- what the neighbours send, polled by every wave for itself ----
+    double vp = 0.0, taup = 0.0, m = 0.0;  // vp of column `lane`, row r0 + b - 1 of column `lane`
+    unsigned long long* const slot =
+        reinterpret_cast<unsigned long long*>(UP) + (2 * k + (par ^ 1)) * b + ((lane - sp) & W);
+    {
+      const double* src = V2 + (f + k - 1) * b + ((lane - s) & W);
+      const double* srct = tau2 + f + k - 1;
+      for (int spins = 0;; ++spins) {
+        unsigned long long xv = 0, xt = 0, xm = 0;
+        if (k > 0) {
+          xv = peek(src);
+          xt = peek(srct);
+        }
+        if (up) xm = peek(reinterpret_cast<const double*>(slot));
+        vp = __builtin_bit_cast(double, xv);
+        taup = __builtin_bit_cast(double, xt);
+        m = __builtin_bit_cast(double, xm);
+        if (__all(xv != kEmpty && xt != kEmpty && xm != kEmpty) || dead) break;
+        if (spins > kBulgeSpinMax) {
+          dead = true;
+          atomicExch(err, 1);  // (-1 before)
+        }
+      }
+    }
+    // (the store that emptied the other slot is acknowledged before this
+    // sweep's reflector goes out)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    sm.m[wave][lane] = m;
+    double yo = 0.0, x;
+    if (k > 0) {
+      O[sp & 15] = wave == sp >> 4 && lane == sp && i > 0 ? m : O[sp & 15];
+      double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+      for (int u = 0; u < 16; u += 2) {
+        t0 = fma(O[u], read_lane(vp, c0 + u), t0);
+        t1 = fma(O[u + 1], read_lane(vp, c0 + u + 1), t1);
+      }
+      sm.yo4[wave][lane] = t0 + t1;
+      sm.vp[wave][lane] = vp;
+    } else if (wave == 0 && lane == sp && i > 0) {
+      sm.oc[sp] = m;
+    }
+    lds_barrier();
+    if (wave == 1 && up)  // (every wave has read it)
+      __hip_atomic_store(slot, kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    x = sm.oc[lane];
+    if (k > 0) {
+      yo = (sm.yo4[0][lane] + sm.yo4[1][lane]) + (sm.yo4[2][lane] + sm.yo4[3][lane]);
+      x -= taup * yo * read_lane(vp, s);
+    }
+    // ---- reflector of the column (row r0 at lane s; rows past the matrix are zero) ----
+    const double alpha = read_lane(x, s);
+    const double sig = wave_total(lane != s ? x * x : 0.0);
+    double tau = 0.0, beta = alpha, scale = 0.0;
+    if (sig != 0.0) {
+      const double n2 = fma(alpha, alpha, sig), r = fast_rsqrt(n2);
+      beta = -copysign(n2 * r, alpha);
+      tau = fma(fabs(alpha), r, 1.0);
+      scale = fast_rcp(alpha - beta);
+    }
+    const double v = lane == s ? 1.0 : x * scale;
+    if (wave == 0) {
+      publish(V2 + (f + k) * b + ((lane - s) & W), v);
+      if (lane == 0) publish(tau2 + f + k, tau);
+    }
+    // ---- row r0 of H O', O' = O (I - taup vp vp^T), leaves for the window before ----
+    double z = 0.0;  // of column cz: H O' = O' - tau v z^T
+    if (k > 0) {
+      const double orow = sm.row[cz], vpz = sm.vp[wave][cz];
+      double p[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) p[u] = O[u] * v;
+      z = wave_total16(p) - taup * vpz * wave_total(yo * v);
+      if ((lane & 12) == 0)
+        publish(UP + (2 * (k - 1) + par) * b + ((cz - s) & W),
+                cz == s ? beta : orow - taup * read_lane(yo, s) * vpz - tau * z);
+    }
+    // ---- row and column r0 + b - 1 of D, and D v ----
+    if (i > 0) {
+      double md = 0.0;
+      if (up && wave == sp >> 4) {
+        unsigned long long xd = kEmpty;
+        for (int spins = 0;; ++spins) {
+          xd = peek(DN + fp + k + 1);
+          if (__all(xd != kEmpty) || dead) break;
+          if (spins > kBulgeSpinMax) {
+            dead = true;
+            atomicExch(err, 1);
+          }
+        }
+        md = __builtin_bit_cast(double, xd);
+      }
+      if (lane == sp) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) D[u] = sm.m[wave][c0 + u];
+      }
+      D[sp & 15] = wave == sp >> 4 ? (lane == sp ? md : m) : D[sp & 15];
+    }
+    {
+      double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+      for (int u = 0; u < 16; u += 2) {
+        t0 = fma(D[u], read_lane(v, c0 + u), t0);
+        t1 = fma(D[u + 1], read_lane(v, c0 + u + 1), t1);
+      }
+      sm.y4[wave][lane] = t0 + t1;
+    }
+    lds_barrier();
+    const double y =
+        tau * ((sm.y4[0][lane] + sm.y4[1][lane]) + (sm.y4[2][lane] + sm.y4[3][lane]));
+    const double w = y - 0.5 * tau * wave_total(y * v) * v;
+    if (wave == s >> 4) {
+      // D(r0, r0) follows the row; d and e from the first window
+      double d = D[s & 15];
+      if (lane == s) {
+        d -= 2.0 * w;  // (v = 1)
+        if (k > 0) {
+          publish(DN + f + k, d);
+        } else {
+          dd[r0] = d;
+          ee[i] = beta;
+        }
+      }
+    }
+    // ---- both blocks; row s is empty for the row that replaces it ----
+    // (broadcasts read again: kept, they would spill)
+    double va = v, vpa = vp;
+    asm volatile("" : "+v"(va), "+v"(vpa));
+    if (k > 0) {
+      const double t1 = taup * yo, t2 = tau * v;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const double zu = read_lane(z, (u & 3) + 16 * ((u >> 2) & 1) + 32 * (u >> 3));
+        O[u] = fma(-t2, zu, fma(-t1, read_lane(vpa, c0 + u), O[u]));
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      D[u] = fma(-w, read_lane(va, c0 + u), fma(-v, read_lane(w, c0 + u), D[u]));
+    // column s of D becomes O's last one; the next sweep's column and row to LDS
+    O[s & 15] = wave == s >> 4 ? D[s & 15] : O[s & 15];
+    if (lane == s) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) O[u] = sm.zero[c0 + u];
+    }
+    const int cn = k > 0 ? (s + 1) & W : s;
+    if (wave == cn >> 4) {
+      const double o = O[cn & 15];
+      if (k > 0 || lane != s) sm.oc[lane] = o;
+    }
+    if (k > 0 && lane == ((s + 1) & W)) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) sm.row[c0 + u] = O[u];
+    }
+    fp = f;
+    f += (n - 1 - i + b - 1) / b;
+  }
+  if (k == 0) {  // the last window: rows n - 2, n - 1
+    const int s = (int)((n - 2) & W), t = (int)((n - 1) & W);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (lane == t && c0 + u == t) dd[n - 1] = D[u];
+      if (lane == t && c0 + u == s) ee[n - 2] = D[u];
+    }
+  }
 }
 
 // Compact WY factor of block (J, k) of the bulge-chasing reflectors: with V
@@ -929,6 +1202,20 @@ struct TwoStage {
 // as one product (k = 2 b kDelay).
 constexpr int kDelay = 8;
 
+// Workgroups of k_bulge_chase the device holds at once (0: no cooperative launches).
+static int64_t bulge_wgs(qsgw_ctx* c) {
+  int coop = 0, cus = 0, per = 0;
+  if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, c->device) != hipSuccess ||
+      !coop ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &per, reinterpret_cast<const void*>(&k_bulge_chase), 256, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return (int64_t)cus * per;
+}
+
 static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
                      TwoStage* ts, bool stage3 = true) {
   const int b = kBand;
@@ -1154,17 +1441,52 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
   hipLaunchKernelGGL(k_band_extract, dim3(blocks_for(n * ldab)), dim3(256), 0, c->stream, A, n, b,
                      ldab, AB);
   CHECK(launch_check(c, "k_band_extract"));
-  for (int64_t t = 0; t < tmax; ++t) {
-    int64_t i_hi = t / kLag;
-    if (i_hi > n - 3) i_hi = n - 3;
-    int64_t i_lo = t - K0 >= 0 ? (t - K0) / kLag + 1 : 0;  // kLag i > t - K0
-    if (i_lo > i_hi) continue;
-    hipLaunchKernelGGL(k_bulge, dim3((unsigned)(i_hi - i_lo + 1)), dim3(256), 0, c->stream, AB,
-                       ldab, n, b, V2, tau2, t, i_lo);
+  // All sweeps in one launch where the device holds a workgroup per step index
+  // (two to a compute unit: orders up to 32,768 on 256 of them), otherwise one
+  // launch per time of the schedule.
+  bool chased = false;
+  if (K0 <= bulge_wgs(c)) {
+    double *UP, *DN;
+    CHECK(ws_get(c, W_EIG_UP, (size_t)(2 * K0 * b + nref + 1), &UP));
+    DN = UP + 2 * K0 * b;
+    int* berr = reinterpret_cast<int*>(DN + nref);
+    auto empty = [&](double* p, int64_t count) {
+      hipLaunchKernelGGL(k_empty, dim3(blocks_for(count)), dim3(256), 0, c->stream,
+                         reinterpret_cast<unsigned long long*>(p), count);
+    };
+    empty(V2, nref * b);
+    empty(tau2, nref);
+    empty(UP, 2 * K0 * b + nref + 1);
+    CHECK(launch_check(c, "k_empty"));
+    int64_t ld = ldab, nn = n;
+    void* args[] = {&AB, &ld, &nn, &V2, &tau2, &UP, &DN, &dd, &ee, &berr};
+    CHECK(aux_queues(c));
+    const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_bulge_chase),
+                                                    dim3((unsigned)K0), dim3(256), args, 0,
+                                                    c->stream);
+    if (e == hipSuccess) {
+      chased = true;
+      int stalled = -1;
+      CHECK(read_flag(c, berr, &stalled));
+      if (stalled != -1)
+        return fail(c, QSGW_ERR_SOLVER, "%s: bulge chasing wait exceeded its bound", what);
+    } else {
+      (void)hipGetLastError();
+    }
   }
-  CHECK(launch_check(c, "k_bulge"));
-  hipLaunchKernelGGL(k_tridiag, dim3(blocks_for(n)), dim3(256), 0, c->stream, AB, n, ldab, dd, ee);
-  CHECK(launch_check(c, "k_tridiag"));
+  if (!chased) {
+    for (int64_t t = 0; t < tmax; ++t) {
+      int64_t i_hi = t / kLag;
+      if (i_hi > n - 3) i_hi = n - 3;
+      int64_t i_lo = t - K0 >= 0 ? (t - K0) / kLag + 1 : 0;  // kLag i > t - K0
+      if (i_lo > i_hi) continue;
+      hipLaunchKernelGGL(k_bulge, dim3((unsigned)(i_hi - i_lo + 1)), dim3(256), 0, c->stream, AB,
+                         ldab, n, b, V2, tau2, t, i_lo);
+    }
+    CHECK(launch_check(c, "k_bulge"));
+    hipLaunchKernelGGL(k_tridiag, dim3(blocks_for(n)), dim3(256), 0, c->stream, AB, n, ldab, dd, ee);
+    CHECK(launch_check(c, "k_tridiag"));
+  }
   hipLaunchKernelGGL(k_q2_tfactor, dim3((unsigned)nJ, (unsigned)K0), dim3(256), 0, c->stream, V2,
                      tau2, off, off + n, n, b, ts->Tb);
   CHECK(launch_check(c, "k_q2_tfactor"));

@@ -24,18 +24,16 @@
 // order reversed).  A root's vector is zh / (d - lambda) there, a deflated one keeps
 // its half's sign.
 #include "internal.hpp"
+#include "wave.hpp"
 
 #include <algorithm>
 
 namespace {
 
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-
 constexpr int kTeamThreads = 512;
 constexpr int kBase = 64;   // largest block of the tridiagonal solved in one workgroup
 constexpr int kLeaf = 16;   // largest QL leaf
 constexpr int kBk = 128;    // reflectors per WY block
-constexpr unsigned long long kEmpty = ~0ull;  // a slot not published yet
 
 // One eigenproblem on the device.
 struct EigDev {
@@ -69,35 +67,6 @@ struct NodeRes {
 };
 
 // ------------------------------------------------------------ wave tools --
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double x) {
-  const u32x2 b = __builtin_bit_cast(u32x2, x);
-  u32x2 r;
-  r[0] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b[0], CTRL, ROWS, 0xf, false);
-  r[1] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b[1], CTRL, ROWS, 0xf, false);
-  return x + __builtin_bit_cast(double, r);
-}
-__device__ __forceinline__ double read_lane(double x, int l) {
-  const u32x2 b = __builtin_bit_cast(u32x2, x);
-  u32x2 r;
-  r[0] = (unsigned)__builtin_amdgcn_readlane((int)b[0], l);
-  r[1] = (unsigned)__builtin_amdgcn_readlane((int)b[1], l);
-  return __builtin_bit_cast(double, r);
-}
-// Sum over the 64 lanes (row shifts by 1, 2, 4, 8, then the row broadcasts), the same in every lane.
-__device__ __forceinline__ double wave_total(double x) {
-  x = dpp_add<0x111, 0xf>(x);
-  x = dpp_add<0x112, 0xf>(x);
-  x = dpp_add<0x114, 0xf>(x);
-  x = dpp_add<0x118, 0xf>(x);
-  x = dpp_add<0x142, 0xa>(x);
-  x = dpp_add<0x143, 0xc>(x);
-  return read_lane(x, 63);
-}
-__device__ __forceinline__ double quad_total(double x) {
-  x = dpp_add<0xB1, 0xf>(x);
-  return dpp_add<0x4E, 0xf>(x);
-}
 __device__ __forceinline__ double wave_max(double x) {
   for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
   return x;
@@ -105,37 +74,6 @@ __device__ __forceinline__ double wave_max(double x) {
 __device__ __forceinline__ double wave_prod(double x) {
   for (int o = 32; o > 0; o >>= 1) x *= __shfl_xor(x, o);
   return x;
-}
-// 1 / x and 1 / sqrt(x) to about one unit in the last place (two Newton steps).
-__device__ __forceinline__ double fast_rcp(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
-}
-__device__ __forceinline__ double fast_rsqrt(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
-}
-// Workgroup barrier for LDS traffic alone: global stores stay in flight (the
-// row that one team member publishes would otherwise hold up its y by a
-// store's round trip in every column).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-// x and y each summed over half of the lanes: lanes 0..31 hold x's sums, 32..63 y's.
-__device__ __forceinline__ double swap_add32(double x, double y) {
-  const u32x2 a = __builtin_bit_cast(u32x2, x), b = __builtin_bit_cast(u32x2, y);
-  const auto l = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
-  return __builtin_bit_cast(double, u32x2{l[0], h[0]}) + __builtin_bit_cast(double, u32x2{l[1], h[1]});
-}
-// The same within each half: 16-lane rows 0 and 2 hold x's sums, 1 and 3 y's.
-__device__ __forceinline__ double swap_add16(double x, double y) {
-  const u32x2 a = __builtin_bit_cast(u32x2, x), b = __builtin_bit_cast(u32x2, y);
-  const auto l = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-  return __builtin_bit_cast(double, u32x2{l[0], h[0]}) + __builtin_bit_cast(double, u32x2{l[1], h[1]});
 }
 // Sums of 4 values over the 64 lanes into out[0..4): the first two steps halve
 // the values as they halve the lanes (a swap of lane halves between two
@@ -159,13 +97,6 @@ struct TriSmem {
   double part[8][64];
   double red[2][4][8], al[2][4];
 };
-
-__device__ __forceinline__ void publish(double* p, double x) {
-  unsigned long long b = __builtin_bit_cast(unsigned long long, x);
-  if (b == kEmpty) b = 0x7ff8000000000000ull;
-  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), b, __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // The 16-byte slots (y, r) of a thread's columns tc + TC u, u < CU, read past
 // the L2 of this XCD (the writers are anywhere on the chip); columns outside

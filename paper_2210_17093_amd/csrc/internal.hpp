@@ -92,6 +92,7 @@ enum Slot {
   W_EIG_BAND,    // two-stage eigensolver: lower band + bulge     [n][2b+1]
   W_EIG_V2,      // two-stage eigensolver: bulge reflectors       [steps][b]
   W_EIG_TAU2,    // two-stage eigensolver: bulge tau              [steps]
+  W_EIG_UP,      // two-stage eigensolver: band rows between bulge windows [windows][2][b], diagonals [steps], error flag
   W_EIG_OFF,     // two-stage eigensolver: first step of a sweep  [n] int64
   W_EIG_DE,      // two-stage eigensolver: tridiagonal d, e       [2 n]
   W_EIG_TB,      // two-stage eigensolver: WY factors of the bulge reflector blocks [blocks][64][64]

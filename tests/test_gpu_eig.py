@@ -305,3 +305,16 @@ def test_projected_iteration_per_column_panels(q, ctx):
     finally:
         ctx.set_tiles(None)
     assert np.max(np.abs(host(e) - st["eps"])) <= QP_TOL
+
+
+@pytest.mark.parametrize("n", [256, 257, 258, 319, 320, 321, 322, 705])
+def test_two_stage_window_edges(q, ctx, n):
+    """Orders around the 64-row windows of the bulge chasing: a last window of
+    one, two, 63 and 64 rows at the first sweep, and of every length later."""
+    print("two-stage eigensolve, order", n, flush=True)
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((n, n))
+    M_ref = A @ A.T / n + np.diag(np.linspace(1.0, 50.0, n))
+    M_ref = 0.5 * (M_ref + M_ref.T)
+    Z, Om = q.qsgw_rpa_solve(ctx, dev(M_ref))
+    check_eigenpairs(M_ref, host(Z), host(Om), np.sqrt(np.linalg.eigvalsh(M_ref)))
