@@ -176,143 +176,213 @@ __global__ __launch_bounds__(256) void k_panel_col(double* __restrict__ P, int64
         (tid >= jn && tid < b) ? red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid] : 0.0;
 }
 
+// 16 matrix elements of a thread: a vector, so that an index that is the same in
+// every lane becomes a register move.
+typedef double d16 __attribute__((ext_vector_type(16)));
+constexpr int kPanelSpinMax = 1 << 21;  // polls before the wait is given up
+
+// Shared memory of a panel workgroup.  pj: the column being annihilated, rows
+// 16 apart shifted by 16 bytes (the four row groups of a wave read other banks).
+struct alignas(16) PanelSmem {
+  double pj[2][256 + 32];
+  double red[4][kBand], sum[4][kBand], row[kBand];
+};
+
 // The same Householder QR of one panel (b = 64 columns) in one cooperative
-// launch: workgroup g keeps rows [256 g, 256 g + 256) of the panel in LDS for
-// the whole factorisation, and the launches of the per-column kernel become
-// grid barriers.  Column j: every workgroup writes its partial dots of column
-// j (part[j % 2][g][c], c >= j) and workgroup 0 the panel's row j as updated
-// so far (rowj[j % 2][c]); after the barrier every workgroup adds the partial
-// dots in the same fixed order, forms the reflector as k_panel_col does and
-// applies it to its rows.  Two parities of the exchange buffers let a
-// workgroup publish column j + 1 while another still reads column j.  The
-// panel goes back to global memory at the end (rows < b as they stand; R
-// comes from Rbuf through k_panel_r).
-// The barrier: each workgroup stores gen = gen0 + j + 1 into its own flag
-// (a release store at agent scope, after a workgroup barrier that has every
-// thread's exchange writes done), then threads 0..G-1 each wait for one
-// workgroup's flag to reach gen (relaxed agent-scope loads) and the workgroup
-// takes an agent-scope acquire fence; no counter is contended.  The
-// cooperative launch guarantees that all G workgroups are resident, so every
-// flag is eventually written; a wait is still bounded (kPanelSpinMax polls),
-// and a workgroup that runs out stops waiting and raises *err, which the host
-// turns into an error.  Flags only grow within a solve (gen0 = 64 p for panel
-// p) and are cleared before each solve.
-constexpr int kPanelSpinMax = 1 << 22;
-__global__ __launch_bounds__(256) void k_panel_coop(double* __restrict__ P, int64_t lda, int64_t m,
-                                                    double* __restrict__ part,
-                                                    double* __restrict__ rowj, int G,
-                                                    double* __restrict__ Rbuf,
-                                                    double* __restrict__ tau,
-                                                    unsigned long long* __restrict__ flags,
-                                                    unsigned long long gen0,
-                                                    int* __restrict__ err) {
-  __shared__ double Ps[kBand][257];  // [column][row of this workgroup], odd pitch
-  __shared__ double wv[kBand];
-  __shared__ double sc[3];
-  __shared__ double red[4][kBand];
-  __shared__ int stalled;
-  if (threadIdx.x == 0) stalled = 0;
-  const int tid = threadIdx.x;
+// launch: workgroup g keeps rows [256 g, 256 g + 256) of the panel in registers
+// (thread: 16 rows of columns cg, cg + 16, cg + 32, cg + 48) for the whole
+// factorisation.  Column j: every workgroup publishes its partial dots of
+// column j (slots[j][g][c], c >= j) and workgroup 0 the panel's row j as updated
+// so far (slots[j][gmax][c]); a slot starts empty and is its own arrival, so a
+// column costs one exchange.  Every workgroup adds the partial dots in the same
+// fixed order, forms the reflector as k_panel_col does and applies it to its
+// rows.  v_j leaves for V and the two V halves of the pending-update operands
+// as it is formed (explicit unit diagonal and zeros above it), row j of R for
+// the panel.  `empty` is the other buffer of slots: the last panel's, emptied
+// here for the next one.
+// The cooperative launch holds all G workgroups at once, so every slot is
+// eventually written; a wait is still bounded (kPanelSpinMax polls), and a wave
+// that runs out stops waiting and raises *err, which the host turns into an
+// error.
+// Bound by the exchange and the serial reflector of a column (3.4 us; the
+// arithmetic of a column is 0.5 us).  162 panels of up to 10,336 rows: 541 us
+// a panel with the rows in LDS and a flag barrier per column, 216 us here
+// (plus 57 us of launches that extracted V and R).
+template <int Q0>
+__device__ __forceinline__ void panel_columns(d16 (&P)[4], double* A, int64_t lda, int64_t m,
+                                              double* slots, double* empty, int G, int gmax,
+                                              double* V, double* U1v, double* U2v, int64_t ldu,
+                                              double* tau, int* err, bool& dead, PanelSmem& sm) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cg = tid & 15, rg = lane >> 4;
   const int g = blockIdx.x;
-  const int64_t r = (int64_t)g * 256 + tid;
-  const bool live = r < m;
-#pragma unroll 8
-  for (int c = 0; c < kBand; ++c) Ps[c][tid] = live ? P[(int64_t)c * lda + r] : 0.0;
-  __syncthreads();
-  const int jmax = m - 1 < kBand ? (int)(m - 1) : kBand;  // columns with rows below the diagonal
-  for (int j = 0; j < jmax; ++j) {
-    const int par = j & 1;
-    // partial dots of column j over this workgroup's rows r > j: thread
-    // (c = tid % 64, q = tid / 64) sums rows 64 q .. 64 q + 63 of column c in
-    // order (rows past m hold zeros; only workgroup 0 has rows r <= j)
-    {
-      const int cc = tid & 63, qd = tid >> 6;
-      double s2 = 0.0;
-      if (cc >= j) {
-#pragma unroll 8
-        for (int u = 0; u < 64; ++u) {
-          const int rl = 64 * qd + u;
-          const double a = (g > 0 || rl > j) ? Ps[j][rl] : 0.0;
-          s2 += a * Ps[cc][rl];
-        }
+  const int at = 64 * wave + 16 * rg;  // this thread's first row
+  const bool top = g == 0 && wave == 0;
+  const int64_t slab = (int64_t)(gmax + 1) * kBand;
+  for (int jj = 0; jj < 16; ++jj) {
+    const int j = 16 * Q0 + jj;
+    double* sl = slots + j * slab;
+    const double* pj = sm.pj[j & 1] + at + 2 * (at >> 4);
+    // row j as it stands, from the lanes that hold it
+    double rowq[4];
+#pragma unroll
+    for (int q = Q0; q < 4; ++q) rowq[q] = P[q][jj];
+    if (top && rg == Q0) {
+#pragma unroll
+      for (int q = Q0; q < 4; ++q) publish(sl + (int64_t)gmax * kBand + cg + 16 * q, rowq[q]);
+    }
+    // partial dots of column j (zero up to row j in pj)
+    double x[16], s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = pj[i];
+#pragma unroll
+    for (int q = Q0; q < 4; ++q) {
+      double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        t0 = fma(x[i], P[q][i], t0);
+        t1 = fma(x[i + 1], P[q][i + 1], t1);
       }
-      red[qd][cc] = s2;
+      s[q] = t0 + t1;
     }
-    __syncthreads();
-    if (tid < kBand) {
-      part[((int64_t)par * G + g) * kBand + tid] =
-          tid >= j ? red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid] : 0.0;
-      if (g == 0) rowj[par * kBand + tid] = Ps[tid][j];  // P[j][tid]: row j < 256 is here
-    }
+    // over the four row groups: lane group h keeps column group 2 (h & 1) + (h >> 1)
+    sm.red[wave][cg + 16 * (2 * (rg & 1) + (rg >> 1))] =
+        swap_add16(swap_add32(s[0], s[1]), swap_add32(s[2], s[3]));
+    lds_barrier();
+    if (wave == 0 && lane >= j)
+      publish(sl + (int64_t)g * kBand + lane, (sm.red[0][lane] + sm.red[1][lane]) +
+                                                  (sm.red[2][lane] + sm.red[3][lane]));
+    if (wave == 1)
+      __hip_atomic_store(reinterpret_cast<unsigned long long*>(empty + j * slab +
+                                                               (int64_t)g * kBand + lane),
+                         kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wave == 2 && g == 0)
+      __hip_atomic_store(reinterpret_cast<unsigned long long*>(empty + j * slab +
+                                                               (int64_t)gmax * kBand + lane),
+                         kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // everyone's, wave w those of workgroups w, w + 4, ..., and the row with wave 3
     {
-      // grid barrier (see above)
-      const unsigned long long gen = gen0 + (unsigned long long)(j + 1);
-      __syncthreads();
-      if (tid == 0)
-        __hip_atomic_store(flags + g, gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      if (tid < G && !stalled) {
-        int spins = 0;
-        while (__hip_atomic_load(flags + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gen) {
-          if (++spins > kPanelSpinMax) {
-            stalled = 1;
-            break;
+      double sum = 0.0;
+      unsigned long long xr = 0;
+      for (int h0 = wave; h0 < G; h0 += 64) {
+        unsigned long long y[16];
+        for (int spins = 0;; ++spins) {
+          bool all = true;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int h = h0 + 4 * e < G ? h0 + 4 * e : h0;
+            y[e] = peek(sl + (int64_t)h * kBand + lane);
           }
-          __builtin_amdgcn_s_sleep(1);
+          if (wave == 3) xr = peek(sl + (int64_t)gmax * kBand + lane);
+#pragma unroll
+          for (int e = 0; e < 16; ++e) all = all && y[e] != kEmpty;
+          if (__all((all && xr != kEmpty) || lane < j) || dead) break;
+          if (spins > kPanelSpinMax) {
+            dead = true;
+            atomicOr(err, 1);
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (h0 + 4 * e < G) sum += __builtin_bit_cast(double, y[e]);
+      }
+      sm.sum[wave][lane] = sum;
+      if (wave == 3) {
+        if (G < 4) {  // (no workgroup of its own to wait for)
+          for (int spins = 0;; ++spins) {
+            xr = peek(sl + (int64_t)gmax * kBand + lane);
+            if (__all(xr != kEmpty || lane < j) || dead) break;
+            if (spins > kPanelSpinMax) {
+              dead = true;
+              atomicOr(err, 1);
+            }
+          }
+        }
+        sm.row[lane] = __builtin_bit_cast(double, xr);
+      }
+    }
+    lds_barrier();
+    auto dot = [&](int c) { return (sm.sum[0][c] + sm.sum[1][c]) + (sm.sum[2][c] + sm.sum[3][c]); };
+    const double alpha = sm.row[j], sig = dot(j);
+    double t = 0.0, beta = alpha, scale = 0.0;
+    if (sig != 0.0) {
+      const double n2 = fma(alpha, alpha, sig), r = fast_rsqrt(n2);
+      beta = -copysign(n2 * r, alpha);
+      t = fma(fabs(alpha), r, 1.0);
+      scale = fast_rcp(alpha - beta);
+    }
+    // w_c = P[j][c] + scale dots[c] (w = v^T P[:, c]), P -= tau v w^T; row j has v = 1
+    d16 v;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = x[i] * scale;
+    v[jj] = top && rg == Q0 ? 1.0 : v[jj];
+#pragma unroll
+    for (int q = Q0; q < 4; ++q) {
+      const int c = cg + 16 * q;
+      const double tw = c > j ? t * fma(scale, dot(c), sm.row[c]) : 0.0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) P[q][i] = fma(-tw, v[i], P[q][i]);
+      if (q == (Q0 < 3 ? Q0 + 1 : 3) || q == Q0) {
+        // column j + 1 to LDS as soon as it is updated
+        const int jn = j + 1;
+        if (q == jn >> 4 && cg == (jn & 15)) {
+          double* to = sm.pj[jn & 1] + at + 2 * (at >> 4);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) to[i] = top && 16 * rg + i <= jn ? 0.0 : P[q][i];
         }
       }
-      __syncthreads();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
+    // v_j (unit diagonal, zeros above it: pj holds zeros there) and row j of R
     {
-      // the same fixed order in every workgroup: four strided partial sums per column
-      const int cc = tid & 63, qd = tid >> 6;
-      double s2 = 0.0;
-      if (cc >= j)
-        for (int h = qd; h < G; h += 4) s2 += part[((int64_t)par * G + h) * kBand + cc];
-      red[qd][cc] = s2;
-    }
-    __syncthreads();
-    if (tid < kBand) wv[tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
-    __syncthreads();
-    if (tid == 0) {
-      const double alpha = rowj[par * kBand + j];
-      const double sig = wv[j];
-      if (sig == 0.0) {
-        sc[0] = 0.0;
-        sc[1] = alpha;
-        sc[2] = 0.0;
-      } else {
-        const double beta = -copysign(sqrt(alpha * alpha + sig), alpha);
-        sc[0] = (beta - alpha) / beta;
-        sc[1] = beta;
-        sc[2] = 1.0 / (alpha - beta);
+      const int64_t r = (int64_t)g * 256 + tid;
+      if (r < m) {
+        const double vr = r == j ? 1.0 : sm.pj[j & 1][tid + 2 * (tid >> 4)] * scale;
+        V[j * m + r] = vr;
+        U1v[j * ldu + r] = vr;
+        U2v[j * ldu + r] = vr;
       }
+      if (g == 0 && tid == 0) tau[j] = t;
     }
-    __syncthreads();
-    const double t = sc[0], scale = sc[2];
-    double wc = 0.0;
-    if (tid > j && tid < kBand) wc = rowj[par * kBand + tid] + scale * wv[tid];
-    __syncthreads();
-    if (tid < kBand) wv[tid] = wc;
-    __syncthreads();
-    if (g == 0 && tid < kBand) {  // row j of R, and tau
-      if (tid == j) Rbuf[(int64_t)j * kBand + j] = sc[1];
-      if (tid > j) Rbuf[(int64_t)j * kBand + tid] = rowj[par * kBand + tid] - t * wv[tid];
-      if (tid == 0) tau[j] = t;
+#pragma unroll
+    for (int q = Q0; q < 4; ++q) {
+      const int c = cg + 16 * q;
+      const double r = P[q][jj];
+      if (top && rg == Q0 && c >= j) A[(int64_t)c * lda + j] = c == j ? beta : r;
     }
-    if (live && r > j) {
-      const double v = Ps[j][tid] * scale;
-      Ps[j][tid] = v;
-      if (t != 0.0)
-        for (int c = j + 1; c < kBand; ++c) Ps[c][tid] -= t * wv[c] * v;
-    }
-    __syncthreads();
+    lds_barrier();
   }
-  if (live) {
-#pragma unroll 8
-    for (int c = 0; c < kBand; ++c) P[(int64_t)c * lda + r] = Ps[c][tid];
+}
+
+__global__ __launch_bounds__(256) void k_panel_coop(double* A, int64_t lda, int64_t m,
+                                                    double* slots, double* empty, int G, int gmax,
+                                                    double* __restrict__ V, double* __restrict__ U1v,
+                                                    double* __restrict__ U2v, int64_t ldu,
+                                                    double* __restrict__ tau, int* err) {
+  __shared__ PanelSmem sm;
+  const int tid = threadIdx.x, wave = tid >> 6, cg = tid & 15, rg = (tid >> 4) & 3;
+  const int64_t r0 = (int64_t)blockIdx.x * 256 + 64 * wave + 16 * rg;
+  d16 P[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) P[q][i] = r0 + i < m ? A[(int64_t)(cg + 16 * q) * lda + r0 + i] : 0.0;
+  if (cg == 0) {
+    const int at = 64 * wave + 16 * rg;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sm.pj[0][at + 2 * (at >> 4) + i] = r0 + i == 0 ? 0.0 : P[0][i];
   }
-  if (tid == 0 && stalled) atomicOr(err, 1);
+  __syncthreads();
+  bool dead = false;
+  panel_columns<0>(P, A, lda, m, slots, empty, G, gmax, V, U1v, U2v, ldu, tau, err, dead, sm);
+  panel_columns<1>(P, A, lda, m, slots, empty, G, gmax, V, U1v, U2v, ldu, tau, err, dead, sm);
+  panel_columns<2>(P, A, lda, m, slots, empty, G, gmax, V, U1v, U2v, ldu, tau, err, dead, sm);
+  panel_columns<3>(P, A, lda, m, slots, empty, G, gmax, V, U1v, U2v, ldu, tau, err, dead, sm);
+}
+
+__global__ void k_empty(unsigned long long* __restrict__ p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = kEmpty;
 }
 
 // R (rows q < b of the panel, columns c >= q) from Rbuf into the panel's upper triangle.
@@ -712,11 +782,6 @@ struct alignas(16) BulgePos {
 };
 constexpr int kBulgeSpinMax = 1 << 21;  // polls before the wait is given up
 
-__global__ void k_empty(unsigned long long* __restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = kEmpty;
-}
-
 // Sums over the 64 lanes of 16 values: lane 16 h + t gets value t % 4 + 4 (h % 2) + 8 (h / 2).
 __device__ __forceinline__ double wave_total16(const double (&x)[16]) {
   double a[8], c[4];
@@ -734,10 +799,6 @@ __device__ __forceinline__ double wave_total16(const double (&x)[16]) {
   const double lo = t & 1 ? c[1] : c[0], hi = t & 1 ? c[3] : c[2];
   return t & 2 ? hi : lo;
 }
-
-// A row's 16 columns: a vector, so that an index that is the same in every lane
-// becomes a register move.
-typedef double d16 __attribute__((ext_vector_type(16)));
 
 __global__ __launch_bounds__(256, 2) void k_bulge_chase(const double* __restrict__ AB, int64_t ldab,
                                                         int64_t n, double* V2, double* tau2,
@@ -1253,14 +1314,19 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
   double* U1a = U1;
   double* U2a = U1 + 2 * kDelay * n * b;
   int dp = 0;  // pending panels
-  // cooperative panel QR: barrier flags (cleared for this solve) and error flag
-  unsigned long long* pflags = nullptr;
+  // cooperative panel QR: two buffers of exchange slots, used in turn, and the error flag
+  double* slots = nullptr;
   int* perr = nullptr;
-  if (c->tiles.panel_coop) {
+  const int64_t gmax = np > 0 ? (ts->pm[0] + 255) / 256 : 0;
+  const int64_t nslot = (int64_t)b * (gmax + 1) * b;
+  if (c->tiles.panel_coop && np > 0 && gmax <= 256) {
     CHECK(aux_queues(c));
-    CHECK(ws_get(c, W_EIG_PFLAG, 257, &pflags));
-    perr = reinterpret_cast<int*>(pflags + 256);
-    HIP_TRY(c, hipMemsetAsync(pflags, 0, 257 * sizeof(unsigned long long), c->stream));
+    CHECK(ws_get(c, W_EIG_PANEL, (size_t)(2 * nslot + 1), &slots));
+    perr = reinterpret_cast<int*>(slots + 2 * nslot);
+    HIP_TRY(c, hipMemsetAsync(perr, 0, sizeof(int), c->stream));
+    hipLaunchKernelGGL(k_empty, dim3(blocks_for(2 * nslot)), dim3(256), 0, c->stream,
+                       reinterpret_cast<unsigned long long*>(slots), 2 * nslot);
+    CHECK(launch_check(c, "k_empty"));
   }
   for (int64_t p = 0; p < np; ++p) {
     const int64_t j = ts->pj[p], m = ts->pm[p], kk = m < b ? m : b;
@@ -1278,29 +1344,28 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
       CHECK((gemm_shape<double, false>(c, SH_64x64, "eig/sy2sb panel", A2, B1, E, b, n - j, Kp,
                                        1)));
     }
+    // this panel's block of the pending operands: columns [2 b dp, 2 b (dp + 1))
+    double* U1s = U1a + 2 * b * dp * n + (j + b);
+    double* U2s = U2a + 2 * b * dp * n + (j + b);
     bool coop_done = false;
-    if (m >= 2 * b && pflags && (m + 255) / 256 <= 256) {
-      // the whole panel in one cooperative launch (see k_panel_coop; one flag per workgroup)
-      const int G = (int)((m + 255) / 256);
-      double *part, *Rbuf;
-      CHECK(ws_get(c, W_EIG_PANEL, (size_t)(2 * G * b + 2 * b + b * b), &part));
-      double* rowj = part + 2 * G * b;
-      Rbuf = rowj + 2 * b;
+    if (m >= 2 * b && slots) {
+      // the whole panel in one cooperative launch (see k_panel_coop)
+      int G = (int)((m + 255) / 256), gm = (int)gmax;
+      double* sl = slots + (p & 1) * nslot;
+      double* se = slots + ((p & 1) ^ 1) * nslot;
+      double *tp = tau1 + p * b, *U2v = U2s + b * n;
       int64_t lda = n, mm = m;
-      double* tp = tau1 + p * b;
-      unsigned long long gen0 = (unsigned long long)p * (unsigned long long)b;
-      void* args[] = {&P, &lda, &mm, &part, &rowj, (void*)&G, &Rbuf, &tp, &pflags, &gen0, &perr};
+      void* args[] = {&P, &lda, &mm, &sl, &se, &G, &gm, &V, &U1s, &U2v, &lda, &tp, &perr};
       const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_panel_coop),
                                                       dim3((unsigned)G), dim3(256), args, 0,
                                                       c->stream);
       if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_panel_r, dim3(blocks_for(b * b)), dim3(256), 0, c->stream, P, n, b,
-                           Rbuf);
         CHECK(launch_check(c, "k_panel_coop"));
         coop_done = true;
       } else {
         // not resident at once on this device: the per-column launches below
         (void)hipGetLastError();
+        slots = nullptr;
       }
     }
     if (coop_done) {
@@ -1309,7 +1374,7 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
       const int rpt = m > 16384 ? 2 : 1;  // rows per thread
       const int G = (int)((m + 256 * rpt - 1) / (256 * rpt));
       double *part, *Rbuf;
-      CHECK(ws_get(c, W_EIG_PANEL, (size_t)(2 * G * b + b * b), &part));
+      CHECK(ws_get(c, W_EIG_PCOL, (size_t)(2 * G * b + b * b), &part));
       Rbuf = part + 2 * G * b;
       for (int jc = -1; jc < b; ++jc) {
         double* pin = part + (size_t)((jc + 2) & 1) * G * b;
@@ -1326,16 +1391,15 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
     } else {
       RB_TRY(c, rocsolver_dgeqrf(h, mi, b, P, ni, tau1 + p * b), what);
     }
-    // this panel's block of the pending operands: columns [2 b dp, 2 b (dp + 1))
-    double* U1s = U1a + 2 * b * dp * n + (j + b);
-    double* U2s = U2a + 2 * b * dp * n + (j + b);
     if (kk < b) {
       HIP_TRY(c, hipMemset2DAsync(U1s, n * sizeof(double), 0, m * sizeof(double), 2 * b, c->stream));
       HIP_TRY(c, hipMemset2DAsync(U2s, n * sizeof(double), 0, m * sizeof(double), 2 * b, c->stream));
     }
-    hipLaunchKernelGGL(k_panel_v, dim3(blocks_for(m * kk)), dim3(256), 0, c->stream, P, n, m, kk,
-                       V, U1s, U2s + b * n, n);
-    CHECK(launch_check(c, "k_panel_v"));
+    if (!coop_done) {
+      hipLaunchKernelGGL(k_panel_v, dim3(blocks_for(m * kk)), dim3(256), 0, c->stream, P, n, m, kk,
+                         V, U1s, U2s + b * n, n);
+      CHECK(launch_check(c, "k_panel_v"));
+    }
     // T from the reflectors' Gram matrix (V^T V, long k = m) and tau
     {
       Strided<true> Av{V, m, 1, 0, kk};
@@ -1445,7 +1509,7 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
   // (two to a compute unit: orders up to 32,768 on 256 of them), otherwise one
   // launch per time of the schedule.
   bool chased = false;
-  if (K0 <= bulge_wgs(c)) {
+  if (c->tiles.panel_coop && K0 <= bulge_wgs(c)) {
     double *UP, *DN;
     CHECK(ws_get(c, W_EIG_UP, (size_t)(2 * K0 * b + nref + 1), &UP));
     DN = UP + 2 * K0 * b;

@@ -98,9 +98,9 @@ enum Slot {
   W_EIG_TB,      // two-stage eigensolver: WY factors of the bulge reflector blocks [blocks][64][64]
   W_EIG_PX,      // two-stage projection: Q2^T Q1^T Bt^T          [naux][ntr]
   W_EIG_XP,      // two-stage eigensolver: split-K partials of X = S V T [nz][b][m]
-  W_EIG_PANEL,   // two-stage eigensolver: panel QR partial dots (two buffers) and R  [2 G b + b b]
+  W_EIG_PANEL,   // two-stage eigensolver: panel QR exchange slots [2][b][G + 1][b], error flag
+  W_EIG_PCOL,    // two-stage eigensolver: panel QR by columns, partial dots (two buffers) and R [2 G b + b b]
   W_EIG_Q1W,     // two-stage eigensolver: V^T X and T V^T X of a panel [2][b][ncols]
-  W_EIG_PFLAG,   // two-stage eigensolver: cooperative panel QR barrier flags [256] u64, error flag
   W_EIG_DCG,     // tridiagonal merge (projection): Q^T X and its sorted rows [2][n][naux]
   W_EIG_DCV,     // tridiagonal merge: poles, weights, roots, rotations [12 n + 8]
   W_EIG_DCI,     // tridiagonal merge: row maps, positions, counts (int64) [9 n + 4]

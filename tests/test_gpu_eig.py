@@ -318,3 +318,23 @@ def test_two_stage_window_edges(q, ctx, n):
     M_ref = 0.5 * (M_ref + M_ref.T)
     Z, Om = q.qsgw_rpa_solve(ctx, dev(M_ref))
     check_eigenpairs(M_ref, host(Z), host(Om), np.sqrt(np.linalg.eigvalsh(M_ref)))
+
+
+def test_two_stage_tall_panels(q, ctx):
+    """An order whose first panels are spread over more than 64 workgroups (a
+    second round of partial sums a column): residual, norm and order of some of
+    the eigenpairs, and the trace."""
+    n = 16_577
+    print("two-stage eigensolve, order", n, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randn(n, n, generator=g, dtype=torch.float64, device="cuda") / n ** 0.5
+    A = 0.5 * (A + A.T)
+    A.diagonal().add_(torch.linspace(10.0, 60.0, n, dtype=torch.float64, device="cuda"))
+    Z, Om = q.qsgw_rpa_solve(ctx, A.clone())
+    ev = Om * Om
+    assert bool((ev[1:] >= ev[:-1]).all())
+    assert abs(float(ev.sum() - A.diagonal().sum())) <= 1e-11 * n * 62
+    some = torch.linspace(0, n - 1, 24, device="cuda").long()
+    Zs = Z[some]  # rows are eigenvectors
+    assert float((Zs @ Z.T - torch.eye(n, dtype=torch.float64, device="cuda")[some]).abs().max()) <= 1e-11
+    assert float((Zs @ A - ev[some, None] * Zs).abs().max()) <= 1e-11 * 62
