@@ -25,6 +25,7 @@
 // its half's sign.
 #include "internal.hpp"
 #include "wave.hpp"
+#include "wy.hpp"
 
 #include <algorithm>
 
@@ -1196,10 +1197,8 @@ __global__ void k_dc_finish(const EigDev* __restrict__ P) {
 }
 
 // ---------------------------------------------------- back-transformation --
-// T of each block of kBk reflectors, H_0 H_1 .. = I - V T V^T, from the Gram
-// matrix G = V^T V and tau (one workgroup a block): the two 64-column halves
-// by columns, T[0:j, j] = -tau_j T[0:j, 0:j] G[0:j, j] (four lanes a row, a
-// fixed trip over the zero-filled row), then T12 = -T11 G12 T22.
+// T of each block of kBk reflectors from their Gram matrix V^T V and tau, one
+// workgroup a block (108 us by columns and halves, 36 us here).
 struct TBlock {
   const double* G;
   const double* tau;
@@ -1207,72 +1206,13 @@ struct TBlock {
   int kb;
 };
 __global__ __launch_bounds__(256) void k_wy_t(const TBlock* __restrict__ blocks) {
-  constexpr int H = kBk / 2;
-  __shared__ double Gs[H][H + 1], Ta[H][H + 1], Tb[H][H + 1], X[H][H + 1];
+  __shared__ double T[kBk][kBk + 1];
+  __shared__ double tau[kBk];
   const TBlock b = blocks[blockIdx.x];
   const int tid = threadIdx.x;
-  for (int half = 0; half < 2; ++half) {
-    double (*T)[H + 1] = half ? Tb : Ta;
-    const int o = half * H;
-    for (int e = tid; e < H * H; e += 256) {
-      const int i = e / H, l = e % H;
-      Gs[i][l] = (o + i < b.kb && o + l < b.kb) ? b.G[(o + i) * kBk + o + l] : 0.0;
-      T[i][l] = 0.0;
-    }
-    __syncthreads();
-    for (int j = 0; j < H; ++j) {
-      const int i = tid >> 2, q = tid & 3;
-      const double tj = o + j < b.kb ? b.tau[o + j] : 0.0;
-      double s = 0.0;
-#pragma unroll
-      for (int u = 0; u < H / 4; ++u) s += T[i][q + 4 * u] * Gs[q + 4 * u][j];
-      s = quad_total(s);
-      __syncthreads();
-      if (q == 0 && i <= j) T[i][j] = i == j ? tj : -tj * s;
-      __syncthreads();
-    }
-  }
-  for (int e = tid; e < H * H; e += 256) {
-    const int i = e / H, l = e % H;
-    Gs[i][l] = (i < b.kb && H + l < b.kb) ? b.G[i * kBk + H + l] : 0.0;
-  }
-  __syncthreads();
-  const int r0 = (tid >> 4) * 4, c0 = (tid & 15);  // 4 rows, columns c0 + 16 q
-  auto product = [&](double (*L)[H + 1], double (*R)[H + 1], double (&acc)[4][4]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[i][q] = 0.0;
-    for (int l = 0; l < H; ++l) {
-      double x[4], y[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = L[r0 + i][l];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) y[q] = R[l][c0 + 16 * q];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[i][q] = fma(x[i], y[q], acc[i][q]);
-    }
-  };
-  double acc[4][4];
-  product(Gs, Tb, acc);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) X[r0 + i][c0 + 16 * q] = acc[i][q];
-  __syncthreads();
-  product(Ta, X, acc);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) b.T[(r0 + i) * kBk + H + c0 + 16 * q] = -acc[i][q];
-  for (int e = tid; e < H * H; e += 256) {
-    const int i = e / H, l = e % H;
-    b.T[i * kBk + l] = Ta[i][l];
-    b.T[(H + i) * kBk + l] = 0.0;
-    b.T[(H + i) * kBk + H + l] = Tb[i][l];
-  }
+  if (tid < kBk) tau[tid] = tid < b.kb ? b.tau[tid] : 0.0;
+  wy_factor<kBk>([&](int i, int j) { return i < b.kb && j < b.kb ? b.G[i * kBk + j] : 0.0; }, tau, T);
+  for (int e = tid; e < kBk * kBk; e += 256) b.T[e] = T[e / kBk][e % kBk];
 }
 
 // X[m][n] -= v
