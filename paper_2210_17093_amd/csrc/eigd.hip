@@ -8,7 +8,7 @@
 //      between the workgroups instead of a pass over the matrix in memory
 //      (k_tri_team).
 //   2. Eigenpairs of T by divide and conquer: blocks of up to 64 rows are
-//      solved in one workgroup (implicit QL on leaves of up to 16, then
+//      solved in one workgroup (implicit QL on leaves of up to 8, then
 //      merges in LDS: k_dc_base), larger ones merged level by level with all
 //      nodes of a level in the same launches (k_dc_*), the eigenvectors of a
 //      merge as two grouped products (each half's rows use only the columns
@@ -33,7 +33,8 @@ namespace {
 
 constexpr int kTeamThreads = 512;
 constexpr int kBase = 64;   // largest block of the tridiagonal solved in one workgroup
-constexpr int kLeaf = 16;   // largest QL leaf
+constexpr int kLeaf = 8;    // largest QL leaf
+constexpr int kBaseThreads = 512;
 constexpr int kBk = 128;    // reflectors per WY block
 
 // One eigenproblem on the device.
@@ -455,51 +456,80 @@ __global__ __launch_bounds__(256) void k_dc_scale(const EigDev* __restrict__ P) 
 // Root of the secular equation j of K (poles d ascending, weights z), by W
 // lanes (4 or 64) that each sum every W-th term: the origin pole's index, mu
 // (the root less that pole).  `total` sums a value over the W lanes.
+// Each step replaces the poles up to j and those above it by one at d_j and
+// one at d_{j+1} with the sums' values and slopes (the "middle way" of R.-C.
+// Li, LAPACK Working Note 89) and takes that model's root, kept inside the
+// bracket; it ends when f is as small as its own rounding.  About 5 steps
+// (Newton on mu f(mu) with a step test alone bisected on noise for most of
+// its 40 or so: K = 24 by 4 lanes, 100,000 cycles).
 template <int W, class F>
 __device__ __forceinline__ void secular_root(const double* d, const double* z, int K, double rho,
                                              int j, int lane, F total, int& org, double& mu) {
-  double a, b;
+  double a, b, m;
   int o;
+  const int jl = j < K - 1 ? j : (K > 1 ? K - 2 : 0), jr = jl + 1 < K ? jl + 1 : jl;
   if (j < K - 1) {
-    const double dj = d[j], half = 0.5 * (d[j + 1] - dj);
+    const double dj = d[j], gap = d[j + 1] - dj, half = 0.5 * gap;
     double s = 0.0;
+#pragma unroll 4
     for (int i = lane; i < K; i += W) s += z[i] * z[i] * fast_rcp((d[i] - dj) - half);
-    s = total(s);
-    if (1.0 + rho * s >= 0.0) {
+    const double fm = 1.0 + rho * total(s);
+    // first guess: the other poles as a constant
+    const double u = rho * z[j] * z[j], v = rho * z[j + 1] * z[j + 1];
+    const double c = fm + (u - v) * fast_rcp(half);
+    if (fm >= 0.0) {
       o = j;
       a = 0.0;
       b = half;
+      const double p = c * gap + u + v, q = sqrt(fabs(p * p - 4.0 * u * gap * c));
+      m = p > 0.0 ? 2.0 * u * gap * fast_rcp(p + q) : (p - q) * 0.5 * fast_rcp(c);
     } else {
       o = j + 1;
       a = -half;
       b = 0.0;
+      const double p = c * gap - u - v, q = sqrt(fabs(p * p + 4.0 * v * gap * c));
+      m = p < 0.0 ? 2.0 * v * gap * fast_rcp(p - q) : -(p + q) * 0.5 * fast_rcp(c);
     }
+    if (!(m > a && m < b)) m = 0.5 * (a + b);
   } else {
     o = j;
     a = 0.0;
     b = rho;
+    m = 0.5 * rho;
   }
-  const double d_o = d[o], z_o2 = z[o] * z[o];
-  // f(mu) increases from -inf to +inf over the bracket; h(mu) = mu f(mu) has
-  // no pole at mu = 0
-  double m = 0.5 * (a + b);
-  for (int it = 0; it < 128; ++it) {
-    double S = 0.0, Sp = 0.0;
+  const double d_o = d[o], dl_l = d[jl] - d_o, dl_r = d[jr] - d_o;
+  for (int it = 0; it < 100; ++it) {
+    double S = 0.0, Sa = 0.0, Pl = 0.0, Pr = 0.0;
+#pragma unroll 4
     for (int i = lane; i < K; i += W) {
-      const double dl = d[i] - d_o;
-      const double r = i == o ? 0.0 : fast_rcp(dl - m);
-      const double q = z[i] * z[i] * r;
+      const double r = fast_rcp((d[i] - d_o) - m);
+      const double q = z[i] * z[i] * r, qr = q * r;
       S += q;
-      Sp = fma(q * dl, r, Sp);
+      Sa += fabs(q);
+      Pl += i <= jl ? qr : 0.0;
+      Pr += i <= jl ? 0.0 : qr;
     }
     S = total(S);
-    Sp = total(Sp);
-    const double h = m * (1.0 + rho * S) - rho * z_o2;
-    const bool fneg = m > 0.0 ? h < 0.0 : h > 0.0;
-    if (fneg) a = m; else b = m;
-    double mn = m - h / (1.0 + rho * Sp);
+    Sa = total(Sa);
+    Pl = rho * total(Pl);
+    Pr = rho * total(Pr);
+    const double f = 1.0 + rho * S;
+    // (f increases over the bracket)
+    if (f < 0.0) a = m; else b = m;
+    if (fabs(f) <= __DBL_EPSILON__ * (8.0 * (1.0 + rho * Sa) + fabs(m) * (Pl + Pr))) break;
+    const double Dl = dl_l - m, Dr = dl_r - m;
+    const double c = f - Dl * Pl - Dr * Pr;
+    const double p = (Dl + Dr) * f - Dl * Dr * (Pl + Pr), w = Dl * Dr * f;
+    const double q = sqrt(fabs(p * p - 4.0 * w * c));
+    double eta;
+    if (j < K - 1)
+      eta = p <= 0.0 ? (p - q) * 0.5 * fast_rcp(c) : 2.0 * w * fast_rcp(p + q);
+    else
+      eta = p >= 0.0 ? (p + q) * 0.5 * fast_rcp(c) : 2.0 * w * fast_rcp(p - q);
+    if (!(f * eta < 0.0)) eta = -f * fast_rcp(Pl + Pr);
+    double mn = m + eta;
     if (!(mn > a && mn < b)) mn = 0.5 * (a + b);
-    const bool done = fabs(mn - m) <= 2.0 * __DBL_EPSILON__ * fabs(mn) ||
+    const bool done = fabs(mn - m) <= __DBL_EPSILON__ * fabs(mn) ||
                       !(b - a > 2.0 * __DBL_EPSILON__ * fmax(fabs(a), fabs(b)));
     m = mn;
     if (done) break;
@@ -515,7 +545,7 @@ __device__ __forceinline__ double zhat_factor(const double* d, int K, double rho
   const double di = d[i];
   const double lj = (dor_j - di) + mu_j;
   const double den = j < i ? d[j] - di : (j < K - 1 ? d[j + 1] - di : rho);
-  return lj / den;
+  return lj * fast_rcp(den);
 }
 
 // Number of entries of the ascending v[0..len) below x, or not above it.
@@ -545,9 +575,11 @@ __device__ int dc_deflate_serial(const double* ds, const double* zs, int n, doub
       continue;
     }
     if (prev >= 0) {
-      const double t = sqrt(zp * zp + zj * zj);
-      const double cc = zj / t, ss = zp / t;
-      if (fabs((dj - dp) * cc * ss) <= tol) {
+      // |(dj - dp) c s| <= tol with c = zj / t, s = zp / t; the square root and
+      // the divisions only where it deflates
+      const double t2 = zp * zp + zj * zj;
+      if (fabs((dj - dp) * zj * zp) <= tol * t2) {
+        const double t = sqrt(t2), cc = zj / t, ss = zp / t;
         ra[nr] = prev;
         rb[nr] = j;
         rc[nr] = cc;
@@ -581,24 +613,28 @@ struct BaseSmem {
   double E[kBase][kBase + 1], E2[kBase][kBase + 1], U[kBase][kBase + 1];  // [column][row]
   double D[kBase], ds[kBase], zs[kBase], dk[kBase], zk[kBase], mu[kBase], dor[kBase], zh[kBase],
       dfv[kBase], rc[kBase], rs[kBase], lam[kBase];
-  int src[kBase], nd[kBase], df[kBase], ra[kBase], rb[kBase], pos[kBase], K[4], nrot[4];
+  int src[kBase], nd[kBase], df[kBase], ra[kBase], rb[kBase], pos[kBase], col[kBase], K[4], nrot[4];
   double rho[4];
 };
 
-// Implicit QL with eigenvectors of the tridiagonal leaf D[b..b+m), off-diagonals
-// eo (lane i: d_i, and e_i between i and i + 1) by one wave, lane r row r of
-// the leaf's block of E; eigenvalues ascending into D.  Returns false if an
-// eigenvalue does not converge.
+// Implicit QL with eigenvectors of a tridiagonal leaf of m <= 8 rows (lane i:
+// d_i, and e_i between i and i + 1) by one wave, lane r row r of the
+// eigenvectors in registers; eigenvalues ascending into D[b..b+m), vectors into
+// the leaf's block of E.  Returns false if an eigenvalue does not converge.
+typedef double d8 __attribute__((ext_vector_type(8)));
 __device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
   const int lane = threadIdx.x & 63;
   bool ok = true;
+  d8 Z;
+#pragma unroll
+  for (int c = 0; c < kLeaf; ++c) Z[c] = lane == c ? 1.0 : 0.0;
   for (int l = 0; l < m; ++l) {
     for (int it = 0;; ++it) {
-      int q = l;
-      for (; q + 1 < m; ++q) {
-        const double dd = fabs(read_lane(d, q)) + fabs(read_lane(d, q + 1));
-        if (fabs(read_lane(e, q)) <= __DBL_EPSILON__ * dd) break;
-      }
+      // first negligible e at or after l (the last row counts as one)
+      const double dn = __shfl_down(d, 1);
+      const unsigned long long small =
+          __ballot(lane + 1 >= m || fabs(e) <= __DBL_EPSILON__ * (fabs(d) + fabs(dn)));
+      const int q = l + __builtin_ctzll(small >> l);
       if (q == l) break;
       if (it >= 60) {
         ok = false;
@@ -606,35 +642,36 @@ __device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
       }
       const double dl = read_lane(d, l), el = read_lane(e, l);
       double gg = (read_lane(d, l + 1) - dl) / (2.0 * el);
-      double r = sqrt(gg * gg + 1.0);
+      const double r = sqrt(gg * gg + 1.0);
       gg = read_lane(d, q) - dl + el / (gg + copysign(r, gg));
       double s = 1.0, c = 1.0, p = 0.0;
       int i = q - 1;
       for (; i >= l; --i) {
         const double ei = read_lane(e, i);
         const double f = s * ei, bb = c * ei;
-        r = sqrt(f * f + gg * gg);
-        if (lane == i + 1) e = r;
-        if (r == 0.0) {
-          if (lane == i + 1) d -= p;
+        const double r2 = fma(f, f, gg * gg);
+        if (r2 == 0.0) {
+          if (lane == i + 1) {
+            e = 0.0;
+            d -= p;
+          }
           if (lane == q) e = 0.0;
           break;
         }
-        const double ri = 1.0 / r;
+        const double ri = fast_rsqrt(r2);
+        if (lane == i + 1) e = r2 * ri;
         s = f * ri;
         c = gg * ri;
         gg = read_lane(d, i + 1) - p;
-        r = (read_lane(d, i) - gg) * s + 2.0 * c * bb;
-        p = s * r;
+        const double t = (read_lane(d, i) - gg) * s + 2.0 * c * bb;
+        p = s * t;
         if (lane == i + 1) d = gg + p;
-        gg = c * r - bb;
-        if (lane < m) {
-          const double z1 = sm.E[b + i + 1][b + lane], z0 = sm.E[b + i][b + lane];
-          sm.E[b + i + 1][b + lane] = s * z0 + c * z1;
-          sm.E[b + i][b + lane] = c * z0 - s * z1;
-        }
+        gg = c * t - bb;
+        const double z1 = Z[i + 1], z0 = Z[i];
+        Z[i + 1] = s * z0 + c * z1;
+        Z[i] = c * z0 - s * z1;
       }
-      if (r == 0.0 && i >= l) continue;
+      if (i >= l) continue;
       if (lane == l) {
         d -= p;
         e = gg;
@@ -648,12 +685,11 @@ __device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
     rank += (dk < d || (dk == d && k < lane)) ? 1 : 0;
   }
   if (lane < m) sm.D[b + rank] = d;
-  for (int k = 0; k < m; ++k) {
+#pragma unroll
+  for (int k = 0; k < kLeaf; ++k) {
     const int rk = __builtin_amdgcn_readlane(rank, k);
-    if (lane < m) sm.E2[b + rk][b + lane] = sm.E[b + k][b + lane];
+    if (k < m && lane < m) sm.E[b + rk][b + lane] = Z[k];
   }
-  for (int k = 0; k < m; ++k)
-    if (lane < m) sm.E[b + k][b + lane] = sm.E2[b + k][b + lane];
   return ok;
 }
 
@@ -681,24 +717,49 @@ __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2
     sm.src[o + pos] = o + tr;
   }
   __syncthreads();
-  if (tr == 0) {
-    double s2 = 0.0, dm = 0.0;
-    for (int i = 0; i < m; ++i) {
-      s2 += sm.zs[o + i] * sm.zs[o + i];
-      dm = fmax(dm, fabs(sm.ds[o + i]));
-    }
-    const double zi = m > 0 ? 1.0 / sqrt(s2) : 0.0;
-    for (int i = 0; i < m; ++i) sm.zs[o + i] *= zi;
-    const double rho = fabs(beta) * s2;
+  if (tr < 64) {  // (the team's first wave)
+    const double z = tr < m ? sm.zs[o + tr] : 0.0;
+    const double s2 = wave_total(z * z), dm = wave_max(tr < m ? fabs(sm.ds[o + tr]) : 0.0);
+    const double rho = fabs(beta) * s2, zi = z * fast_rsqrt(s2), di = tr < m ? sm.ds[o + tr] : 0.0;
     const double tol = 8.0 * __DBL_EPSILON__ * fmax(dm, rho);
-    sm.rho[team] = rho;
-    sm.K[team] = dc_deflate_serial(sm.ds + o, sm.zs + o, m, rho, tol, sm.nd + o, sm.dk + o,
-                                   sm.zk + o, sm.df + o, sm.dfv + o, sm.ra + o, sm.rb + o,
-                                   sm.rc + o, sm.rs + o, &sm.nrot[team]);
+    // the poles that stay, and whether two neighbours among them are close
+    const bool stays = tr < m && rho * fabs(zi) > tol;
+    const unsigned long long mask = __ballot(stays);
+    const int at = __popcll(mask & ((1ull << tr) - 1));
+    const unsigned long long later = tr < 63 ? mask >> (tr + 1) : 0;
+    const int nx = later ? tr + 1 + __builtin_ctzll(later) : tr;
+    const double dn = __shfl(di, nx), zn = __shfl(zi, nx);
+    const bool close =
+        stays && later && fabs((dn - di) * zi * zn) <= tol * (zi * zi + zn * zn);
+    if (__ballot(close) == 0) {
+      if (stays) {
+        sm.nd[o + at] = tr;
+        sm.dk[o + at] = di;
+        sm.zk[o + at] = zi;
+      } else if (tr < m) {
+        sm.df[o + tr - at] = tr;
+        sm.dfv[o + tr - at] = di;
+      }
+      if (tr == 0) {
+        sm.rho[team] = rho;
+        sm.K[team] = __popcll(mask);
+        sm.nrot[team] = 0;
+      }
+    } else {
+      if (tr < m) sm.zs[o + tr] = zi;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (tr == 0) {
+        sm.rho[team] = rho;
+        sm.K[team] = dc_deflate_serial(sm.ds + o, sm.zs + o, m, rho, tol, sm.nd + o, sm.dk + o,
+                                       sm.zk + o, sm.df + o, sm.dfv + o, sm.ra + o, sm.rb + o,
+                                       sm.rc + o, sm.rs + o, &sm.nrot[team]);
+      }
+    }
   }
   __syncthreads();
   const int K = sm.K[team], ndf = m - K, nrot = sm.nrot[team];
   const double rho = sm.rho[team];
+  if (tr < K) sm.col[o + tr] = sm.src[o + sm.nd[o + tr]];
   if (tr < m)
     for (int q = 0; q < nrot; ++q) {
       double* xa = &sm.E[sm.src[o + sm.ra[o + q]]][o + tr];
@@ -734,12 +795,12 @@ __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2
     const double dj = sm.dor[o + j], mu = sm.mu[o + j];
     double s2 = 0.0;
     for (int i = ql; i < K; i += 4) {
-      const double u = sm.zh[o + i] / ((sm.dk[o + i] - dj) - mu);
+      const double u = sm.zh[o + i] * fast_rcp((sm.dk[o + i] - dj) - mu);
       sm.U[o + j][o + i] = u;
       s2 += u * u;
     }
     s2 = quad_total(s2);
-    const double inv = 1.0 / sqrt(s2);
+    const double inv = fast_rsqrt(s2);
     for (int i = ql; i < K; i += 4) sm.U[o + j][o + i] *= inv;
   }
   // final positions: roots j < K, then deflated values (rank by counting)
@@ -765,31 +826,33 @@ __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2
     sm.D[o + pos] = val;  // (the old values were last read before the secular step)
   }
   __syncthreads();
-  // E2[pos] = sum_i E[src(nd_i)] U[root][i]: a 4 x 4 block of (root, row) per
-  // thread for m = 64 and TS = 256 (rows tr % 16, + 16, ..)
+  // E2[pos] = sum_i E[col_i] U[root][i] on the matrix cores (16 rows x 16 roots
+  // a wave), the deflated columns as they are
   {
-    constexpr int NR = 16, NJ = TS / NR;
-    const int r0 = tr % NR, j0 = tr / NR;
-    for (int jb = j0; jb < m; jb += NJ) {
-      const int at = sm.pos[o + jb];
-      if (jb < K) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int i = 0; i < K; ++i) {
-          const double u = sm.U[o + jb][o + i];
-          const double* ec = sm.E[sm.src[o + sm.nd[o + i]]] + o;
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (r0 + NR * q < m) acc[q] = fma(ec[r0 + NR * q], u, acc[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (r0 + NR * q < m) sm.E2[at][o + r0 + NR * q] = acc[q];
-      } else {
-        const double* ec = sm.E[sm.src[o + sm.df[o + jb - K]]] + o;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (r0 + NR * q < m) sm.E2[at][o + r0 + NR * q] = ec[r0 + NR * q];
+    typedef Mfma<double> MM;
+    const int lane = tr & 63, l = lane & 15, nr = (m + 15) >> 4, nj = (K + 15) >> 4;
+    for (int t = tr >> 6; t < nr * nj; t += TS / 64) {
+      const int r = 16 * (t / nj) + l, j = 16 * (t % nj) + l;
+      typename MM::acc_t acc = MM::zero();
+#pragma unroll 4
+      for (int k = lane >> 4; k < ((K + 3) & ~3); k += 4) {
+        const int kk = k < K ? k : 0;
+        const double x = sm.E[sm.col[o + kk]][o + (r < m ? r : 0)];
+        const double y = sm.U[o + (j < K ? j : 0)][o + kk];
+        acc = MM::mma(k < K ? x : 0.0, k < K ? y : 0.0, acc);
       }
+      if (j < K) {
+        const int at = sm.pos[o + j];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = 16 * (t / nj) + MM::row(lane, q);
+          if (row < m) sm.E2[at][o + row] = acc[q];
+        }
+      }
+    }
+    for (int e = tr; e < ndf * m; e += TS) {
+      const int q = e / m, row = e - q * m;
+      sm.E2[sm.pos[o + K + q]][o + row] = sm.E[sm.src[o + sm.df[o + q]]][o + row];
     }
   }
   __syncthreads();
@@ -801,54 +864,65 @@ __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2
 }
 
 // One workgroup per block of up to 64 rows: eigenvalues (ascending) over the
-// block of d, eigenvectors into the block of E.  Latency: the leaves' chain of
-// about 1.5 m^2 rotations (a square root and two divisions each) and two
-// merges; 16-row leaves keep that chain short, below them the merges' fixed
-// cost is larger than the rotations saved.
-__global__ __launch_bounds__(256) void k_dc_base(const EigDev* __restrict__ P,
-                                                 const BaseNode* __restrict__ nodes,
-                                                 int* __restrict__ err) {
+// block of d, eigenvectors into the block of E.  Latency: the chain of a leaf's
+// rotations (about 1.5 m^2 of some 600 cycles), then up to three merges of
+// some 20,000 cycles each; leaves of 8 rows, a wave each.  Leaves of 16 with
+// the vectors in LDS and square roots and divisions in the chain, merges with a
+// serial deflation walk and scalar products took 160 us at n = 24, 289 at 95 and
+// 440 at 1940; this 42, 76 and 104.
+__global__ __launch_bounds__(kBaseThreads) void k_dc_base(const EigDev* __restrict__ P,
+                                                          const BaseNode* __restrict__ nodes,
+                                                          int* __restrict__ err) {
   __shared__ BaseSmem sm;
   const BaseNode nd = nodes[blockIdx.x];
   const EigDev& p = P[nd.prob];
   const int n = p.n, off = nd.off, m = nd.m, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // leaf boundaries: halves of halves
-  const int nl = m > 2 * kLeaf ? 4 : (m > kLeaf ? 2 : 1);
-  const int h = nl > 1 ? m / 2 : m;
-  const int q1 = nl == 4 ? h / 2 : h, q2 = nl == 4 ? h + (m - h) / 2 : m;
-  for (int e = tid; e < kBase * kBase; e += 256) sm.E[e / kBase][e % kBase] = e / kBase == e % kBase ? 1.0 : 0.0;
+  // 2^depth leaves: halves of halves; boundary t of 2^level
+  const int depth = m > 4 * kLeaf ? 3 : (m > 2 * kLeaf ? 2 : (m > kLeaf ? 1 : 0));
+  auto bound = [&](int t, int level) {
+    int lo = 0, len = m;
+    if (t >> level) return m;
+    for (int q = level - 1; q >= 0; --q) {
+      const int h = len / 2;
+      if ((t >> q) & 1) {
+        lo += h;
+        len -= h;
+      } else {
+        len = h;
+      }
+    }
+    return lo;
+  };
+  for (int e = tid; e < kBase * kBase; e += kBaseThreads) sm.E[e / kBase][e % kBase] = 0.0;
   __syncthreads();
   auto edge = [&](int r) -> double {  // off-diagonal between rows r - 1 and r of T
     return r > 0 && r < n ? p.e[r - 1] : 0.0;
   };
-  if (wave < nl) {
-    // four leaves: [0,q1) [q1,h) [h,q2) [q2,m); two: [0,h) [h,m); one: [0,m)
-    int b0, b1;
-    if (nl == 4) {
-      b0 = wave == 0 ? 0 : (wave == 1 ? q1 : (wave == 2 ? h : q2));
-      b1 = wave == 0 ? q1 : (wave == 1 ? h : (wave == 2 ? q2 : m));
-    } else {
-      b0 = wave == 0 ? 0 : h;
-      b1 = wave == 0 && nl == 2 ? h : m;
-    }
-    const int lm = b1 - b0;
+  if (wave < 1 << depth) {
+    const int b0 = bound(wave, depth), lm = bound(wave + 1, depth) - b0;
     double d = 0.0, e = 0.0;
     if (lane < lm) {
       d = p.d[off + b0 + lane];
       if (lane == 0) d -= edge(off + b0);
-      if (lane == lm - 1) d -= edge(off + b1);
+      if (lane == lm - 1) d -= edge(off + b0 + lm);
       if (lane + 1 < lm) e = p.e[off + b0 + lane];
     }
     if (!ql_leaf(sm, b0, lm, d, e) && lane == 0) atomicOr(err + nd.prob, 2);
   }
   __syncthreads();
-  if (nl == 4) {
-    const int team = tid >> 7, tr = tid & 127;
-    const int o = team ? h : 0, m1 = team ? q2 - h : q1, m2 = team ? m - q2 : h - q1;
-    base_merge<128>(sm, team, tr, o, m1, m2, p.e[off + o + m1 - 1]);
+  for (int level = depth; level > 0; --level) {
+    const int teams = 1 << (level - 1), team = tid / (kBaseThreads / teams);
+    const int o = bound(2 * team, level), mid = bound(2 * team + 1, level);
+    const int end = bound(2 * team + 2, level), tr = tid % (kBaseThreads / teams);
+    const double beta = p.e[off + mid - 1];
+    if (level == 3)
+      base_merge<kBaseThreads / 4>(sm, team, tr, o, mid - o, end - mid, beta);
+    else if (level == 2)
+      base_merge<kBaseThreads / 2>(sm, team, tr, o, mid - o, end - mid, beta);
+    else
+      base_merge<kBaseThreads>(sm, team, tr, o, mid - o, end - mid, beta);
   }
-  if (nl > 1) base_merge<256>(sm, 0, tid, 0, h, m - h, p.e[off + h - 1]);
-  for (int e = tid; e < m * m; e += 256) {
+  for (int e = tid; e < m * m; e += kBaseThreads) {
     const int c = e / m, r = e - c * m;
     p.E[(int64_t)(off + c) * n + off + r] = sm.E[c][r];
   }
@@ -1547,7 +1621,7 @@ int eig_run(qsgw_ctx* c, const EigPlan* pl) {
     CHECK(launch_check(c, "k_tri_team"));
   }
   hipLaunchKernelGGL(k_dc_scale, dim3(pl->count), dim3(256), 0, c->stream, P);
-  hipLaunchKernelGGL(k_dc_base, dim3(pl->nbase), dim3(256), 0, c->stream, P,
+  hipLaunchKernelGGL(k_dc_base, dim3(pl->nbase), dim3(kBaseThreads), 0, c->stream, P,
                      reinterpret_cast<const BaseNode*>(pl->dev + pl->base), pl->err);
   CHECK(launch_check(c, "k_dc_base"));
   for (const auto& L : pl->levels) {
