@@ -1318,6 +1318,24 @@ void add_job(std::vector<J>& v, int64_t& wg, OA a, OB b, EPI e, int64_t M, int64
   wg += ((M + 63) / 64) * ((N + 63) / 64);
 }
 
+// A grouped launch with fewer 64 x 64 tiles than the chip has compute units is
+// bound by the matrix cores of those it reaches: it takes 32 x 32 tiles (k tiles
+// of 32, half the barriers), as long as the launch stays this small.  Order 1940,
+// V^T X of a block (62 tiles of 64): 59 -> 27 us.
+constexpr int64_t kFewTiles = 256;
+template <class J>
+bool fine_tiles(std::vector<J>& v, int64_t& wg) {
+  if (wg >= kFewTiles) return false;
+  wg = 0;
+  for (J& j : v) {
+    j.tiles_m = (j.M + 31) / 32;
+    j.tiles_n = (j.N + 31) / 32;
+    j.wg_begin = wg;
+    wg += j.tiles_m * j.tiles_n;
+  }
+  return true;
+}
+
 // Appends a table to the upload image; returns its offset.
 template <class T>
 size_t put(std::vector<char>& img, const std::vector<T>& v) {
@@ -1356,10 +1374,12 @@ struct EigPlan {
     size_t nodes, pre, preq, res, jobs;
     int nn, cols, qblk;
     int64_t njobs, nwg;
+    bool fine;
   };
   struct Products {
     size_t at;
     int64_t n, nwg;
+    bool fine;  // 32 x 32 tiles
   };
   struct Step {
     Products w, x;
@@ -1527,6 +1547,7 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
               EpiEigCols{Eb + nd2.n1, N, pos}, n, nd2.n2, n);
     }
     EigPlan::Level L;
+    L.fine = fine_tiles(jobs, wg);
     L.nodes = put(pl->img, lev[dep]);
     L.pre = put(pl->img, pre);
     L.preq = put(pl->img, preq);
@@ -1559,8 +1580,9 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
               EpiStore{p.U + j0 * n, n, 0, 0, 1.0}, kb, len, kb);
     }
   }
-  pl->gram = {put(pl->img, gram), (int64_t)gram.size(), gwg};
-  pl->y = {put(pl->img, yj), (int64_t)yj.size(), ywg};
+  const bool gf = fine_tiles(gram, gwg), yf = fine_tiles(yj, ywg);
+  pl->gram = {put(pl->img, gram), (int64_t)gram.size(), gwg, gf};
+  pl->y = {put(pl->img, yj), (int64_t)yj.size(), ywg, yf};
   pl->tblocks = put(pl->img, tb);
   pl->ntb = (unsigned)tb.size();
   for (int64_t s = 0; s < maxb; ++s) {
@@ -1578,8 +1600,9 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
               Strided<false>{p.U + j0 * n, 1, n, 0, len}, EpiMinus{p.E, n}, n, len, kb);
     }
     EigPlan::Step st;
-    st.w = {put(pl->img, wj), (int64_t)wj.size(), wwg};
-    st.x = {put(pl->img, xj), (int64_t)xj.size(), xwg};
+    const bool wf = fine_tiles(wj, wwg), xf = fine_tiles(xj, xwg);
+    st.w = {put(pl->img, wj), (int64_t)wj.size(), wwg, wf};
+    st.x = {put(pl->img, xj), (int64_t)xj.size(), xwg, xf};
     pl->steps.push_back(st);
   }
   CHECK(ws_get(c, W_EIGD_T + 3 * set, pl->img.size() + 256, &pl->dev));
@@ -1597,8 +1620,12 @@ static int run_products(qsgw_ctx* c, const EigPlan* pl, const EigPlan::Products&
   typedef decltype(jobs->a) OA;
   typedef decltype(jobs->b) OB;
   typedef decltype(jobs->e) EP;
-  hipLaunchKernelGGL((gemm_grouped_kernel<64, 64, OA, OB, EP, false>), dim3((unsigned)g.nwg),
-                     dim3(256), 0, c->stream, jobs, g.n, g.nwg);
+  if (g.fine)
+    hipLaunchKernelGGL((gemm_grouped_kernel<32, 32, OA, OB, EP, false, 32>),
+                       dim3((unsigned)g.nwg), dim3(256), 0, c->stream, jobs, g.n, g.nwg);
+  else
+    hipLaunchKernelGGL((gemm_grouped_kernel<64, 64, OA, OB, EP, false>), dim3((unsigned)g.nwg),
+                       dim3(256), 0, c->stream, jobs, g.n, g.nwg);
   return launch_check(c, what);
 }
 
@@ -1639,7 +1666,7 @@ int eig_run(qsgw_ctx* c, const EigPlan* pl) {
     hipLaunchKernelGGL(k_dc_vecs, dim3((unsigned)L.cols), dim3(256), 0, c->stream, P, nodes, L.nn,
                        pre, res);
     CHECK(launch_check(c, "k_dc_vecs"));
-    CHECK(run_products(c, pl, EigPlan::Products{L.jobs, L.njobs, L.nwg}, (const JobMerge*)nullptr,
+    CHECK(run_products(c, pl, EigPlan::Products{L.jobs, L.njobs, L.nwg, L.fine}, (const JobMerge*)nullptr,
                        "eig merge"));
   }
   hipLaunchKernelGGL(k_dc_finish, dim3(pl->count), dim3(256), 0, c->stream, P);
