@@ -534,8 +534,9 @@ int qsgw_iterate_batched(qsgw_ctx* ctx, int64_t nmol, const qsgw_problem* probs,
  * persistent grid of n workgroups per compute unit that walk contiguous
  * tile ranges; dc_leaf (integer in [16, 46340]): the two-stage solver's
  * projection (inside qsgw_iterate) solves the tridiagonal eigenproblem by
- * divide and conquer, halving blocks larger than dc_leaf and handing blocks
- * up to that order to rocSOLVER dstedc; panel_coop (0 or 1): 1 factors each
+ * divide and conquer, halving blocks larger than dc_leaf and forming the
+ * eigenvectors of blocks up to that order (orders above 6144 by rocSOLVER
+ * dstedc); panel_coop (0 or 1): 1 factors each
  * Householder panel of the two-stage solver's dense -> band stage in one
  * cooperative launch (the panel's rows held on chip, one exchange between
  * workgroups a column) and chases the band's bulges in one (a window a

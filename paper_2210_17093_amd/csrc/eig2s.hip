@@ -18,7 +18,8 @@
 //      order.  One launch for all sweeps, a workgroup per k
 //      (k_bulge_chase); orders with more steps a sweep than the device holds
 //      workgroups take one launch per time (k_bulge);
-//   3. tridiagonal eigenproblem: rocSOLVER divide and conquer (dstedc),
+//   3. tridiagonal eigenproblem: divide and conquer (eigd.hip up to order
+//      kEigTridiagMax, rocSOLVER dstedc above it),
 //      eigenvectors E of the tridiagonal matrix;
 //   4. back-transformations Z = Q1 Q2 E: the bulge-chasing reflectors in
 //      blocks of g consecutive sweeps at one step k (block (J, k) needs
@@ -1544,11 +1545,15 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
 
   if (!stage3) return QSGW_OK;
   // ---- stage 3: tridiagonal eigenproblem (eigenvectors E into A) ----
-  RB_TRY(c, rocsolver_dstedc(h, rocblas_evect_tridiagonal, ni, dd, ee, A, ni,
-                             (rocblas_int*)(flags + 1)), what);
-  int info = 0;
-  CHECK(read_flag(c, flags + 1, &info));
-  if (info != 0) return fail(c, QSGW_ERR_SOLVER, "%s: dstedc info = %d", what, info);
+  if (n <= kEigTridiagMax) {
+    CHECK(eig_tridiag(c, n, dd, ee, A, what));
+  } else {
+    RB_TRY(c, rocsolver_dstedc(h, rocblas_evect_tridiagonal, ni, dd, ee, A, ni,
+                               (rocblas_int*)(flags + 1)), what);
+    int info = 0;
+    CHECK(read_flag(c, flags + 1, &info));
+    if (info != 0) return fail(c, QSGW_ERR_SOLVER, "%s: dstedc info = %d", what, info);
+  }
   HIP_TRY(c, hipMemcpyAsync(evals, dd, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice,
                             c->stream));
   return QSGW_OK;

@@ -954,8 +954,8 @@ typedef GemmJob<Strided<true>, Strided<false>, EpiEigCols> JobMerge;
 
 constexpr int kPrepThreads = 1024;
 struct PrepSmem {
-  double ds[kEigTeamMax], zs[kEigTeamMax];
-  int src[kEigTeamMax], S[kEigTeamMax];
+  double ds[kEigTridiagMax], zs[kEigTridiagMax];
+  int src[kEigTridiagMax], S[kEigTridiagMax];
   double red[2][16];
   int wsum[16], any, K, nrot;
 };
@@ -1422,6 +1422,68 @@ bool eig_team_fits(qsgw_ctx* c, int64_t n) {
   return team <= 1 || team <= team_budget(c);
 }
 
+// Tables of the divide and conquer: base blocks, then the merges level by level.
+static void plan_merges(EigPlan* pl, const std::vector<EigDev>& P) {
+  std::vector<BaseNode> base;
+  std::vector<std::vector<Node>> lev;
+  struct Rec {
+    int prob, off, n, depth;
+  };
+  std::vector<Rec> stack;
+  for (size_t i = 0; i < P.size(); ++i) stack.push_back({(int)i, 0, P[i].n, 0});
+  while (!stack.empty()) {
+    const Rec r = stack.back();
+    stack.pop_back();
+    if (r.n <= kBase) {
+      base.push_back({r.prob, r.off, r.n});
+      continue;
+    }
+    if ((int)lev.size() <= r.depth) lev.resize((size_t)r.depth + 1);
+    const int n1 = r.n / 2;
+    lev[(size_t)r.depth].push_back({r.prob, r.off, n1, r.n - n1});
+    stack.push_back({r.prob, r.off, n1, r.depth + 1});
+    stack.push_back({r.prob, r.off + n1, r.n - n1, r.depth + 1});
+  }
+  pl->base = put(pl->img, base);
+  pl->nbase = (unsigned)base.size();
+  for (size_t dep = lev.size(); dep-- > 0;) {
+    std::vector<int> pre, preq;
+    std::vector<JobMerge> jobs;
+    std::vector<NodeRes> res(lev[dep].size());
+    int cols = 0, qb = 0;
+    int64_t wg = 0;
+    for (const Node& nd2 : lev[dep]) {
+      const EigDev& p = P[(size_t)nd2.prob];
+      const int64_t N = p.n, n = nd2.n1 + nd2.n2, off = nd2.off;
+      pre.push_back(cols);
+      preq.push_back(qb);
+      cols += (int)n;
+      qb += (int)((n + 3) / 4);
+      const double* Ub = p.U + off * N;
+      const double* Bb = p.B + off * N + off;
+      const int* pos = p.idx + I_POS * N + off;
+      double* Eb = p.E + off * N + off;
+      add_job(jobs, wg, Strided<true>{Ub, n, 1, 0, n}, Strided<false>{Bb, 1, N, 0, nd2.n1},
+              EpiEigCols{Eb, N, pos}, n, nd2.n1, n);
+      add_job(jobs, wg, Strided<true>{Ub, n, 1, 0, n}, Strided<false>{Bb + nd2.n1, 1, N, 0, nd2.n2},
+              EpiEigCols{Eb + nd2.n1, N, pos}, n, nd2.n2, n);
+    }
+    EigPlan::Level L;
+    L.fine = fine_tiles(jobs, wg);
+    L.nodes = put(pl->img, lev[dep]);
+    L.pre = put(pl->img, pre);
+    L.preq = put(pl->img, preq);
+    L.res = put(pl->img, res);
+    L.jobs = put(pl->img, jobs);
+    L.nn = (int)lev[dep].size();
+    L.cols = cols;
+    L.qblk = qb;
+    L.njobs = (int64_t)jobs.size();
+    L.nwg = wg;
+    pl->levels.push_back(L);
+  }
+}
+
 int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, int set) {
   pl->count = (unsigned)count;
   std::vector<EigDev> P((size_t)count);
@@ -1501,65 +1563,7 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
     if (wg.empty()) return fail(c, QSGW_ERR_UNSUPPORTED, "eigensolver: a team exceeds the device");
     pl->rounds.push_back({put(pl->img, wg), (unsigned)wg.size(), coop});
   }
-  // ---- divide and conquer tree ----
-  std::vector<BaseNode> base;
-  std::vector<std::vector<Node>> lev;
-  struct Rec {
-    int prob, off, n, depth;
-  };
-  std::vector<Rec> stack;
-  for (int64_t i = 0; i < count; ++i) stack.push_back({(int)i, 0, P[(size_t)i].n, 0});
-  while (!stack.empty()) {
-    const Rec r = stack.back();
-    stack.pop_back();
-    if (r.n <= kBase) {
-      base.push_back({r.prob, r.off, r.n});
-      continue;
-    }
-    if ((int)lev.size() <= r.depth) lev.resize((size_t)r.depth + 1);
-    const int n1 = r.n / 2;
-    lev[(size_t)r.depth].push_back({r.prob, r.off, n1, r.n - n1});
-    stack.push_back({r.prob, r.off, n1, r.depth + 1});
-    stack.push_back({r.prob, r.off + n1, r.n - n1, r.depth + 1});
-  }
-  pl->base = put(pl->img, base);
-  pl->nbase = (unsigned)base.size();
-  for (size_t dep = lev.size(); dep-- > 0;) {
-    std::vector<int> pre, preq;
-    std::vector<JobMerge> jobs;
-    std::vector<NodeRes> res(lev[dep].size());
-    int cols = 0, qb = 0;
-    int64_t wg = 0;
-    for (const Node& nd2 : lev[dep]) {
-      const EigDev& p = P[(size_t)nd2.prob];
-      const int64_t N = p.n, n = nd2.n1 + nd2.n2, off = nd2.off;
-      pre.push_back(cols);
-      preq.push_back(qb);
-      cols += (int)n;
-      qb += (int)((n + 3) / 4);
-      const double* Ub = p.U + off * N;
-      const double* Bb = p.B + off * N + off;
-      const int* pos = p.idx + I_POS * N + off;
-      double* Eb = p.E + off * N + off;
-      add_job(jobs, wg, Strided<true>{Ub, n, 1, 0, n}, Strided<false>{Bb, 1, N, 0, nd2.n1},
-              EpiEigCols{Eb, N, pos}, n, nd2.n1, n);
-      add_job(jobs, wg, Strided<true>{Ub, n, 1, 0, n}, Strided<false>{Bb + nd2.n1, 1, N, 0, nd2.n2},
-              EpiEigCols{Eb + nd2.n1, N, pos}, n, nd2.n2, n);
-    }
-    EigPlan::Level L;
-    L.fine = fine_tiles(jobs, wg);
-    L.nodes = put(pl->img, lev[dep]);
-    L.pre = put(pl->img, pre);
-    L.preq = put(pl->img, preq);
-    L.res = put(pl->img, res);
-    L.jobs = put(pl->img, jobs);
-    L.nn = (int)lev[dep].size();
-    L.cols = cols;
-    L.qblk = qb;
-    L.njobs = (int64_t)jobs.size();
-    L.nwg = wg;
-    pl->levels.push_back(L);
-  }
+  plan_merges(pl, P);
   // ---- back-transformation ----
   std::vector<JobGW> gram;
   std::vector<JobY> yj;
@@ -1629,24 +1633,8 @@ static int run_products(qsgw_ctx* c, const EigPlan* pl, const EigPlan::Products&
   return launch_check(c, what);
 }
 
-int eig_run(qsgw_ctx* c, const EigPlan* pl) {
-  const EigDev* P = reinterpret_cast<const EigDev*>(pl->dev + pl->probs);
-  const dim3 per_prob(pl->count > 8 ? 64 : 512, pl->count);
-  if (pl->clear) hipLaunchKernelGGL(k_tri_clear, per_prob, dim3(256), 0, c->stream, P);
-  CHECK(launch_check(c, "k_tri_clear"));
-  for (const auto& r : pl->rounds) {
-    const TeamWg* wg = reinterpret_cast<const TeamWg*>(pl->dev + r.at);
-    int* err = pl->err;
-    if (r.coop) {
-      CHECK(aux_queues(c));
-      void* args[] = {&P, &wg, &err};
-      HIP_TRY(c, hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_tri_team), dim3(r.wgs),
-                                            dim3(kTeamThreads), args, 0, c->stream));
-    } else {
-      hipLaunchKernelGGL(k_tri_team, dim3(r.wgs), dim3(kTeamThreads), 0, c->stream, P, wg, err);
-    }
-    CHECK(launch_check(c, "k_tri_team"));
-  }
+// Eigenpairs of every problem's d, e: E, and ev ascending.
+static int run_merges(qsgw_ctx* c, const EigPlan* pl, const EigDev* P) {
   hipLaunchKernelGGL(k_dc_scale, dim3(pl->count), dim3(256), 0, c->stream, P);
   hipLaunchKernelGGL(k_dc_base, dim3(pl->nbase), dim3(kBaseThreads), 0, c->stream, P,
                      reinterpret_cast<const BaseNode*>(pl->dev + pl->base), pl->err);
@@ -1670,6 +1658,28 @@ int eig_run(qsgw_ctx* c, const EigPlan* pl) {
                        "eig merge"));
   }
   hipLaunchKernelGGL(k_dc_finish, dim3(pl->count), dim3(256), 0, c->stream, P);
+  return launch_check(c, "k_dc_finish");
+}
+
+int eig_run(qsgw_ctx* c, const EigPlan* pl) {
+  const EigDev* P = reinterpret_cast<const EigDev*>(pl->dev + pl->probs);
+  const dim3 per_prob(pl->count > 8 ? 64 : 512, pl->count);
+  if (pl->clear) hipLaunchKernelGGL(k_tri_clear, per_prob, dim3(256), 0, c->stream, P);
+  CHECK(launch_check(c, "k_tri_clear"));
+  for (const auto& r : pl->rounds) {
+    const TeamWg* wg = reinterpret_cast<const TeamWg*>(pl->dev + r.at);
+    int* err = pl->err;
+    if (r.coop) {
+      CHECK(aux_queues(c));
+      void* args[] = {&P, &wg, &err};
+      HIP_TRY(c, hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_tri_team), dim3(r.wgs),
+                                            dim3(kTeamThreads), args, 0, c->stream));
+    } else {
+      hipLaunchKernelGGL(k_tri_team, dim3(r.wgs), dim3(kTeamThreads), 0, c->stream, P, wg, err);
+    }
+    CHECK(launch_check(c, "k_tri_team"));
+  }
+  CHECK(run_merges(c, pl, P));
   CHECK(run_products(c, pl, pl->gram, (const JobGW*)nullptr, "eig Gram"));
   if (pl->ntb > 0)
     hipLaunchKernelGGL(k_wy_t, dim3(pl->ntb), dim3(256), 0, c->stream,
@@ -1705,4 +1715,39 @@ int eig_team(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what)
   CHECK(eig_plan(c, &pl, &p, 1, 0));
   CHECK(eig_run(c, &pl));
   return eig_check(c, &pl, what, nullptr);
+}
+
+// Eigenpairs of the tridiagonal d, e of order n <= kEigTridiagMax: d ascending
+// eigenvalues, E [n][n] the eigenvectors (column-major); e is destroyed.
+int eig_tridiag(qsgw_ctx* c, int64_t n, double* d, double* e, double* E, const char* what) {
+  if (n < 1 || n > kEigTridiagMax)
+    return fail(c, QSGW_ERR_UNSUPPORTED, "%s: tridiagonal order %lld", what, (long long)n);
+  EigPlan pl;
+  pl.count = 1;
+  double* D = nullptr;
+  int* I = nullptr;
+  CHECK(ws_get(c, W_EIGD_F, (size_t)(2 * n * n + kVec * n + 8), &D));
+  CHECK(ws_get(c, W_EIGD_I, (size_t)(1 + kIdx * n), &I));
+  pl.err = I;
+  hipLaunchKernelGGL(k_eig_clear_err, dim3(1), dim3(256), 0, c->stream, pl.err, (int64_t)1);
+  CHECK(launch_check(c, "k_eig_clear_err"));
+  EigDev p{};
+  p.n = (int)n;
+  p.ev = p.d = d;
+  p.e = e;
+  p.E = E;
+  p.B = D;
+  p.U = D + n * n;
+  p.vec = D + 2 * n * n;
+  p.scale = p.vec + kVec * n;
+  p.idx = I + 1;
+  const std::vector<EigDev> P(1, p);
+  pl.probs = put(pl.img, P);
+  plan_merges(&pl, P);
+  CHECK(ws_get(c, W_EIGD_T, pl.img.size() + 256, &pl.dev));
+  HIP_TRY(c, hipMemcpyAsync(pl.dev, pl.img.data(), pl.img.size(), hipMemcpyHostToDevice,
+                            c->stream));
+  CHECK(run_merges(c, &pl, reinterpret_cast<const EigDev*>(pl.dev + pl.probs)));
+  int64_t at = 0;
+  return eig_check(c, &pl, what, &at);
 }

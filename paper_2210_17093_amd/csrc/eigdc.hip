@@ -1,14 +1,15 @@
 // Tridiagonal stage of the two-stage Casida eigensolver in projection mode:
 // divide and conquer whose merges are done here, on the projected columns
-// only; the leaves (order <= the tile table's dc_leaf) are solved by rocSOLVER
-// dstedc.
+// only; the leaves (order <= the tile table's dc_leaf) are solved with their
+// eigenvectors formed: up to kEigTridiagMax by the one-stage solver's divide and
+// conquer (eigd.hip), above it by rocSOLVER dstedc.
 //
 // A tridiagonal T (order n, diagonal d, off-diagonal e) is torn at
 // n1 = n / 2 (Cuppen): with beta = e[n1 - 1],
 //   T = diag(T1, T2) + |beta| v v^T,  v = e_{n1-1} + sign(beta) e_{n1},
 // where T1 and T2 are the leading and trailing blocks with |beta| taken off
 // their touching diagonal entries.  With T1 = E1 D1 E1^T and T2 = E2 D2 E2^T
-// (rocSOLVER dstedc) and Q = diag(E1, E2), T = Q (D + rho z z^T) Q^T with
+// (leaves) and Q = diag(E1, E2), T = Q (D + rho z z^T) Q^T with
 // z = Q^T v / |Q^T v| and rho = |beta| |Q^T v|^2.  The eigenpairs of the
 // rank-one modification D + rho z z^T (poles d sorted ascending):
 //   - deflated: a pole with rho |z_i| <= tol = 8 eps max(max |d|, rho) is an
@@ -456,9 +457,9 @@ struct DcLevel {
 };
 struct DcRun {
   std::vector<DcLevel> lv;
-  int* info;  // one dstedc status per leaf
+  int* info;  // one status per leaf that dstedc solves
   int leaves = 0;
-  int64_t leaf;  // leaves up to this order go to rocSOLVER dstedc
+  int64_t leaf;  // blocks up to this order are leaves
   const char* what;
 };
 
@@ -536,11 +537,17 @@ static int dc_merge(qsgw_ctx* c, int64_t n1, int64_t n2, const double* w, const 
 static int dc_node(qsgw_ctx* c, DcRun& run, int depth, int64_t n, double* d, double* e, double* A,
                    const double* X, int64_t ldx, int64_t q, double* evals, double* R) {
   if (n <= run.leaf) {
-    rocblas_status st = rocsolver_dstedc(c->blas, rocblas_evect_tridiagonal, (rocblas_int)n, d, e,
-                                         A, (rocblas_int)n, (rocblas_int*)(run.info + run.leaves));
-    ++run.leaves;
-    if (st != rocblas_status_success)
-      return fail(c, QSGW_ERR_SOLVER, "%s: rocsolver_dstedc status %d", run.what, (int)st);
+    // (two leaves of 5,200: 72 ms by dstedc, 11 ms by our own merges)
+    if (n <= kEigTridiagMax) {
+      CHECK(eig_tridiag(c, n, d, e, A, run.what));
+    } else {
+      rocblas_status st = rocsolver_dstedc(c->blas, rocblas_evect_tridiagonal, (rocblas_int)n, d,
+                                           e, A, (rocblas_int)n,
+                                           (rocblas_int*)(run.info + run.leaves));
+      ++run.leaves;
+      if (st != rocblas_status_success)
+        return fail(c, QSGW_ERR_SOLVER, "%s: rocsolver_dstedc status %d", run.what, (int)st);
+    }
     // R[P][s] = sum_r X[P][r] E[r][s] (E column-major in A)
     Strided<true> Ax{X, ldx, 1, 0, q};
     Strided<true> Be{A, n, 1, 0, n};
@@ -635,6 +642,7 @@ int tridiag_project_dc(qsgw_ctx* c, int64_t n, double* d, double* e, double* A, 
   } else {
     CHECK(dc_node(c, run, 0, n, d, e, A, X, n, naux, evals, R));
   }
+  if (run.leaves == 0) return QSGW_OK;
   std::vector<int> hinfo((size_t)run.leaves, 0);
   HIP_TRY(c, hipMemcpyAsync(hinfo.data(), run.info, hinfo.size() * sizeof(int),
                             hipMemcpyDeviceToHost, c->stream));

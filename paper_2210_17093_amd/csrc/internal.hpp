@@ -136,7 +136,7 @@ struct Tiles {
   // persistent grid of n workgroups per compute unit walking tile ranges
   int64_t persistent = 0;
   // projected divide and conquer of the two-stage eigensolver: tridiagonal
-  // blocks up to this order are solved by rocSOLVER dstedc
+  // blocks up to this order are solved with their eigenvectors formed
   int64_t dc_leaf = 6144;
   // two-stage eigensolver: 1 = panel QR in one cooperative launch per panel
   // (the per-column launches when the device refuses it), 0 = per-column launches
@@ -216,6 +216,11 @@ int eig_run(qsgw_ctx* c, const EigPlan* pl);
 int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what, int64_t* at);
 // One problem with ld = n, checked.
 int eig_team(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what);
+// Eigenpairs of a tridiagonal of order up to kEigTridiagMax (its divide and
+// conquer alone), checked: d ascending eigenvalues, E [n][n] column-major
+// eigenvectors; e is destroyed.
+constexpr int kEigTridiagMax = 6144;  // (a merge's poles and weights fit in LDS)
+int eig_tridiag(qsgw_ctx* c, int64_t n, double* d, double* e, double* E, const char* what);
 
 // Two-stage dense symmetric eigensolver (eig2s.hip): A [n][n] in, its
 // eigenvectors column-major out, eigenvalues ascending.

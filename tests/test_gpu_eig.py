@@ -338,3 +338,24 @@ def test_two_stage_tall_panels(q, ctx):
     Zs = Z[some]  # rows are eigenvectors
     assert float((Zs @ Z.T - torch.eye(n, dtype=torch.float64, device="cuda")[some]).abs().max()) <= 1e-11
     assert float((Zs @ A - ev[some, None] * Zs).abs().max()) <= 1e-11 * 62
+
+
+@pytest.mark.parametrize("n", [3073, 6143])
+def test_two_stage_large_tridiagonals(q, ctx, n):
+    """Orders of the two-stage solver whose whole tridiagonal problem is solved by
+    the merges with formed eigenvectors, up to the largest: residual, norm and
+    order of some of the eigenpairs, and the trace."""
+    print("two-stage eigensolve, order", n, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randn(n, n, generator=g, dtype=torch.float64, device="cuda") / n ** 0.5
+    A = 0.5 * (A + A.T)
+    A.diagonal().add_(torch.linspace(10.0, 60.0, n, dtype=torch.float64, device="cuda"))
+    Z, Om = q.qsgw_rpa_solve(ctx, A.clone())
+    ev = Om * Om
+    assert bool((ev[1:] >= ev[:-1]).all())
+    assert abs(float(ev.sum() - A.diagonal().sum())) <= 1e-11 * n * 62
+    some = torch.linspace(0, n - 1, 24, device="cuda").long()
+    Zs = Z[some]  # rows are eigenvectors
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")[some]
+    assert float((Zs @ Z.T - eye).abs().max()) <= 1e-11
+    assert float((Zs @ A - ev[some, None] * Zs).abs().max()) <= 1e-11 * 62
