@@ -398,7 +398,7 @@ __global__ void k_panel_r(double* __restrict__ P, int64_t lda, int b, const doub
 // T factor of a panel's k reflectors from their Gram matrix G[i][j] = v_i . v_j
 // (row-major, ld k) and tau, one workgroup (the forward, column-wise convention:
 // H_0 H_1 ... H_{k-1} = I - V T V^T); T column-major, ld ldt.
-// One column after another took 115 us a panel of 64, this 23 us.
+// One column after another took 100 us a panel of 64, this 11 us.
 __global__ __launch_bounds__(256) void k_panel_t(const double* __restrict__ G, int k,
                                                  const double* __restrict__ tau,
                                                  double* __restrict__ T, int ldt) {
@@ -1344,6 +1344,11 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
       double *tp = tau1 + p * b, *U2v = U2s + b * n;
       int64_t lda = n, mm = m;
       void* args[] = {&P, &lda, &mm, &sl, &se, &G, &gm, &V, &U1s, &U2v, &lda, &tp, &perr};
+      // The cooperative queue must not wait for this stream's kernels: while one of
+      // its packets does, every kernel here takes 14 to 28 us longer (order 10,400:
+      // a panel's 12 launches 18 to 46 us each, 4 to 18 with the wait on the host;
+      // iteration with 300 basis functions 298 -> 240 ms).
+      HIP_TRY(c, hipStreamSynchronize(c->stream));
       const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_panel_coop),
                                                       dim3((unsigned)G), dim3(256), args, 0,
                                                       c->stream);
