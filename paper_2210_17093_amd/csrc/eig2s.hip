@@ -452,6 +452,16 @@ static int gemm_long_k(qsgw_ctx* c, const char* what, OA A, OB B, double* C, int
   return gemm_shape<double, false, 32>(c, SH_64x64, what, A, B, E, M, N, K, 1);
 }
 
+// A panel's thin products (64 rows: as many 64 x 64 tiles as the other side has
+// blocks of 64, one to a compute unit at best): 32 x 32 tiles put several
+// workgroups on each, which hide each other's loads, and k tiles of 32 halve
+// the barriers.  Order 10,400, panel, W and X corrections: 25.9 -> 14.1 us.
+template <class OA, class OB, class EPI>
+static int gemm_thin(qsgw_ctx* c, const char* what, OA A, OB B, EPI E, int64_t M, int64_t N,
+                     int64_t K) {
+  return gemm_t<double, 32, 32, false, 32>(c, what, A, B, E, M, N, K, 1, SplitPlan{0, 1});
+}
+
 // X[m][n] -= v (a plain product subtracted from its output).
 struct EpiSub {
   double* X;
@@ -1329,8 +1339,7 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
       Strided<false> A2{U2a + j, 1, n, 0, b};
       Strided<false> B1{U1a + j, 1, n, 0, n - j};
       EpiSub E{A + j * n + j, n};
-      CHECK((gemm_shape<double, false>(c, SH_64x64, "eig/sy2sb panel", A2, B1, E, b, n - j, Kp,
-                                       1)));
+      CHECK(gemm_thin(c, "eig/sy2sb panel", A2, B1, E, b, n - j, Kp));
     }
     // this panel's block of the pending operands: columns [2 b dp, 2 b (dp + 1))
     double* U1s = U1a + 2 * b * dp * n + (j + b);
@@ -1406,7 +1415,7 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
       Strided<true> At{T, b, 1, 0, kk};
       Strided<false> Bv{V, 1, m, 0, m};
       EpiStore E{Y, m, 0, 0, 1.0};
-      CHECK((gemm_shape<double, false>(c, SH_64x64, "eig/sy2sb Y", At, Bv, E, kk, m, kk, 1)));
+      CHECK(gemm_thin(c, "eig/sy2sb Y", At, Bv, E, kk, m, kk));
     }
     // X = S Y  (X^T[c][r] = sum_k Y[k][c] S[k][r], S symmetric), split over k,
     // minus the pending updates: X -= U1a (U2a^T Y) on rows j+b .. n-1
@@ -1421,7 +1430,7 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
         Strided<false> Ag{Gp, 1, kk, 0, kk};
         Strided<false> Bu{U1a + j + b, 1, n, 0, m};
         EpiSub E{X, m};
-        CHECK((gemm_shape<double, false>(c, SH_64x64, "eig/sy2sb X corr", Ag, Bu, E, kk, m, Kp, 1)));
+        CHECK(gemm_thin(c, "eig/sy2sb X corr", Ag, Bu, E, kk, m, Kp));
       }
     }
     // Z1 = V^T X  (Z1[i][c] = sum_r V(r, i) X(r, c)), Z2 = T^T Z1
@@ -1432,14 +1441,14 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
       Strided<true> At{T, b, 1, 0, kk};
       Strided<false> Bz{Z1, 1, kk, 0, kk};
       EpiStore E{Z2, kk, 0, 0, 1.0};
-      CHECK((gemm_shape<double, false>(c, SH_64x64, "eig/sy2sb Z2", At, Bz, E, kk, kk, kk, 1)));
+      CHECK(gemm_thin(c, "eig/sy2sb Z2", At, Bz, E, kk, kk, kk));
     }
     // W = X - 1/2 V Z2 into this panel's W halves of U1a and U2a
     {
       Strided<false> Az{Z2, 1, kk, 0, kk};
       Strided<false> Bv{V, 1, m, 0, m};
       EpiPanelW E{X, U1s + b * n, U2s, m, n};
-      CHECK((gemm_shape<double, false>(c, SH_64x64, "eig/sy2sb W", Az, Bv, E, kk, m, kk, 1)));
+      CHECK(gemm_thin(c, "eig/sy2sb W", Az, Bv, E, kk, m, kk));
     }
     ++dp;
     if (dp == kDelay || p == np - 1) {
