@@ -141,6 +141,7 @@ struct Tiles {
   // two-stage eigensolver: 1 = panel QR in one cooperative launch per panel
   // (the per-column launches when the device refuses it), 0 = per-column launches
   int64_t panel_coop = 1;
+  bool chosen = false;  // a table was set: its shapes are taken as they are
 };
 inline int shape_m(int s) { return s == SH_64x64 ? 64 : 128; }
 inline int shape_n(int s) { return s == SH_128x128 ? 128 : 64; }
@@ -430,10 +431,33 @@ inline SplitPlan exchange_split(const Tiles& tl, int64_t nbf, int64_t naux, int6
   return split_plan(naux * nocc, splits_for(t * (t + 1) / 2, naux * nocc, tl.exchange_target));
 }
 
+// FP64 products whose tiles would leave compute units idle take smaller ones,
+// unless a tile table was set: below 256 workgroups (the chip's compute units)
+// 64 x 64, below that again 32 x 32.  The terms of an element and their order
+// stay the same.  24 basis functions, 95 transitions: rho 33 -> 8 us, Casida
+// matrix 28 -> 8 us, residues (tiles of 128 pairs x 128 or 32) 55 -> 24 us.
+constexpr int64_t kFewWgs = 256;
+template <int BM, int BN, bool TRI>
+bool few_wgs(const qsgw_ctx* c, int64_t M, int64_t N, int64_t batch, int64_t nz) {
+  const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
+  return !c->tiles.chosen &&
+         (TRI ? tm * (tm + 1) / 2 : tm * tn) * batch * (nz > 1 ? nz : 1) < kFewWgs;
+}
+
 // GEMM with the tile shape chosen at run time (BK: k-tile depth).
 template <class T, bool TRI, int BK = 16, class OA, class OB, class EPI>
 int gemm_shape(qsgw_ctx* c, int shape, const char* what, OA a, OB b, EPI e, int64_t M, int64_t N,
                int64_t K, int64_t batch, SplitPlan sp = {0, 1}) {
+  if constexpr (std::is_same<T, double>::value) {
+    const bool few = shape == SH_64x64    ? true
+                     : shape == SH_128x64 ? few_wgs<128, 64, TRI>(c, M, N, batch, sp.nz)
+                                          : few_wgs<128, 128, TRI>(c, M, N, batch, sp.nz);
+    if (few) {
+      if (few_wgs<64, 64, TRI>(c, M, N, batch, sp.nz))
+        return gemm_t<T, 32, 32, TRI, BK>(c, what, a, b, e, M, N, K, batch, sp);
+      shape = SH_64x64;
+    }
+  }
   switch (shape) {
     case SH_64x64:
       return gemm_t<T, 64, 64, TRI, BK>(c, what, a, b, e, M, N, K, batch, sp);

@@ -394,7 +394,10 @@ int stage_residues_t(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t ntr, const 
     } else {
       PairRows<8, 16> A{B_mo, nn, 0, nbf, blocks};
       Strided<false> B{rho, 1, ldr, 0, ns};
-      CHECK((gemm_t<CT, 128, 128, false>(c, "residues/w", A, B, E, nblk * 128, ns, naux, 1)));
+      if (few_wgs<128, 128, false>(c, nblk * 128, ns, 1, 1))
+        CHECK((gemm_t<CT, 128, 32, false>(c, "residues/w", A, B, E, nblk * 128, ns, naux, 1)));
+      else
+        CHECK((gemm_t<CT, 128, 128, false>(c, "residues/w", A, B, E, nblk * 128, ns, naux, 1)));
     }
     SPAN_CLOSE(sp);
   }
@@ -1624,6 +1627,7 @@ int qsgw_set_tiles(qsgw_ctx* c, const char* spec) {
   if (!c) return QSGW_ERR_INVALID_ARG;
   Tiles t;  // defaults
   if (spec && *spec) {
+    t.chosen = true;
     static const char* names[TU_COUNT] = {"mo1", "mo2", "casida", "rho", "sigma", "exchange"};
     static const bool square[TU_COUNT] = {false, true, true, false, false, true};
     std::string all(spec);

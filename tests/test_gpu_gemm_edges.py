@@ -7,7 +7,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 F64 = torch.float64
-SHAPES = ["128x128", "128x64", "64x64"]
+SHAPES = ["128x128", "128x64", "64x64", None]  # None: the default table, smaller tiles for few
 # (naux, nbf, nocc): k of 3 to 130, rows of 4 to 17161 with every remainder class
 SIZES = [(3, 2, 1), (7, 5, 2), (16, 16, 3), (17, 31, 8), (33, 65, 1), (130, 63, 9), (31, 131, 2)]
 
@@ -36,7 +36,8 @@ def test_products_at_tile_edges(ctx, naux, nbf, nocc, shape, precision):
     import paper_2210_17093_amd.qsgw as q
     prec, u = {"fp64": (q.PREC_FP64, 2.0 ** -53), "fp32": (q.PREC_FP32, 2.0 ** -24)}[precision]
     mo2 = shape if shape != "128x64" else "64x64"
-    ctx.set_tiles(f"mo1={shape},mo2={mo2},casida={mo2},rho={shape},sigma={shape},rho_target=64")
+    ctx.set_tiles(shape and f"mo1={shape},mo2={mo2},casida={mo2},rho={shape},sigma={shape},"
+                  "rho_target=64")
     try:
         g = torch.Generator().manual_seed(naux * 1000 + nbf)
         B = torch.randn(naux, nbf, nbf, generator=g, dtype=F64)
