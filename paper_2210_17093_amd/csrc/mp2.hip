@@ -58,7 +58,7 @@ int stage_mp2(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc, const double
                          c->stream, D, xo, xsn, xsi, eps, nbf, nocc, i0, ni, eta, R);
       CHECK(launch_check(c, "k_mp2_rhs_occ"));
       const int64_t nvt = (nv + 31) / 32;
-      hipLaunchKernelGGL(k_mp2_rhs_vir, dim3((unsigned)(nvt * nvt), (unsigned)ni, (unsigned)nbf),
+      hipLaunchKernelGGL(k_mp2_rhs_vir, dim3((unsigned)(nvt * (nvt + 1) / 2), (unsigned)ni, (unsigned)nbf),
                          dim3(256), 0, c->stream, D, eps, nbf, nocc, i0, ni, eta, R);
       CHECK(launch_check(c, "k_mp2_rhs_vir"));
     }
