@@ -144,15 +144,16 @@ int qsgw_rpa_build(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc, const
 #define QSGW_EIG_ROCSOLVER 1 /* rocSOLVER dsyevd (one-stage tridiagonal reduction) */
 /* Two-stage reduction, all FP64: dense -> band of half-width 64 by blocked
  * Householder panels whose two-sided updates are matrix products, band ->
- * tridiagonal by bulge chasing, rocSOLVER divide and conquer (dstedc) on the
- * tridiagonal matrix, then both back-transformations (the bulge-chasing
+ * tridiagonal by bulge chasing, divide and conquer on the tridiagonal matrix
+ * (above order 6144 rocSOLVER dstedc), then both back-transformations (the bulge-chasing
  * reflectors in blocks of 64 sweeps, the panel reflectors as block
  * reflectors).  Inside qsgw_iterate and qsgw_gw_unrestricted (and so the
  * open-shell iteration) only the projection of the auxiliary basis on the
  * eigenvectors is needed: the back-transformations act on its
  * N_aux columns and the tridiagonal eigenproblem is solved by divide and
  * conquer whose merges act on those columns too (blocks up to the tile
- * table's dc_leaf by dstedc), so no eigenvector matrix is formed.  Below
+ * table's dc_leaf with their eigenvectors formed), so no whole eigenvector
+ * matrix is.  Below
  * n = 256 it calls dsyevd. */
 #define QSGW_EIG_TWO_STAGE 2
 
@@ -545,8 +546,8 @@ int qsgw_iterate_batched(qsgw_ctx* ctx, int64_t nmol, const qsgw_problem* probs,
  * defaults (mo1=128x64, mo2=64x64, casida=128x128, rho=128x128,
  * sigma=64x64, exchange=64x64, 4096, 2048, 2048, mp2_target=32768,
  * persistent=0, dc_leaf=6144, panel_coop=1); NULL or "" restores all
- * defaults.  Every later product and
- * iteration on the context uses the table (results change only by rounding
+ * defaults (FP64 products with few tiles then take smaller ones).  Every
+ * later product and iteration on the context uses the table (results change only by rounding
  * order).  qsgw_get_tiles writes the current table in the same format.
  */
 int qsgw_set_tiles(qsgw_ctx* ctx, const char* spec);

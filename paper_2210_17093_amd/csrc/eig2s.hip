@@ -16,8 +16,8 @@
 //      of sweep i runs at time 2i + k: the steps sharing a time touch
 //      disjoint rows of the band, so the result equals the sweep-by-sweep
 //      order.  One launch for all sweeps, a workgroup per k
-//      (k_bulge_chase); orders with more steps a sweep than the device holds
-//      workgroups take one launch per time (k_bulge);
+//      (k_bulge_chase); where the device cannot hold one per step, or with
+//      panel_coop = 0, one launch per time (k_bulge);
 //   3. tridiagonal eigenproblem: divide and conquer (eigd.hip up to order
 //      kEigTridiagMax, rocSOLVER dstedc above it),
 //      eigenvectors E of the tridiagonal matrix;
@@ -1508,8 +1508,8 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
                      ldab, AB);
   CHECK(launch_check(c, "k_band_extract"));
   // All sweeps in one launch where the device holds a workgroup per step index
-  // (two to a compute unit: orders up to 32,768 on 256 of them), otherwise one
-  // launch per time of the schedule.
+  // (four to a compute unit: every order the solver takes, on 256 of them),
+  // otherwise one launch per time of the schedule.
   bool chased = false;
   if (c->tiles.panel_coop && K0 <= bulge_wgs(c)) {
     double *UP, *DN;
