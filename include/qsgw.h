@@ -137,9 +137,9 @@ int qsgw_rpa_build(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc, const
 /* Default: up to n = 3072 the library's one-stage solver, which holds the
  * matrix on the chip during its reduction (FP64 iterations and
  * qsgw_rpa_solve; the reduced-precision iterations take dsyevd, as their
- * trajectories hang on the last bits of the eigenvectors); the two-stage
- * solver for n >= 8192; rocSOLVER dsyevd between (and where the device has no
- * cooperative launches). */
+ * trajectories hang on the last bits of the eigenvectors); above it the
+ * two-stage solver, in the reduced precisions from n = 8192 on and dsyevd
+ * below (as up to n = 3072 where the device has no cooperative launches). */
 #define QSGW_EIG_AUTO 0
 #define QSGW_EIG_ROCSOLVER 1 /* rocSOLVER dsyevd (one-stage tridiagonal reduction) */
 /* Two-stage reduction, all FP64: dense -> band of half-width 64 by blocked

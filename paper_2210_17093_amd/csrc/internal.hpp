@@ -598,11 +598,14 @@ int syevd(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what) {
   return QSGW_OK;
 }
 
-// Casida eigenproblems: the two-stage solver from this size on (QSGW_EIG_AUTO).
+// Casida eigenproblems: the two-stage solver above the team solver's orders in
+// FP64 (order 3100: 37 ms, dsyevd 96; 5300: 89 and 239; 8100: 297 and 669),
+// from kEigTwoStageMin on in the reduced precisions (see eig_dense)
+// (QSGW_EIG_AUTO).
 constexpr int64_t kEigTwoStageMin = 8192;
-inline bool eig_two_stage_for(const qsgw_ctx* c, int64_t n) {
+inline bool eig_two_stage_for(const qsgw_ctx* c, int64_t n, bool fp64) {
   return c->eig_solver == QSGW_EIG_TWO_STAGE ||
-         (c->eig_solver == QSGW_EIG_AUTO && n >= kEigTwoStageMin);
+         (c->eig_solver == QSGW_EIG_AUTO && n >= (fp64 ? kEigTeamMax + 1 : kEigTwoStageMin));
 }
 // Dense symmetric eigensolve: the team solver for the orders it holds on the
 // chip, rocSOLVER above, and rocSOLVER for the iterations of the reduced
@@ -619,7 +622,7 @@ inline int eig_dense(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
 }
 inline int eig_casida(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
                       bool fp64) {
-  if (eig_two_stage_for(c, n)) return eig_two_stage(c, n, A, evals, what);
+  if (eig_two_stage_for(c, n, fp64)) return eig_two_stage(c, n, A, evals, what);
   return eig_dense(c, n, A, evals, what, fp64 && c->eig_solver == QSGW_EIG_AUTO);
 }
 

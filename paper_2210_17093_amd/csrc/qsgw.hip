@@ -759,8 +759,9 @@ int qsgw_rpa_solve(qsgw_ctx* c, int64_t ntr, double* M_to_Z, double* Omega) {
   if (ntr < 1 || !M_to_Z || !Omega) return fail(c, QSGW_ERR_INVALID_ARG, "bad arguments");
   CHECK(check_finite(c, "qsgw_rpa_solve", {fin(M_to_Z, ntr * ntr, "M")}));
   CHECK(single_begin(c, kStageEigRpa));
-  if (!eig_two_stage_for(c, ntr)) {
-    // a caller's matrix counts by its lower triangle (row-major), whichever solver takes it
+  if (!eig_two_stage_for(c, ntr, false)) {
+    // below kEigTwoStageMin a caller's matrix counts by its lower triangle (row-major),
+    // whichever solver takes it
     hipLaunchKernelGGL(k_mirror_lower, dim3(blocks_for(ntr, 32), blocks_for(ntr, 32)), dim3(256), 0,
                        c->stream, M_to_Z, ntr);
     CHECK(launch_check(c, "k_mirror_lower"));
@@ -951,7 +952,7 @@ int iterate_impl(qsgw_ctx* c, const qsgw_problem* p, qsgw_state* st, const qsgw_
   unsigned long long* fprint = nullptr;
   // the two-stage solver hands the residues rho' of every excitation
   // directly (projection), the rocSOLVER path the eigenvectors Z
-  const bool fold = !qsmp2 && eig_two_stage_for(c, ntr);
+  const bool fold = !qsmp2 && eig_two_stage_for(c, ntr, !fp32);
   if (!qsmp2) {  // (the qsMP2 potential replaces Casida, residues and the qsGW product)
     if (replay && (c->eig_ntr != ntr || c->eig_fold != fold))
       return fail(c, QSGW_ERR_INVALID_ARG,
@@ -1391,7 +1392,7 @@ int qsgw_gw_unrestricted(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc_a,
   CHECK(ws_get(c, W_WH, (size_t)(nn * sb), &wh));
   // with the two-stage solver the eigensolve hands rho' of every excitation
   // (projection of the spin-stacked Bt, the eigenvectors never formed)
-  const bool fold = eig_two_stage_for(c, ntr);
+  const bool fold = eig_two_stage_for(c, ntr, true);
   double *PX = nullptr, *rhoF = nullptr;
   if (fold) {
     CHECK(ws_get(c, W_EIG_PX, (size_t)(naux * ntr), &PX));

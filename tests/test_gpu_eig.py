@@ -359,3 +359,25 @@ def test_two_stage_large_tridiagonals(q, ctx, n):
     eye = torch.eye(n, dtype=torch.float64, device="cuda")[some]
     assert float((Zs @ Z.T - eye).abs().max()) <= 1e-11
     assert float((Zs @ A - ev[some, None] * Zs).abs().max()) <= 1e-11 * 62
+
+
+@pytest.mark.parametrize("n", [3073, 5001])
+def test_automatic_solver_above_one_stage_orders(q, n):
+    """The default choice just above the one-stage solver's orders and between:
+    the two-stage solver, and still the lower triangle alone counts."""
+    print("automatic eigensolver, order", n, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randn(n, n, generator=g, dtype=torch.float64, device="cuda") / n ** 0.5
+    A = 0.5 * (A + A.T)
+    A.diagonal().add_(torch.linspace(10.0, 60.0, n, dtype=torch.float64, device="cuda"))
+    given = torch.tril(A) + torch.triu(torch.ones_like(A), 1)
+    with q.Context() as c:
+        Z, Om = q.qsgw_rpa_solve(c, given)
+        torch.cuda.synchronize()
+    ev = Om * Om
+    assert bool((ev[1:] >= ev[:-1]).all())
+    some = torch.linspace(0, n - 1, 24, device="cuda").long()
+    Zs = Z[some]
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")[some]
+    assert float((Zs @ Z.T - eye).abs().max()) <= 1e-11
+    assert float((Zs @ A - ev[some, None] * Zs).abs().max()) <= 1e-11 * 62
