@@ -24,6 +24,7 @@
 // order reversed).  A root's vector is zh / (d - lambda) there, a deflated one keeps
 // its half's sign.
 #include "internal.hpp"
+#include "poles.hpp"
 #include "wave.hpp"
 #include "wy.hpp"
 
@@ -432,25 +433,34 @@ __global__ void k_tri_clear(const EigDev* __restrict__ P) {
 
 // ------------------------------------------------------ divide and conquer --
 // T divided by the power of two of its largest entry (one workgroup a problem).
-__global__ __launch_bounds__(256) void k_dc_scale(const EigDev* __restrict__ P) {
+// The merges' index maps take their places from comparisons of poles and are
+// whole only for finite ones: a T with an entry that is not finite (a product
+// that overflowed, a wait of the reduction that was given up) is replaced by
+// zeros and flagged.
+__global__ __launch_bounds__(256) void k_dc_scale(const EigDev* __restrict__ P,
+                                                  int* __restrict__ err) {
   __shared__ double red[4];
   const EigDev& p = P[blockIdx.x];
   double m = 0.0;
   for (int i = threadIdx.x; i < p.n; i += 256) {
-    m = fmax(m, fabs(p.d[i]));
-    if (i + 1 < p.n) m = fmax(m, fabs(p.e[i]));
+    m = fmax(m, finite_magnitude(p.d[i]));
+    if (i + 1 < p.n) m = fmax(m, finite_magnitude(p.e[i]));
   }
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
   m = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  const bool ok = isfinite(m);
   int ex = 0;
-  if (m > 0.0 && isfinite(m)) (void)frexp(m, &ex);
+  if (m > 0.0 && ok) (void)frexp(m, &ex);
   for (int i = threadIdx.x; i < p.n; i += 256) {
-    p.d[i] = ldexp(p.d[i], -ex);
-    if (i + 1 < p.n) p.e[i] = ldexp(p.e[i], -ex);
+    p.d[i] = ok ? ldexp(p.d[i], -ex) : 0.0;
+    if (i + 1 < p.n) p.e[i] = ok ? ldexp(p.e[i], -ex) : 0.0;
   }
-  if (threadIdx.x == 0) *p.scale = ldexp(1.0, ex);
+  if (threadIdx.x == 0) {
+    *p.scale = ldexp(1.0, ex);
+    if (!ok) atomicOr(err + blockIdx.x, 4);
+  }
 }
 
 // Root of the secular equation j of K (poles d ascending, weights z), by W
@@ -548,17 +558,6 @@ __device__ __forceinline__ double zhat_factor(const double* d, int K, double rho
   return lj * fast_rcp(den);
 }
 
-// Number of entries of the ascending v[0..len) below x, or not above it.
-__device__ __forceinline__ int dc_count(const double* v, int len, double x, bool or_equal) {
-  int lo = 0, hi = len;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    const bool below = or_equal ? v[mid] <= x : v[mid] < x;
-    if (below) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
 // Serial deflation of n sorted poles ds with unit weights zs (one thread): the
 // non-deflated positions nd[0..K) with values dk, zk, the deflated positions
 // df with values dfv, the rotations (ra, rb, rc, rs) in order.  Returns K.
@@ -620,10 +619,12 @@ struct BaseSmem {
 // Implicit QL with eigenvectors of a tridiagonal leaf of m <= 8 rows (lane i:
 // d_i, and e_i between i and i + 1) by one wave, lane r row r of the
 // eigenvectors in registers; eigenvalues ascending into D[b..b+m), vectors into
-// the leaf's block of E.  Returns false if an eigenvalue does not converge.
+// the leaf's block of E.  If an eigenvalue does not converge it returns false
+// and leaves the diagonal with unit vectors, which the merges can work on.
 typedef double d8 __attribute__((ext_vector_type(8)));
 __device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
   const int lane = threadIdx.x & 63;
+  const double d0 = d;
   bool ok = true;
   d8 Z;
 #pragma unroll
@@ -679,6 +680,11 @@ __device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
       if (lane == q) e = 0.0;
     }
   }
+  if (!ok) {
+    d = d0;
+#pragma unroll
+    for (int c = 0; c < kLeaf; ++c) Z[c] = lane == c ? 1.0 : 0.0;
+  }
   int rank = 0;
   for (int k = 0; k < m; ++k) {
     const double dk = read_lane(d, k);
@@ -702,15 +708,8 @@ __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2
   const bool neg = beta < 0.0;
   if (tr < m) {
     const double val = sm.D[o + tr];
-    int pos;
-    double z;
-    if (tr < m1) {
-      pos = tr + dc_count(sm.D + o + m1, m2, val, false);
-      z = sm.E[o + tr][o + m1 - 1];
-    } else {
-      pos = tr - m1 + dc_count(sm.D + o, m1, val, true);
-      z = sm.E[o + tr][o + m1];
-    }
+    int pos = merged_place(sm.D + o, m1, m, tr);
+    const double z = sm.E[o + tr][tr < m1 ? o + m1 - 1 : o + m1];
     if (neg) pos = m - 1 - pos;
     sm.ds[o + pos] = neg ? -val : val;
     sm.zs[o + pos] = z;
@@ -1001,15 +1000,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_dc_prep(const EigDev* __restri
   for (int t = tid; t < n; t += kPrepThreads) {
     const double val = d[t];
     const double* Ec = p.E + (int64_t)(off + t) * N + off;
-    int pos;
-    double z;
-    if (t < n1) {
-      pos = t + dc_count(d + n1, n - n1, val, false);
-      z = Ec[n1 - 1];
-    } else {
-      pos = t - n1 + dc_count(d, n1, val, true);
-      z = Ec[n1];
-    }
+    int pos = merged_place(d, n1, n, t);
+    const double z = Ec[t < n1 ? n1 - 1 : n1];
     if (neg) pos = n - 1 - pos;
     sm.ds[pos] = neg ? -val : val;
     sm.zs[pos] = z;
@@ -1635,7 +1627,7 @@ static int run_products(qsgw_ctx* c, const EigPlan* pl, const EigPlan::Products&
 
 // Eigenpairs of every problem's d, e: E, and ev ascending.
 static int run_merges(qsgw_ctx* c, const EigPlan* pl, const EigDev* P) {
-  hipLaunchKernelGGL(k_dc_scale, dim3(pl->count), dim3(256), 0, c->stream, P);
+  hipLaunchKernelGGL(k_dc_scale, dim3(pl->count), dim3(256), 0, c->stream, P, pl->err);
   hipLaunchKernelGGL(k_dc_base, dim3(pl->nbase), dim3(kBaseThreads), 0, c->stream, P,
                      reinterpret_cast<const BaseNode*>(pl->dev + pl->base), pl->err);
   CHECK(launch_check(c, "k_dc_base"));
@@ -1704,6 +1696,7 @@ int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what, int64_t* at) {
     if (!e[i]) continue;
     if (at) *at = (int64_t)i;
     if (e[i] & 1) return fail(c, QSGW_ERR_SOLVER, "%s: reduction wait exceeded its bound", what);
+    if (e[i] & 4) return fail(c, QSGW_ERR_SOLVER, "%s: a value is not finite", what);
     return fail(c, QSGW_ERR_SOLVER, "%s: a tridiagonal block did not converge", what);
   }
   return QSGW_OK;

@@ -1,0 +1,63 @@
+"""Values that leave the range of FP64 inside a call: the eigensolvers return an
+error code or, where the eigenvalues themselves can be represented, the right
+eigenpairs, and the context goes on working."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2210_17093_amd.qsgw as q
+    return q
+
+
+@pytest.fixture()
+def ctx(q):
+    c = q.Context()
+    yield c
+    c.close()
+
+
+def spd(n, seed):
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((n, max(2, n // 4))) * 0.3
+    return np.diag(rng.uniform(0.1, 2500.0, n)) + X @ X.T
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def check_solve(q, ctx, M, scale=1.0):
+    """Eigenpairs of scale * M (scale a power of two) against LAPACK's of M, with
+    the bounds of the other eigensolver tests."""
+    n = M.shape[0]
+    ref = np.linalg.eigvalsh(M)
+    Z, Om = q.qsgw_rpa_solve(ctx, dev(M * scale))
+    torch.cuda.synchronize()
+    norm = np.abs(ref).max()
+    bound = 1e-13 * max(4.0, np.sqrt(n))
+    lam = (Om.cpu().numpy() / np.sqrt(scale)) ** 2
+    assert np.max(np.abs(lam - ref)) <= bound * norm
+    assert float((Z @ Z.T - torch.eye(n, dtype=torch.float64, device="cuda")).abs().max()) <= bound
+    assert float((Z @ dev(M) - dev(lam)[:, None] * Z).abs().max()) <= bound * norm
+
+
+@pytest.mark.parametrize("nbf", [40, 80, 300])
+def test_overflow_before_the_eigensolve_is_an_error(q, ctx, nbf):
+    """C^T h C overflows, so the Fock matrix is not finite."""
+    print("fock overflow", nbf, flush=True)
+    eye = np.eye(nbf)
+    h = spd(nbf, nbf) * 1e200
+    args = [dev(np.zeros((3, nbf, nbf))), dev(np.zeros((3, nbf, nbf))), dev(h), dev(0.0 * eye),
+            dev(0.0 * eye), 4, 3, dev(np.zeros(nbf)), dev(np.zeros(nbf)), dev(eye * 1e60),
+            dev(eye * 1e60)]
+    with pytest.raises(q.QsgwError) as ei:
+        q.qsgw_fock_unrestricted(ctx, *args)
+    assert ei.value.code == q.ERR_SOLVER and "not finite" in str(ei.value)
+    check_solve(q, ctx, spd(nbf, 1))
