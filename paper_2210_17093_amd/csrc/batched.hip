@@ -140,11 +140,15 @@ __global__ void kb_pad(const Mol* mols, const int64_t* pre, int64_t nmol, int64_
   A[li] = (t == u) ? m.pad[which] : 0.0;
 }
 
+// Omega.  The flags are read at the end of the iteration, so the molecule of an
+// eigenvalue without a root goes on to its Fock eigensolve: with Omega = 1 there,
+// as its residues, scaled by sqrt(2 / Omega), have to stay finite.
 __global__ void kb_omega(const Mol* mols, const int64_t* pre, int64_t nmol, int64_t total) {
   SEG_PROLOGUE(total)
   const double l = m.Mev[li];
-  if (!(l > 0.0) || !isfinite(l)) atomicOr(m.flag, 2);
-  m.Mev[li] = sqrt(l > 0.0 ? l : 0.0);
+  const bool ok = l > 0.0 && isfinite(l);
+  if (!ok) atomicOr(m.flag, 2);
+  m.Mev[li] = ok ? sqrt(l) : 1.0;
 }
 
 __global__ void kb_rho_reduce(const Mol* mols, const int64_t* pre, int64_t nmol, int64_t total) {

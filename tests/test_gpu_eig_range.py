@@ -61,3 +61,36 @@ def test_overflow_before_the_eigensolve_is_an_error(q, ctx, nbf):
         q.qsgw_fock_unrestricted(ctx, *args)
     assert ei.value.code == q.ERR_SOLVER and "not finite" in str(ei.value)
     check_solve(q, ctx, spd(nbf, 1))
+
+
+def test_batch_with_a_zero_gap_names_the_molecule(q):
+    """A molecule of 80 functions whose HOMO and LUMO are equal: its Casida matrix
+    has a zero eigenvalue.  The call says which molecule it is, and the others of
+    the batch take their iteration as they do alone."""
+    from qsgw_inputs import make_problem
+    stream = torch.cuda.Stream()
+    c = q.Context(stream)
+    try:
+        mols, alone = [], []
+        with torch.cuda.stream(stream):
+            for nbf, seed in ((33, 1), (80, 2), (20, 3), (95, 4)):
+                p = make_problem(nbf, 4 * nbf, nbf // 6, 2 * nbf, 0.99, 900 + seed)
+                B, C, e = dev(p.B_ao), dev(p.C0), p.eps0.copy()
+                h = q.qsgw_hf_core(c, B, C, dev(e), p.nocc)
+                if nbf == 80:
+                    e[p.nocc] = e[p.nocc - 1]
+                else:
+                    e1, C1 = dev(e), C.clone()
+                    q.qsgw_iterate(c, B, h, p.nocc, e1, C1, 1e-3, tol=0.0, max_iter=1)
+                    alone.append(e1)
+                mols.append(dict(B_ao=B, h=h, nocc=p.nocc, eps=dev(e), C=C.clone()))
+            print("batch with a zero gap", flush=True)
+            with pytest.raises(q.QsgwError) as ei:
+                q.qsgw_iterate_batched(c, mols, 1e-3, tol=0.0, max_iter=1)
+        assert ei.value.code == q.ERR_INVALID_ARG and "molecule 1:" in str(ei.value)
+        good = [m["eps"] for m in mols if m["eps"].shape[0] != 80]
+        for a, b in zip(alone, good):
+            assert float((a - b).abs().max()) <= 1e-8
+        stream.synchronize()
+    finally:
+        c.close()
