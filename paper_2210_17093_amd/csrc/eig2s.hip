@@ -30,6 +30,7 @@
 // All arrays are column-major; a symmetric row-major matrix is its own
 // column-major view.  Everything runs in FP64.
 #include "internal.hpp"
+#include "poles.hpp"
 #include "wave.hpp"
 #include "wy.hpp"
 
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(256) void k_panel_col(double* __restrict__ P, int64
     if (tid == 0) {
       const double alpha = P[(int64_t)j * lda + j];
       const double sig = wv[j];
-      if (sig == 0.0) {
+      if (sig <= kTinySquare) {
         sc[0] = 0.0;
         sc[1] = alpha;
         sc[2] = 0.0;
@@ -308,7 +309,7 @@ __device__ __forceinline__ void panel_columns(d16 (&P)[4], double* A, int64_t ld
     auto dot = [&](int c) { return (sm.sum[0][c] + sm.sum[1][c]) + (sm.sum[2][c] + sm.sum[3][c]); };
     const double alpha = sm.row[j], sig = dot(j);
     double t = 0.0, beta = alpha, scale = 0.0;
-    if (sig != 0.0) {
+    if (!(sig <= kTinySquare)) {
       const double n2 = fma(alpha, alpha, sig), r = fast_rsqrt(n2);
       beta = -copysign(n2 * r, alpha);
       t = fma(fabs(alpha), r, 1.0);
@@ -385,6 +386,37 @@ __global__ __launch_bounds__(256) void k_panel_coop(double* A, int64_t lda, int6
 __global__ void k_empty(unsigned long long* __restrict__ p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = kEmpty;
+}
+
+// *out (0 or more before) becomes at least the largest magnitude of x[0..len),
+// infinity where one is not finite.  Bound by reading x once.
+__global__ __launch_bounds__(256) void k_abs_max(const double* __restrict__ x, int64_t len,
+                                                 double* out) {
+  __shared__ double red[4];
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  double m = 0.0;
+#pragma unroll 8
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < len; i += step)
+    m = fmax(m, finite_magnitude(x[i]));
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)  // (bit patterns of numbers from 0 to infinity are in their order)
+    atomicMax(reinterpret_cast<unsigned long long*>(out),
+              __builtin_bit_cast(unsigned long long, fmax(fmax(red[0], red[1]), fmax(red[2], red[3]))));
+}
+
+__global__ void k_ldexp(double* __restrict__ x, int64_t len, int ex) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < len) x[i] = ldexp(x[i], ex);
+}
+
+// Entries of a panel (m rows, b columns) whose squares lose their bits become zero.
+__global__ void k_zero_tiny(double* __restrict__ P, int64_t lda, int64_t m, int b) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= m * b) return;
+  double* x = P + idx / m * lda + idx % m;
+  if (fabs(*x) < kTinyEntry) *x = 0.0;
 }
 
 // R (rows q < b of the panel, columns c >= q) from Rbuf into the panel's upper triangle.
@@ -544,7 +576,7 @@ __device__ void householder(const double* x, int L, double* v, double* sc) {
     const double s = wave_sum(xv * xv);
     if (tid == 0) {
       const double alpha = x[0];
-      if (s == 0.0) {
+      if (s <= kTinySquare) {
         sc[0] = 0.0;     // tau: H = I
         sc[1] = alpha;   // beta
         sc[2] = 0.0;     // scale of x[1:]
@@ -896,7 +928,7 @@ __global__ __launch_bounds__(256, 2) void k_bulge_chase(const double* __restrict
     const double alpha = read_lane(x, s);
     const double sig = wave_total(lane != s ? x * x : 0.0);
     double tau = 0.0, beta = alpha, scale = 0.0;
-    if (sig != 0.0) {
+    if (!(sig <= kTinySquare)) {
       const double n2 = fma(alpha, alpha, sig), r = fast_rsqrt(n2);
       beta = -copysign(n2 * r, alpha);
       tau = fma(fabs(alpha), r, 1.0);
@@ -1391,6 +1423,9 @@ static int ts_reduce(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
       hipLaunchKernelGGL(k_panel_r, dim3(blocks_for(b * b)), dim3(256), 0, c->stream, P, n, b, Rbuf);
       CHECK(launch_check(c, "k_panel_col"));
     } else {
+      // (its reflectors square entries as they are)
+      hipLaunchKernelGGL(k_zero_tiny, dim3(blocks_for(m * b)), dim3(256), 0, c->stream, P, n, m, b);
+      CHECK(launch_check(c, "k_zero_tiny"));
       RB_TRY(c, rocsolver_dgeqrf(h, mi, b, P, ni, tau1 + p * b), what);
     }
     if (kk < b) {
@@ -1659,6 +1694,29 @@ static int ts_apply(qsgw_ctx* c, const TwoStage& ts, int64_t n, double* X, int64
   return QSGW_OK;
 }
 
+// Multiplies A by the power of two that range_exponent asks for; *ex its exponent.
+int ts_range(qsgw_ctx* c, int64_t n, double* A, int* ex, const char* what) {
+  int* flags = nullptr;
+  CHECK(ws_get(c, W_FLAGS, 8, &flags));
+  double* mx = reinterpret_cast<double*>(flags + 4);
+  HIP_TRY(c, hipMemsetAsync(mx, 0, sizeof(double), c->stream));
+  hipLaunchKernelGGL(k_abs_max, dim3(1024), dim3(256), 0, c->stream, A, n * n, mx);
+  CHECK(launch_check(c, "k_abs_max"));
+  double m = 0.0;
+  HIP_TRY(c, hipMemcpyAsync(&m, mx, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (m >= HUGE_VAL) return fail(c, QSGW_ERR_SOLVER, "%s: a value is not finite", what);
+  *ex = range_exponent(m);
+  if (*ex == 0) return QSGW_OK;
+  hipLaunchKernelGGL(k_ldexp, dim3(blocks_for(n * n)), dim3(256), 0, c->stream, A, n * n, *ex);
+  return launch_check(c, "k_ldexp");
+}
+int ts_unrange(qsgw_ctx* c, int64_t n, double* evals, int ex) {
+  if (ex == 0) return QSGW_OK;
+  hipLaunchKernelGGL(k_ldexp, dim3(blocks_for(n)), dim3(256), 0, c->stream, evals, n, -ex);
+  return launch_check(c, "k_ldexp");
+}
+
 }  // namespace
 
 // Two-stage eigensolve: A [n][n] symmetric (column-major view) in, its
@@ -1667,7 +1725,10 @@ int eig_two_stage(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* 
   if (n > 46340) return fail(c, QSGW_ERR_UNSUPPORTED, "%s: n too large for the two-stage solver", what);
   if (n < 4 * kBand) return syevd(c, n, A, evals, what);
   TwoStage ts;
+  int ex = 0;
+  CHECK(ts_range(c, n, A, &ex, what));
   CHECK(ts_reduce(c, n, A, evals, what, &ts));
+  CHECK(ts_unrange(c, n, evals, ex));
   return ts_apply(c, ts, n, A, n, false, what);
 }
 
@@ -1691,11 +1752,14 @@ int eig_two_stage_project(qsgw_ctx* c, int64_t n, double* A, double* evals, int6
     return QSGW_OK;
   }
   TwoStage ts;
+  int ex = 0;
+  CHECK(ts_range(c, n, A, &ex, what));
   CHECK(ts_reduce(c, n, A, evals, what, &ts, false));
   HIP_TRY(c, hipMemcpyAsync(X, Bt, (size_t)(naux * n) * sizeof(double), hipMemcpyDeviceToDevice,
                             c->stream));
   CHECK(ts_apply(c, ts, n, X, naux, true, what));
   double* dd = nullptr;
   CHECK(ws_get(c, W_EIG_DE, (size_t)(2 * n), &dd));
-  return tridiag_project_dc(c, n, dd, dd + n, A, naux, X, evals, R, what);
+  CHECK(tridiag_project_dc(c, n, dd, dd + n, A, naux, X, evals, R, what));
+  return ts_unrange(c, n, evals, ex);
 }

@@ -47,10 +47,13 @@ struct EigDev {
   double* vec;         // merge vectors, kVec x n
   int* idx;            // merge index maps, kIdx x n
   double *G, *T;       // Gram matrices and T factors [blocks][128][128]
-  double* scale;       // power of two that T was divided by
+  double* scale;       // kScale words, see below
   int64_t ld;
   int n, team, cfg, pad;
 };
+// scale[S_T]: power of two that T was divided by, [S_RANGE]: exponent of the one that the
+// matrix was multiplied by (range_exponent), [S_MAX]: its largest magnitude.
+enum { S_T = 0, S_RANGE, S_MAX, kScale = 8 };
 enum { V_DK = 0, V_ZK, V_LAM, V_MU, V_DOR, V_ZH, V_DFS, V_RC, V_RS, kVec };
 enum { I_COL = 0, I_P1, I_P2, I_DFC, I_DFF, I_POS, I_RA, I_RB, I_FLAG, kIdx };
 
@@ -209,6 +212,31 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
     v[u] = vp[u] = wp[u] = 0.0;
     if (c < n && rg == 0) sm.v[1][c] = sm.w[1][c] = 0.0;
   }
+  // ---- entries far from 1 ----
+  double mx = 0.0;
+  if (G > 1) {
+    mx = P.scale[S_MAX];  // (k_tri_clear)
+  } else {
+#pragma unroll
+    for (int u = 0; u < CU; ++u)
+#pragma unroll
+      for (int l = 0; l < RL; ++l) mx = fmax(mx, finite_magnitude(a[l][u]));
+    mx = wave_max(mx);
+    if (lane == 0) sm.part[wave][0] = mx;
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < kTeamThreads / 64; ++q) mx = fmax(mx, sm.part[q][0]);
+  }
+  const int ex = __builtin_amdgcn_readfirstlane(range_exponent(mx));
+  if (ex != 0) {
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      col[u] = ldexp(col[u], ex);
+#pragma unroll
+      for (int l = 0; l < RL; ++l) a[l][u] = ldexp(a[l][u], ex);
+    }
+  }
+  if (g == 0 && tid == 0) P.scale[S_RANGE] = ex;
   if (g == 0 && tid == 0) P.d[n - 1] = col[0];
   bool dead = false;
   for (int j = 0; j + 1 < n; ++j) {
@@ -231,7 +259,7 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
     // beta = -sign(alpha) r, tau = (beta - alpha) / beta = 1 + |alpha| / r,
     // 1 / (alpha - beta) = sign(alpha) / (|alpha| + r)
     double tau = 0.0, beta = alpha, scale = 0.0;
-    if (sig != 0.0) {
+    if (!(sig <= kTinySquare)) {
       const double x = alpha * alpha + sig;
       const double ir = fast_rsqrt(x), nr = x * ir;
       const double r = fma(fma(-nr, nr, x), 0.5 * ir, nr);
@@ -416,19 +444,34 @@ __global__ __launch_bounds__(kTeamThreads, 2) void k_tri_team(const EigDev* __re
   }
 }
 
-__global__ void k_eig_clear_err(int* err, int64_t n) {
+__global__ void k_eig_init(const EigDev* __restrict__ P, int* err, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) err[i] = 0;
+  if (i >= n) return;
+  err[i] = 0;
+  P[i].scale[S_RANGE] = P[i].scale[S_MAX] = 0.0;
 }
 
-// kEmpty into the exchange slots of every problem (blockIdx.y) solved by more than one workgroup.
-__global__ void k_tri_clear(const EigDev* __restrict__ P) {
+// kEmpty into the exchange slots of every problem (blockIdx.y) solved by more
+// than one workgroup, and its matrix's largest magnitude (bit patterns of
+// numbers from 0 to infinity are in their order).
+__global__ __launch_bounds__(256) void k_tri_clear(const EigDev* __restrict__ P) {
+  __shared__ double red[4];
   const EigDev& p = P[blockIdx.y];
   if (p.team <= 1) return;
   const int64_t nn = (int64_t)p.n * p.n, step = (int64_t)gridDim.x * blockDim.x;
   ulonglong2* x = reinterpret_cast<ulonglong2*>(p.E);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += step)
     x[i] = ulonglong2{kEmpty, kEmpty};
+  double m = 0.0;
+  for (int64_t r = blockIdx.x; r < p.n; r += gridDim.x)
+    for (int c = threadIdx.x; c < p.n; c += 256) m = fmax(m, finite_magnitude(p.A[r * p.ld + c]));
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  if (threadIdx.x == 0 && m > __builtin_bit_cast(double, peek(p.scale + S_MAX)))
+    atomicMax(reinterpret_cast<unsigned long long*>(p.scale + S_MAX),
+              __builtin_bit_cast(unsigned long long, m));
 }
 
 // ------------------------------------------------------ divide and conquer --
@@ -458,7 +501,7 @@ __global__ __launch_bounds__(256) void k_dc_scale(const EigDev* __restrict__ P,
     if (i + 1 < p.n) p.e[i] = ok ? ldexp(p.e[i], -ex) : 0.0;
   }
   if (threadIdx.x == 0) {
-    *p.scale = ldexp(1.0, ex);
+    p.scale[S_T] = ldexp(1.0, ex);
     if (!ok) atomicOr(err + blockIdx.x, 4);
   }
 }
@@ -634,7 +677,7 @@ __device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
       // first negligible e at or after l (the last row counts as one)
       const double dn = __shfl_down(d, 1);
       const unsigned long long small =
-          __ballot(lane + 1 >= m || fabs(e) <= __DBL_EPSILON__ * (fabs(d) + fabs(dn)));
+          __ballot(lane + 1 >= m || fabs(e) <= fmax(__DBL_EPSILON__ * (fabs(d) + fabs(dn)), kTinyEntry));
       const int q = l + __builtin_ctzll(small >> l);
       if (q == l) break;
       if (it >= 60) {
@@ -651,7 +694,7 @@ __device__ bool ql_leaf(BaseSmem& sm, int b, int m, double d, double e) {
         const double ei = read_lane(e, i);
         const double f = s * ei, bb = c * ei;
         const double r2 = fma(f, f, gg * gg);
-        if (r2 == 0.0) {
+        if (r2 <= kTinySquare) {
           if (lane == i + 1) {
             e = 0.0;
             d -= p;
@@ -720,7 +763,7 @@ __device__ void base_merge(BaseSmem& sm, int team, int tr, int o, int m1, int m2
     const double z = tr < m ? sm.zs[o + tr] : 0.0;
     const double s2 = wave_total(z * z), dm = wave_max(tr < m ? fabs(sm.ds[o + tr]) : 0.0);
     const double rho = fabs(beta) * s2, zi = z * fast_rsqrt(s2), di = tr < m ? sm.ds[o + tr] : 0.0;
-    const double tol = 8.0 * __DBL_EPSILON__ * fmax(dm, rho);
+    const double tol = fmax(8.0 * __DBL_EPSILON__ * fmax(dm, rho), kTinyEntry);
     // the poles that stay, and whether two neighbours among them are close
     const bool stays = tr < m && rho * fabs(zi) > tol;
     const unsigned long long mask = __ballot(stays);
@@ -1024,7 +1067,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_dc_prep(const EigDev* __restri
   }
   const double zi = 1.0 / sqrt(s2);
   const double rho = fabs(beta) * s2;
-  const double tol = 8.0 * __DBL_EPSILON__ * fmax(dm, rho);
+  const double tol = fmax(8.0 * __DBL_EPSILON__ * fmax(dm, rho), kTinyEntry);
   // survivors of the weight test, in order
   const int per = (n + kPrepThreads - 1) / kPrepThreads;
   const int t0 = tid * per, t1 = min(t0 + per, n);
@@ -1258,8 +1301,11 @@ __global__ __launch_bounds__(256) void k_dc_vecs(const EigDev* __restrict__ P,
 
 __global__ void k_dc_finish(const EigDev* __restrict__ P) {
   const EigDev& p = P[blockIdx.x];
-  const double s = *p.scale;
-  for (int i = threadIdx.x; i < p.n; i += blockDim.x) p.ev[i] = p.d[i] * s;
+  const double s = p.scale[S_T];
+  const int ex = (int)p.scale[S_RANGE];
+  for (int i = threadIdx.x; i < p.n; i += blockDim.x)
+    p.ev[i] = ex == 0 ? p.d[i] * s : ldexp(p.d[i] * s, -ex);
+  if (threadIdx.x == 0) p.scale[S_MAX] = 0.0;  // (for the plan's next run)
 }
 
 // ---------------------------------------------------- back-transformation --
@@ -1476,6 +1522,16 @@ static void plan_merges(EigPlan* pl, const std::vector<EigDev>& P) {
   }
 }
 
+// The plan's tables to the device, its error flags and range words cleared.
+static int upload_plan(qsgw_ctx* c, const EigPlan* pl) {
+  HIP_TRY(c, hipMemcpyAsync(pl->dev, pl->img.data(), pl->img.size(), hipMemcpyHostToDevice,
+                            c->stream));
+  hipLaunchKernelGGL(k_eig_init, dim3(blocks_for(pl->count)), dim3(256), 0, c->stream,
+                     reinterpret_cast<const EigDev*>(pl->dev + pl->probs), pl->err,
+                     (int64_t)pl->count);
+  return launch_check(c, "k_eig_init");
+}
+
 int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, int set) {
   pl->count = (unsigned)count;
   std::vector<EigDev> P((size_t)count);
@@ -1491,7 +1547,7 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
   size_t nd = 8, ni = (size_t)count;
   for (int64_t i = 0; i < count; ++i) {
     const int64_t n = prob[i].n, nb = (n - 1 + kBk - 1) / kBk;
-    nd += (size_t)(3 * n * n + (3 + kVec) * n + 2 + 2 * nb * kBk * kBk + 8);
+    nd += (size_t)(3 * n * n + (3 + kVec) * n + 2 + 2 * nb * kBk * kBk + kScale);
     ni += (size_t)(kIdx * n);
   }
   double* D = nullptr;
@@ -1500,9 +1556,6 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
   CHECK(ws_get(c, W_EIGD_I + 3 * set, ni, &I));
   pl->err = I;
   I += count;
-  hipLaunchKernelGGL(k_eig_clear_err, dim3(blocks_for(count)), dim3(256), 0, c->stream, pl->err,
-                     count);
-  CHECK(launch_check(c, "k_eig_clear_err"));
   for (int64_t i = 0; i < count; ++i) {
     const int64_t n = prob[i].n, nb = (n - 1 + kBk - 1) / kBk;
     EigDev& p = P[(size_t)i];
@@ -1525,7 +1578,7 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
     p.T = D + nb * kBk * kBk;
     D += 2 * nb * kBk * kBk;
     p.scale = D;
-    D += 8;
+    D += kScale;
     p.idx = I;
     I += kIdx * n;
     pl->clear = pl->clear || p.team > 1;
@@ -1602,9 +1655,7 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
     pl->steps.push_back(st);
   }
   CHECK(ws_get(c, W_EIGD_T + 3 * set, pl->img.size() + 256, &pl->dev));
-  HIP_TRY(c, hipMemcpyAsync(pl->dev, pl->img.data(), pl->img.size(), hipMemcpyHostToDevice,
-                            c->stream));
-  return QSGW_OK;
+  return upload_plan(c, pl);
 }
 
 template <class J>
@@ -1719,11 +1770,9 @@ int eig_tridiag(qsgw_ctx* c, int64_t n, double* d, double* e, double* E, const c
   pl.count = 1;
   double* D = nullptr;
   int* I = nullptr;
-  CHECK(ws_get(c, W_EIGD_F, (size_t)(2 * n * n + kVec * n + 8), &D));
+  CHECK(ws_get(c, W_EIGD_F, (size_t)(2 * n * n + kVec * n + kScale), &D));
   CHECK(ws_get(c, W_EIGD_I, (size_t)(1 + kIdx * n), &I));
   pl.err = I;
-  hipLaunchKernelGGL(k_eig_clear_err, dim3(1), dim3(256), 0, c->stream, pl.err, (int64_t)1);
-  CHECK(launch_check(c, "k_eig_clear_err"));
   EigDev p{};
   p.n = (int)n;
   p.ev = p.d = d;
@@ -1738,8 +1787,7 @@ int eig_tridiag(qsgw_ctx* c, int64_t n, double* d, double* e, double* E, const c
   pl.probs = put(pl.img, P);
   plan_merges(&pl, P);
   CHECK(ws_get(c, W_EIGD_T, pl.img.size() + 256, &pl.dev));
-  HIP_TRY(c, hipMemcpyAsync(pl.dev, pl.img.data(), pl.img.size(), hipMemcpyHostToDevice,
-                            c->stream));
+  CHECK(upload_plan(c, &pl));
   CHECK(run_merges(c, &pl, reinterpret_cast<const EigDev*>(pl.dev + pl.probs)));
   int64_t at = 0;
   return eig_check(c, &pl, what, &at);

@@ -94,3 +94,49 @@ def test_batch_with_a_zero_gap_names_the_molecule(q):
         stream.synchronize()
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 24, 95, 300, 1100, 3200])
+@pytest.mark.parametrize("power", [-1000, -600, 600, 1000])
+def test_entries_whose_squares_leave_the_range(q, ctx, n, power):
+    """A matrix of entries near 2^power (orders on both sides of the solvers' limit)."""
+    print("eigensolve of 2^%d, order %d" % (power, n), flush=True)
+    check_solve(q, ctx, spd(n, n), 2.0 ** power)
+
+
+@pytest.mark.parametrize("n", [24, 95, 300, 3200])
+@pytest.mark.parametrize("t", [1e-150, 1e-156, 1e-159, 1e-162, 1e-200])
+def test_couplings_whose_squares_underflow(q, ctx, n, t):
+    """Columns whose sums of squares are zero or have lost their bits."""
+    print("eigensolve with couplings of %g, order %d" % (t, n), flush=True)
+    M = spd(n, n)
+    M[n // 3:, :n // 3] *= t
+    M[:n // 3, n // 3:] *= t
+    M[n // 3:, n // 3:] = np.diag(np.diag(M)[n // 3:]) + t * (M[n // 3:, n // 3:])
+    check_solve(q, ctx, M)
+
+
+@pytest.mark.parametrize("nbf", [24, 120, 300])
+def test_blocks_of_very_different_scale(q, ctx, nbf):
+    """A symmetric matrix (the core Hamiltonian of a call without interaction) of
+    four blocks down to the smallest normal numbers: its eigenvectors are
+    orthonormal and its residuals small beside its largest eigenvalue."""
+    print("blocks of different scale", nbf, flush=True)
+    h = np.zeros((nbf, nbf))
+    k = nbf // 4
+    for b, s in enumerate((1.0, 1e-152, 1e-163, 1e-304)):
+        o = b * k
+        A = spd(k, b + 1)
+        h[o:o + k, o:o + k] = s * (A - 0.5 * np.diag(np.diag(A)))
+    eye = np.eye(nbf)
+    Ca, Cb, ea, eb = dev(eye), dev(eye), dev(np.zeros(nbf)), dev(np.zeros(nbf))
+    zero = dev(np.zeros((3, nbf, nbf)))
+    q.qsgw_fock_unrestricted(ctx, zero, zero, dev(h), dev(0.0 * eye), dev(0.0 * eye), 4, 3, ea, eb,
+                             Ca, Cb)
+    ref = np.linalg.eigvalsh(h)
+    norm = np.abs(ref).max()
+    bound = 1e-13 * max(4.0, np.sqrt(nbf))
+    for C, e in ((Ca, ea), (Cb, eb)):
+        assert float((C.T @ C - dev(eye)).abs().max()) <= bound
+        assert float((dev(h) @ C - C * e[None, :]).abs().max()) <= bound * norm
+        assert np.max(np.abs(e.cpu().numpy() - ref)) <= bound * norm
