@@ -953,6 +953,31 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
   for (int64_t i = 0; i < nmol; ++i) any_diag = any_diag || P.mols[i].diag != nullptr;
   const int seg_stage[4] = {kStageMo, kStageRes, kStageSigma, kStageFock};
   int status = QSGW_OK;
+  // The first solve that failed: dsyevd's info of the last call of each bucket, the
+  // plans' error flags of all runs so far.
+  auto solver_status = [&]() -> int {
+    for (auto* bs : {&P.bM, &P.bF})
+      for (auto& b : *bs) {
+        std::vector<int> info(b.mols.size());
+        HIP_TRY(c, hipMemcpy(info.data(), b.info, info.size() * sizeof(int), hipMemcpyDeviceToHost));
+        for (size_t j = 0; j < info.size(); ++j)
+          if (info[j] != 0)
+            return fail(c, QSGW_ERR_SOLVER, "molecule %lld: dsyevd info %d", (long long)b.mols[j],
+                        info[j]);
+      }
+    for (int f = 0; f < 2; ++f) {
+      const EigPlan* e = f ? P.eF : P.eM;
+      if (!e) continue;
+      int64_t at = -1;
+      const int rc = eig_check(c, e, f ? "batched Fock eigensolve" : "batched Casida eigensolve", &at);
+      if (rc < 0 && at >= 0)
+        return fail(c, f ? rc : QSGW_ERR_SOLVER, "molecule %lld: %s",
+                    (long long)(f ? P.mF : P.mM)[(size_t)at],
+                    std::string(c->err).c_str());
+      if (rc < 0) return rc;
+    }
+    return QSGW_OK;
+  };
   for (int64_t it = 0; it < o->max_iter; ++it) {
     // stage spans: the kernel segments and the two eigensolves; kernel spans
     // inside the segments when they run eagerly
@@ -1015,6 +1040,11 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
         ms_hot += ms;
       }
     }
+    // A solve that failed comes first: what the flags and energies say hangs on its
+    // results.
+    bool suspect = false;
+    for (int64_t i = 0; i < nmol; ++i) suspect = suspect || flag_h[i] || !isfinite(deps[i]);
+    if (suspect) status = solver_status();
     for (int64_t i = 0; i < nmol; ++i) {
       if (status >= 0) {
         if (flag_h[i] & 1)
@@ -1031,26 +1061,7 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
     }
     if (status < 0) break;
   }
-  // solver info of the last call of each bucket
-  for (auto* bs : {&P.bM, &P.bF})
-    for (auto& b : *bs) {
-      std::vector<int> info(b.mols.size());
-      HIP_TRY(c, hipMemcpy(info.data(), b.info, info.size() * sizeof(int), hipMemcpyDeviceToHost));
-      for (size_t j = 0; j < info.size(); ++j)
-        if (info[j] != 0 && status >= 0)
-          status = fail(c, QSGW_ERR_SOLVER, "molecule %lld: dsyevd info %d", (long long)b.mols[j], info[j]);
-    }
-  for (int f = 0; f < 2 && status >= 0; ++f) {
-    const EigPlan* e = f ? P.eF : P.eM;
-    int64_t at = -1;
-    const int rc = e ? eig_check(c, e, f ? "batched Fock eigensolve" : "batched Casida eigensolve", &at)
-                     : QSGW_OK;
-    if (rc < 0 && at >= 0)
-      status = fail(c, rc, "molecule %lld: %s", (long long)(f ? P.mF : P.mM)[(size_t)at],
-                    std::string(c->err).c_str());
-    else if (rc < 0)
-      status = rc;
-  }
+  if (status >= 0) status = solver_status();
   bool all = true;
   for (int64_t i = 0; i < nmol; ++i) {
     all = all && first_ok[i] > 0;

@@ -1299,12 +1299,14 @@ __global__ __launch_bounds__(256) void k_dc_vecs(const EigDev* __restrict__ P,
   }
 }
 
-__global__ void k_dc_finish(const EigDev* __restrict__ P) {
+// Eigenvalues; NaN if the problem's error flags are set.
+__global__ void k_dc_finish(const EigDev* __restrict__ P, const int* __restrict__ err) {
   const EigDev& p = P[blockIdx.x];
   const double s = p.scale[S_T];
   const int ex = (int)p.scale[S_RANGE];
+  const bool ok = err[blockIdx.x] == 0;
   for (int i = threadIdx.x; i < p.n; i += blockDim.x)
-    p.ev[i] = ex == 0 ? p.d[i] * s : ldexp(p.d[i] * s, -ex);
+    p.ev[i] = !ok ? NAN : (ex == 0 ? p.d[i] * s : ldexp(p.d[i] * s, -ex));
   if (threadIdx.x == 0) p.scale[S_MAX] = 0.0;  // (for the plan's next run)
 }
 
@@ -1700,7 +1702,7 @@ static int run_merges(qsgw_ctx* c, const EigPlan* pl, const EigDev* P) {
     CHECK(run_products(c, pl, EigPlan::Products{L.jobs, L.njobs, L.nwg, L.fine}, (const JobMerge*)nullptr,
                        "eig merge"));
   }
-  hipLaunchKernelGGL(k_dc_finish, dim3(pl->count), dim3(256), 0, c->stream, P);
+  hipLaunchKernelGGL(k_dc_finish, dim3(pl->count), dim3(256), 0, c->stream, P, pl->err);
   return launch_check(c, "k_dc_finish");
 }
 
@@ -1747,7 +1749,7 @@ int eig_check(qsgw_ctx* c, const EigPlan* pl, const char* what, int64_t* at) {
     if (!e[i]) continue;
     if (at) *at = (int64_t)i;
     if (e[i] & 1) return fail(c, QSGW_ERR_SOLVER, "%s: reduction wait exceeded its bound", what);
-    if (e[i] & 4) return fail(c, QSGW_ERR_SOLVER, "%s: a value is not finite", what);
+    if (e[i] & 4) return fail(c, QSGW_ERR_NONFINITE, "%s: a value is not finite", what);
     return fail(c, QSGW_ERR_SOLVER, "%s: a tridiagonal block did not converge", what);
   }
   return QSGW_OK;

@@ -623,7 +623,8 @@ inline int eig_dense(qsgw_ctx* c, int64_t n, double* A, double* evals, const cha
 inline int eig_casida(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
                       bool fp64) {
   if (eig_two_stage_for(c, n, fp64)) return eig_two_stage(c, n, A, evals, what);
-  return eig_dense(c, n, A, evals, what, fp64 && c->eig_solver == QSGW_EIG_AUTO);
+  const int rc = eig_dense(c, n, A, evals, what, fp64 && c->eig_solver == QSGW_EIG_AUTO);
+  return rc == QSGW_ERR_NONFINITE ? QSGW_ERR_SOLVER : rc;  // (what an eigenvalue without a root is too)
 }
 
 // V (+)= 1/2 (G + G^T), G = sum of the nz partial slices of part.  Long sums

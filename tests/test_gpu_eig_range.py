@@ -59,7 +59,7 @@ def test_overflow_before_the_eigensolve_is_an_error(q, ctx, nbf):
             dev(eye * 1e60)]
     with pytest.raises(q.QsgwError) as ei:
         q.qsgw_fock_unrestricted(ctx, *args)
-    assert ei.value.code == q.ERR_SOLVER and "not finite" in str(ei.value)
+    assert ei.value.code == q.ERR_NONFINITE and "not finite" in str(ei.value)
     check_solve(q, ctx, spd(nbf, 1))
 
 
@@ -140,3 +140,29 @@ def test_blocks_of_very_different_scale(q, ctx, nbf):
         assert float((C.T @ C - dev(eye)).abs().max()) <= bound
         assert float((dev(h) @ C - C * e[None, :]).abs().max()) <= bound * norm
         assert np.max(np.abs(e.cpu().numpy() - ref)) <= bound * norm
+
+
+@pytest.mark.parametrize("iters", [1, 3])
+def test_batch_reports_the_eigensolve_that_failed(q, iters):
+    """A Fock matrix of a batch overflows: the call says so and names the molecule,
+    whatever the numbers that the eigensolve leaves look like afterwards."""
+    from qsgw_inputs import make_problem
+    stream = torch.cuda.Stream()
+    c = q.Context(stream)
+    try:
+        mols = []
+        with torch.cuda.stream(stream):
+            for nbf, seed in ((33, 1), (80, 2), (20, 3)):
+                p = make_problem(nbf, 4 * nbf, nbf // 6, 2 * nbf, 0.99, 900 + seed)
+                B, C, e = dev(p.B_ao), dev(p.C0), dev(p.eps0)
+                h = q.qsgw_hf_core(c, B, C, e, p.nocc)
+                if nbf == 80:
+                    h, C = torch.full_like(h, 1e308), C * 1e3
+                mols.append(dict(B_ao=B, h=h, nocc=p.nocc, eps=e, C=C))
+            print("batch with a Fock matrix that overflows", iters, flush=True)
+            with pytest.raises(q.QsgwError) as ei:
+                q.qsgw_iterate_batched(c, mols, 1e-3, tol=0.0, max_iter=iters)
+        assert ei.value.code == q.ERR_NONFINITE
+        assert "molecule 1: batched Fock eigensolve" in str(ei.value)
+    finally:
+        c.close()
