@@ -1424,6 +1424,7 @@ struct EigPlan {
   struct Step {
     Products w, x;
   };
+  std::vector<EigProblem> prob;
   std::vector<char> img;  // host image of the device tables (alive until the run's last wait)
   char* dev = nullptr;
   int* err = nullptr;
@@ -1524,18 +1525,24 @@ static void plan_merges(EigPlan* pl, const std::vector<EigDev>& P) {
   }
 }
 
-// The plan's tables to the device, its error flags and range words cleared.
-static int upload_plan(qsgw_ctx* c, const EigPlan* pl) {
-  HIP_TRY(c, hipMemcpyAsync(pl->dev, pl->img.data(), pl->img.size(), hipMemcpyHostToDevice,
-                            c->stream));
+// Error flags and range words cleared.
+static int init_plan(qsgw_ctx* c, const EigPlan* pl) {
   hipLaunchKernelGGL(k_eig_init, dim3(blocks_for(pl->count)), dim3(256), 0, c->stream,
                      reinterpret_cast<const EigDev*>(pl->dev + pl->probs), pl->err,
                      (int64_t)pl->count);
   return launch_check(c, "k_eig_init");
 }
 
+// The plan's tables to the device.
+static int upload_plan(qsgw_ctx* c, const EigPlan* pl) {
+  HIP_TRY(c, hipMemcpyAsync(pl->dev, pl->img.data(), pl->img.size(), hipMemcpyHostToDevice,
+                            c->stream));
+  return init_plan(c, pl);
+}
+
 int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, int set) {
   pl->count = (unsigned)count;
+  pl->prob.assign(prob, prob + count);
   std::vector<EigDev> P((size_t)count);
   // ---- sizes and teams ----
   int64_t wide_wgs = 0;
@@ -1592,24 +1599,30 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
   std::sort(order.begin(), order.end(), [&](int a, int b) {
     return P[(size_t)a].n != P[(size_t)b].n ? P[(size_t)a].n > P[(size_t)b].n : a < b;
   });
+  // (a problem in one workgroup needs no other one resident: it fills a round up,
+  // and what is left of them goes out in a launch of its own)
   std::vector<char> done((size_t)count, 0);
-  size_t left = (size_t)count;
-  while (left > 0) {
+  std::vector<std::vector<TeamWg>> coop;
+  auto add = [&](std::vector<TeamWg>& wg, int i) {
+    for (int g = 0; g < P[(size_t)i].team; ++g) wg.push_back({i, g});
+    done[(size_t)i] = 1;
+  };
+  for (int first : order) {
+    if (done[(size_t)first] || P[(size_t)first].team <= 1) continue;
+    if (P[(size_t)first].team > budget)
+      return fail(c, QSGW_ERR_UNSUPPORTED, "eigensolver: a team exceeds the device");
     std::vector<TeamWg> wg;
-    bool coop = false;
-    for (int i : order) {
-      const EigDev& p = P[(size_t)i];
-      if (done[(size_t)i]) continue;
-      // (a problem in one workgroup needs no co-resident partner)
-      if ((int64_t)wg.size() + p.team > (budget > 0 ? budget : 1)) continue;
-      for (int g = 0; g < p.team; ++g) wg.push_back({i, g});
-      coop = coop || p.team > 1;
-      done[(size_t)i] = 1;
-      --left;
-    }
-    if (wg.empty()) return fail(c, QSGW_ERR_UNSUPPORTED, "eigensolver: a team exceeds the device");
-    pl->rounds.push_back({put(pl->img, wg), (unsigned)wg.size(), coop});
+    for (int i : order)
+      if (!done[(size_t)i] && (int64_t)wg.size() + P[(size_t)i].team <= budget) add(wg, i);
+    coop.push_back(std::move(wg));
   }
+  // (the largest launch first: see eig_run)
+  std::stable_sort(coop.begin(), coop.end(), [](const auto& a, const auto& b) { return a.size() > b.size(); });
+  for (const auto& wg : coop) pl->rounds.push_back({put(pl->img, wg), (unsigned)wg.size(), true});
+  std::vector<TeamWg> rest;
+  for (int i : order)
+    if (!done[(size_t)i]) add(rest, i);
+  if (!rest.empty()) pl->rounds.push_back({put(pl->img, rest), (unsigned)rest.size(), false});
   plan_merges(pl, P);
   // ---- back-transformation ----
   std::vector<JobGW> gram;
@@ -1706,6 +1719,16 @@ static int run_merges(qsgw_ctx* c, const EigPlan* pl, const EigDev* P) {
   return launch_check(c, "k_dc_finish");
 }
 
+// Every problem of the plan by rocSOLVER dsyevd, one after another.
+static int run_library(qsgw_ctx* c, const EigPlan* pl) {
+  CHECK(init_plan(c, pl));  // (the range words of the round that did not run)
+  for (const EigProblem& p : pl->prob) {
+    if (p.ld != p.n) return fail(c, QSGW_ERR_UNSUPPORTED, "eigensolver: ld %lld", (long long)p.ld);
+    CHECK(syevd(c, p.n, p.A, p.evals, "eigensolver"));
+  }
+  return QSGW_OK;
+}
+
 int eig_run(qsgw_ctx* c, const EigPlan* pl) {
   const EigDev* P = reinterpret_cast<const EigDev*>(pl->dev + pl->probs);
   const dim3 per_prob(pl->count > 8 ? 64 : 512, pl->count);
@@ -1717,8 +1740,19 @@ int eig_run(qsgw_ctx* c, const EigPlan* pl) {
     if (r.coop) {
       CHECK(aux_queues(c));
       void* args[] = {&P, &wg, &err};
-      HIP_TRY(c, hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_tri_team), dim3(r.wgs),
-                                            dim3(kTeamThreads), args, 0, c->stream));
+      const hipError_t e =
+          hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_tri_team), dim3(r.wgs),
+                                     dim3(kTeamThreads), args, 0, c->stream);
+      if (e != hipSuccess) {
+        // The device does not take the launch now, whatever its properties say
+        // (another process may hold its queue for them).  A refusal of the first and
+        // largest round leaves the matrices as they were; one after that means that
+        // something else is wrong.
+        (void)hipGetLastError();
+        if (&r != &pl->rounds.front())
+          return fail(c, QSGW_ERR_HIP, "cooperative launch: %s", hipGetErrorString(e));
+        return run_library(c, pl);
+      }
     } else {
       hipLaunchKernelGGL(k_tri_team, dim3(r.wgs), dim3(kTeamThreads), 0, c->stream, P, wg, err);
     }
