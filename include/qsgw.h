@@ -131,17 +131,19 @@ int qsgw_rpa_build(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc, const
 
 /* Solvers of the Casida eigenproblem M Z = Z Omega^2 (Eq. (12)), chosen per
  * context with qsgw_set_eigensolver.  They apply to qsgw_rpa_solve and to the
- * Casida eigensolves inside qsgw_iterate and qsgw_gw_unrestricted (the Fock
- * eigensolves always take the automatic choice for their order, and so do
- * both eigensolves of the batched path). */
+ * Casida eigensolves inside qsgw_iterate and qsgw_gw_unrestricted. */
 /* Default: up to n = 3072 the library's one-stage solver, which holds the
  * matrix on the chip during its reduction (FP64 iterations and
  * qsgw_rpa_solve; the reduced-precision iterations take dsyevd, as their
  * trajectories hang on the last bits of the eigenvectors); above it the
  * two-stage solver, in the reduced precisions from n = 8192 on and dsyevd
- * below (as up to n = 3072 where the device has no cooperative launches). */
+ * below (as up to n = 3072 where the device takes no cooperative launches).
+ * The Fock eigensolves and both eigensolves of the batched path take the
+ * one-stage solver in FP64 up to n = 3072 and dsyevd otherwise. */
 #define QSGW_EIG_AUTO 0
-#define QSGW_EIG_ROCSOLVER 1 /* rocSOLVER dsyevd (one-stage tridiagonal reduction) */
+/* rocSOLVER dsyevd (one-stage tridiagonal reduction), for the Fock eigensolves
+ * and the batched path too */
+#define QSGW_EIG_ROCSOLVER 1
 /* Two-stage reduction, all FP64: dense -> band of half-width 64 by blocked
  * Householder panels whose two-sided updates are matrix products, band ->
  * tridiagonal by bulge chasing, divide and conquer on the tridiagonal matrix
@@ -494,7 +496,8 @@ int qsgw_iterate_unrestricted(qsgw_ctx* ctx, const qsgw_problem* prob, int64_t n
  * Each molecule's arithmetic is that of qsgw_iterate (same tile shapes, K
  * splits and epilogues).  In FP64 the Casida (and the Fock) eigensolves of
  * every molecule run in the same launches of the one-stage solver (orders up
- * to 3072); larger ones and those of the reduced precisions are rocSOLVER
+ * to 3072); larger ones, those of the reduced precisions and all of a context
+ * set to QSGW_EIG_ROCSOLVER are rocSOLVER
  * strided-batched dsyevd calls, one per size bucket, each matrix stored padded
  * to its bucket size with zero coupling and a diagonal above its Gershgorin
  * bound, so its own eigenpairs come first.  With QSGW_OPT_GRAPH

@@ -12,8 +12,8 @@
 //     search;
 //   * in FP64 one plan of the dense eigensolver (eigd.hip) each for the Casida
 //     and the Fock eigenproblems of every molecule it takes, all solved in the
-//     same launches.  Larger orders and the reduced precisions go to rocSOLVER
-//     strided-batched dsyevd, one call per size bucket: a matrix of order n in a bucket of order nb is stored
+//     same launches.  Larger orders, the reduced precisions and a context set to
+//     QSGW_EIG_ROCSOLVER go to rocSOLVER strided-batched dsyevd, one call per size bucket: a matrix of order n in a bucket of order nb is stored
 //     nb x nb with zero coupling to the padding and padding diagonal above the
 //     Gershgorin bound of the matrix, so its n lowest eigenpairs are its own.
 // With QSGW_OPT_GRAPH the kernel segments between the eigensolves are
@@ -580,10 +580,6 @@ struct Graphs {
   }
 };
 
-// Whether an eigenproblem of order n goes to the plan of the dense solver
-// (not in the reduced precisions, see eig_dense).
-bool in_team(qsgw_ctx* c, int64_t n, bool reduced) { return !reduced && eig_team_fits(c, n); }
-
 int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
 
 }  // namespace
@@ -639,7 +635,7 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
     m.nv = m.nbf - m.nocc;
     m.ntr = m.nocc * m.nv;
     m.nn = m.nbf * m.nbf;
-    const bool tM = in_team(c, m.ntr, fp32), tF = in_team(c, m.nbf, fp32);
+    const bool tM = eig_team_for(c, m.ntr, !fp32), tF = eig_team_for(c, m.nbf, !fp32);
     m.nbM = tM ? m.ntr : round_up(m.ntr, 128);
     m.nbF = tF ? m.nbf : round_up(m.nbf, 32);
     m.B_ao = p.B_ao;
@@ -803,7 +799,7 @@ extern "C" int qsgw_iterate_batched(qsgw_ctx* c, int64_t nmol, const qsgw_proble
     for (int64_t i = 0; i < nmol; ++i) {
       const Mol& m = P.mols[i];
       pre[s * nmol + i] = acc;
-      const bool pM = !in_team(c, m.ntr, fp32), pF = !in_team(c, m.nbf, fp32);
+      const bool pM = !eig_team_for(c, m.ntr, !fp32), pF = !eig_team_for(c, m.nbf, !fp32);
       const int64_t cnt[S_COUNT] = {m.ntr, m.naux * m.ntr, m.nn, pM ? m.nbM * m.nbM : 0,
                                     pF ? m.nbF * m.nbF : 0, m.naux, m.nbf,
                                     pM ? (m.ntr + kGerCols - 1) / kGerCols : 0,

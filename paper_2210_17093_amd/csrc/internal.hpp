@@ -614,16 +614,20 @@ inline bool eig_two_stage_for(const qsgw_ctx* c, int64_t n, bool fp64) {
 // last FP64 bits: two solvers of equal accuracy give trajectories that part at
 // the level of these variants' own error (up to 2e-7 in the orbitals after two
 // iterations at 117 basis functions, against 1e-12 in FP64), so these variants
-// keep the solver their results were obtained with.
+// keep the solver their results were obtained with.  QSGW_EIG_ROCSOLVER asks for
+// rocSOLVER everywhere.
+inline bool eig_team_for(qsgw_ctx* c, int64_t n, bool fp64) {
+  return fp64 && c->eig_solver != QSGW_EIG_ROCSOLVER && eig_team_fits(c, n);
+}
 inline int eig_dense(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
                      bool fp64) {
-  if (fp64 && eig_team_fits(c, n)) return eig_team(c, n, A, evals, what);
+  if (eig_team_for(c, n, fp64)) return eig_team(c, n, A, evals, what);
   return syevd(c, n, A, evals, what);
 }
 inline int eig_casida(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
                       bool fp64) {
   if (eig_two_stage_for(c, n, fp64)) return eig_two_stage(c, n, A, evals, what);
-  const int rc = eig_dense(c, n, A, evals, what, fp64 && c->eig_solver == QSGW_EIG_AUTO);
+  const int rc = eig_dense(c, n, A, evals, what, fp64);
   return rc == QSGW_ERR_NONFINITE ? QSGW_ERR_SOLVER : rc;  // (what an eigenvalue without a root is too)
 }
 

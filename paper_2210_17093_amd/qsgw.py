@@ -201,7 +201,7 @@ class Context:
         self.check(lib().qsgw_set_tiles(self.handle, spec.encode() if spec else None))
 
     def set_eigensolver(self, solver: int):
-        """Casida eigensolver of the context (EIG_AUTO, EIG_ROCSOLVER, EIG_TWO_STAGE)."""
+        """Eigensolver of the context (EIG_AUTO, EIG_ROCSOLVER, EIG_TWO_STAGE)."""
         self.check(lib().qsgw_set_eigensolver(self.handle, int(solver)))
 
     def get_tiles(self) -> str:

@@ -72,3 +72,31 @@ for a, m in zip(alone, mols):
     assert float((a - m["eps"]).abs().max()) <= 1e-8
 c.close()
 """)
+
+
+def test_rocsolver_choice_reaches_every_eigensolve(tmp_path):
+    """A context set to EIG_ROCSOLVER asks for no cooperative launch: Casida and
+    Fock eigensolves, single and batched.  (Without that choice all of them do.)"""
+    run_child(tmp_path, COOP, """
+from test_gpu_eig_range import dev
+from qsgw_inputs import make_problem
+c = q.Context()
+p = make_problem(140, 200, 9, 100, 0.99, 77)
+B, C, e = dev(p.B_ao), dev(p.C0), dev(p.eps0)
+h = q.qsgw_hf_core(c, B, C, e, p.nocc)
+def calls(solver, step):
+    c.set_eigensolver(solver)
+    before = shim.refused()
+    step()
+    return shim.refused() - before
+def single():
+    q.qsgw_iterate(c, B, h, p.nocc, e.clone(), C.clone(), 1e-3, tol=0.0, max_iter=1)
+def batch():
+    q.qsgw_iterate_batched(c, [dict(B_ao=B, h=h, nocc=p.nocc, eps=e.clone(), C=C.clone())], 1e-3,
+                           tol=0.0, max_iter=1)
+for step in (single, batch):
+    print("eigensolver choice", step.__name__, flush=True)
+    assert calls(q.EIG_AUTO, step) == 2
+    assert calls(q.EIG_ROCSOLVER, step) == 0
+c.close()
+""")
