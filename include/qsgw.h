@@ -549,9 +549,10 @@ int qsgw_iterate_batched(qsgw_ctx* ctx, int64_t nmol, const qsgw_problem* probs,
  * defaults (mo1=128x64, mo2=64x64, casida=128x128, rho=128x128,
  * sigma=64x64, exchange=64x64, 4096, 2048, 2048, mp2_target=32768,
  * persistent=0, dc_leaf=6144, panel_coop=1); NULL or "" restores all
- * defaults (FP64 products with few tiles then take smaller ones).  Every
- * later product and iteration on the context uses the table (results change only by rounding
- * order).  qsgw_get_tiles writes the current table in the same format.
+ * defaults.  An FP64 product whose shape is the default one takes smaller tiles
+ * where it has few (outside the batched path); any other shape is taken as it
+ * is.  Every later product and iteration on the context uses the table (results
+ * change only by rounding order).  qsgw_get_tiles writes the current table in the same format.
  */
 int qsgw_set_tiles(qsgw_ctx* ctx, const char* spec);
 int qsgw_get_tiles(qsgw_ctx* ctx, char* buf, int64_t size);

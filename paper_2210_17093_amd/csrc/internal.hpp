@@ -19,6 +19,7 @@
 #include "../../include/qsgw.h"
 #include "gemm_f64.hpp"
 #include "kernels.hpp"
+#include "tiles.hpp"
 
 using namespace qsgw;
 
@@ -121,30 +122,6 @@ struct Buffer {
   void* p = nullptr;
   size_t bytes = 0;
 };
-
-// Tile shapes of the tunable products (qsgw_set_tiles).  Symmetric (upper
-// tile) products take square shapes only.
-enum Shape { SH_64x64 = 0, SH_128x64 = 1, SH_128x128 = 2, SH_COUNT };
-enum Tunable { TU_MO1 = 0, TU_MO2, TU_CASIDA, TU_RHO, TU_SIGMA, TU_EXCHANGE, TU_COUNT };
-struct Tiles {
-  int shape[TU_COUNT] = {SH_128x64, SH_64x64, SH_128x128, SH_128x128, SH_64x64, SH_64x64};
-  // workgroups a K-split aims for when the output tiles alone are few
-  int64_t sigma_target = 4096, rho_target = 2048, exchange_target = 2048;
-  // the qsMP2 contraction (K = nbf * block transitions) wants more splits
-  int64_t mp2_target = 32768;
-  // batched grouped products: 0 = one workgroup per tile, n > 0 = a
-  // persistent grid of n workgroups per compute unit walking tile ranges
-  int64_t persistent = 0;
-  // projected divide and conquer of the two-stage eigensolver: tridiagonal
-  // blocks up to this order are solved with their eigenvectors formed
-  int64_t dc_leaf = 6144;
-  // two-stage eigensolver: 1 = panel QR in one cooperative launch per panel
-  // (the per-column launches when the device refuses it), 0 = per-column launches
-  int64_t panel_coop = 1;
-  bool chosen = false;  // a table was set: its shapes are taken as they are
-};
-inline int shape_m(int s) { return s == SH_64x64 ? 64 : 128; }
-inline int shape_n(int s) { return s == SH_128x128 ? 128 : 64; }
 
 }  // namespace
 
@@ -431,34 +408,15 @@ inline SplitPlan exchange_split(const Tiles& tl, int64_t nbf, int64_t naux, int6
   return split_plan(naux * nocc, splits_for(t * (t + 1) / 2, naux * nocc, tl.exchange_target));
 }
 
-// FP64 products whose tiles would leave compute units idle take smaller ones,
-// unless a tile table was set: below 256 workgroups (the chip's compute units)
-// 64 x 64, below that again 32 x 32.  The terms of an element and their order
-// stay the same.  24 basis functions, 95 transitions: rho 33 -> 8 us, Casida
-// matrix 28 -> 8 us, residues (tiles of 128 pairs x 128 or 32) 55 -> 24 us.
-constexpr int64_t kFewWgs = 256;
-template <int BM, int BN, bool TRI>
-bool few_wgs(const qsgw_ctx* c, int64_t M, int64_t N, int64_t batch, int64_t nz) {
-  const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
-  return !c->tiles.chosen &&
-         (TRI ? tm * (tm + 1) / 2 : tm * tn) * batch * (nz > 1 ? nz : 1) < kFewWgs;
-}
-
-// GEMM with the tile shape chosen at run time (BK: k-tile depth).
+// GEMM with a tile shape known at run time (BK: k-tile depth).
 template <class T, bool TRI, int BK = 16, class OA, class OB, class EPI>
-int gemm_shape(qsgw_ctx* c, int shape, const char* what, OA a, OB b, EPI e, int64_t M, int64_t N,
-               int64_t K, int64_t batch, SplitPlan sp = {0, 1}) {
-  if constexpr (std::is_same<T, double>::value) {
-    const bool few = shape == SH_64x64    ? true
-                     : shape == SH_128x64 ? few_wgs<128, 64, TRI>(c, M, N, batch, sp.nz)
-                                          : few_wgs<128, 128, TRI>(c, M, N, batch, sp.nz);
-    if (few) {
-      if (few_wgs<64, 64, TRI>(c, M, N, batch, sp.nz))
-        return gemm_t<T, 32, 32, TRI, BK>(c, what, a, b, e, M, N, K, batch, sp);
-      shape = SH_64x64;
-    }
-  }
+int gemm_tiles(qsgw_ctx* c, int shape, const char* what, OA a, OB b, EPI e, int64_t M, int64_t N,
+               int64_t K, int64_t batch, SplitPlan sp) {
   switch (shape) {
+    case SH_32x32:  // (FP64 only)
+      if constexpr (std::is_same<T, double>::value)
+        return gemm_t<T, 32, 32, TRI, BK>(c, what, a, b, e, M, N, K, batch, sp);
+      [[fallthrough]];
     case SH_64x64:
       return gemm_t<T, 64, 64, TRI, BK>(c, what, a, b, e, M, N, K, batch, sp);
     case SH_128x128:
@@ -470,6 +428,24 @@ int gemm_shape(qsgw_ctx* c, int shape, const char* what, OA a, OB b, EPI e, int6
         return gemm_t<T, 128, 64, false, BK>(c, what, a, b, e, M, N, K, batch, sp);
       }
   }
+}
+
+// GEMM of the shape `shape`, in FP64 a smaller one where its tiles are few.
+template <class T, bool TRI, int BK = 16, class OA, class OB, class EPI>
+int gemm_shape(qsgw_ctx* c, int shape, const char* what, OA a, OB b, EPI e, int64_t M, int64_t N,
+               int64_t K, int64_t batch, SplitPlan sp = {0, 1}) {
+  if constexpr (std::is_same<T, double>::value)
+    shape = fitting_shape(shape, TRI, M, N, batch, sp.nz);
+  return gemm_tiles<T, TRI, BK>(c, shape, what, a, b, e, M, N, K, batch, sp);
+}
+// GEMM of the tile table's product k.
+template <class T, bool TRI, int BK = 16, class OA, class OB, class EPI>
+int gemm_table(qsgw_ctx* c, Tunable k, const char* what, OA a, OB b, EPI e, int64_t M, int64_t N,
+               int64_t K, int64_t batch, SplitPlan sp = {0, 1}) {
+  const int shape = std::is_same<T, double>::value
+                        ? table_shape(c->tiles, k, TRI, M, N, batch, sp.nz)
+                        : c->tiles.shape[k];
+  return gemm_tiles<T, TRI, BK>(c, shape, what, a, b, e, M, N, K, batch, sp);
 }
 
 // A K-split plan with chunks rounded up to a multiple of `bk`.

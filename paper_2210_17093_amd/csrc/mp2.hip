@@ -69,7 +69,7 @@ int stage_mp2(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc, const double
       Strided<true> A{D, nbf * ntb, 1, 0, nbf};
       Strided<true> B{R, nbf * ntb, 1, 0, nbf};
       EpiStore Ep{part, nbf, 0, nn, 1.0};
-      CHECK((gemm_shape<double, false>(c, c->tiles.shape[TU_SIGMA], "mp2/sigma", A, B, Ep, nbf,
+      CHECK((gemm_table<double, false>(c, TU_SIGMA, "mp2/sigma", A, B, Ep, nbf,
                                        nbf, nbf * ntb, 1, sp)));
       CHECK(reduce_sym(c, part, sp.nz, nbf, V, (b > 0 || accumulate) ? 1 : 0));
     }

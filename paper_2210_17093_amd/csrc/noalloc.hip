@@ -97,11 +97,11 @@ int qsgw_sigma_qs_noalloc(qsgw_ctx* c, int64_t nbf, int64_t nocc, int64_t ns, co
   EpiStore E{part, nbf, 0, nn, 1.0};
   if (wh) {
     Strided<true> A{wh, nbf * ns, 1, 0, nbf};
-    CHECK((gemm_shape<double, false>(c, c->tiles.shape[TU_SIGMA], "sigma_qs_noalloc", A, B, E, nbf,
+    CHECK((gemm_table<double, false>(c, TU_SIGMA, "sigma_qs_noalloc", A, B, E, nbf,
                                      nbf, nbf * ns, 1, sp)));
   } else {
     PoleScaledResidueOp A{w, eps, Omega, nbf, nocc, ns, eta};
-    CHECK((gemm_shape<double, false>(c, c->tiles.shape[TU_SIGMA], "sigma_qs_noalloc", A, B, E, nbf,
+    CHECK((gemm_table<double, false>(c, TU_SIGMA, "sigma_qs_noalloc", A, B, E, nbf,
                                      nbf, nbf * ns, 1, sp)));
   }
   hipLaunchKernelGGL(k_reduce_sym, dim3(blocks_for(nn)), dim3(256), 0, c->stream, part, sp.nz, nbf,

@@ -130,7 +130,7 @@ int stage_mo_transform_t(qsgw_ctx* c, int64_t nbf, int64_t naux, const double* B
     EpiStore E{T, nbf, 0, 0, 1.0};
     E.nt = true;
     SPAN_OPEN(sp, kKMo1);
-    CHECK((gemm_shape<CT, false, BKm>(c, c->tiles.shape[TU_MO1], "mo_transform/1", A, B, E, naux * nbf,
+    CHECK((gemm_table<CT, false, BKm>(c, TU_MO1, "mo_transform/1", A, B, E, naux * nbf,
                                  nbf, nbf, 1)));
     SPAN_CLOSE(sp);
   }
@@ -140,7 +140,7 @@ int stage_mo_transform_t(qsgw_ctx* c, int64_t nbf, int64_t naux, const double* B
     EpiStore E{B_mo, nbf, nn, 0, 1.0};
     E.c32 = B_mo32;  // FP32 copy for the residue product of the FP32 variant
     SPAN_OPEN(sp, kKMo2);
-    CHECK((gemm_shape<CT, true, BKm>(c, c->tiles.shape[TU_MO2], "mo_transform/2", A, B, E, nbf, nbf, nbf,
+    CHECK((gemm_table<CT, true, BKm>(c, TU_MO2, "mo_transform/2", A, B, E, nbf, nbf, nbf,
                                 naux)));
     SPAN_CLOSE(sp);
   }
@@ -182,7 +182,7 @@ int stage_rpa_build(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc, const 
   EpiCasida E{M, delta, ntr};
   if (prec == QSGW_PREC_FP32) {
     Strided<false, float> A{Bt32, 1, ntr, 0, ntr};
-    CHECK((gemm_shape<float, true, 32>(c, c->tiles.shape[TU_CASIDA], "rpa_build", A, A, E, ntr,
+    CHECK((gemm_table<float, true, 32>(c, TU_CASIDA, "rpa_build", A, A, E, ntr,
                                        ntr, naux, 1)));
   } else if (prec == QSGW_PREC_SPLIT_BF16) {
     // Bt split once into BF16 halves in k-blocks of 8 (rows t, k = P)
@@ -193,11 +193,11 @@ int stage_rpa_build(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc, const 
                        ntr, ntr, naux, rp, kpad, bs);
     CHECK(launch_check(c, "k_split_cols"));
     Split8 A{bs, rp, kpad * rp, 0};
-    CHECK((gemm_shape<Bf16x3, true, 32>(c, c->tiles.shape[TU_CASIDA], "rpa_build", A, A, E, ntr,
+    CHECK((gemm_table<Bf16x3, true, 32>(c, TU_CASIDA, "rpa_build", A, A, E, ntr,
                                         ntr, kpad, 1)));
   } else {
     Strided<false> A{Bt, 1, ntr, 0, ntr};
-    CHECK((gemm_shape<double, true>(c, c->tiles.shape[TU_CASIDA], "rpa_build", A, A, E, ntr, ntr,
+    CHECK((gemm_table<double, true>(c, TU_CASIDA, "rpa_build", A, A, E, ntr, ntr,
                                     naux, 1)));
   }
   SPAN_CLOSE(sp);
@@ -331,17 +331,17 @@ int stage_residues_t(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t ntr, const 
       if constexpr (x3) {
         Split8 A{splitRA, naux_pad, kpt * naux_pad, 0};
         Split8 B{splitZ, ns_pad, kpt * ns_pad, 0};
-        return gemm_shape<CT, false, 32>(c, c->tiles.shape[TU_RHO], "residues/rho", A, B, E, naux,
+        return gemm_table<CT, false, 32>(c, TU_RHO, "residues/rho", A, B, E, naux,
                                          ns, kpt, 1, p);
       } else if constexpr (f32) {
         Strided<true, float> A{Bt32, ntr, 1, 0, naux};
         Strided<true, float> B{Z32, ntr, 1, 0, ns};
-        return gemm_shape<CT, false, 32>(c, c->tiles.shape[TU_RHO], "residues/rho", A, B, E, naux,
+        return gemm_table<CT, false, 32>(c, TU_RHO, "residues/rho", A, B, E, naux,
                                          ns, ntr, 1, p);
       } else {
         Strided<true> A{Bt, ntr, 1, 0, naux};
         Strided<true> B{Z + s0 * ntr, ntr, 1, 0, ns};
-        return gemm_shape<CT, false>(c, c->tiles.shape[TU_RHO], "residues/rho", A, B, E, naux, ns,
+        return gemm_table<CT, false>(c, TU_RHO, "residues/rho", A, B, E, naux, ns,
                                      ntr, 1, p);
       }
     };
@@ -394,7 +394,7 @@ int stage_residues_t(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t ntr, const 
     } else {
       PairRows<8, 16> A{B_mo, nn, 0, nbf, blocks};
       Strided<false> B{rho, 1, ldr, 0, ns};
-      if (few_wgs<128, 128, false>(c, nblk * 128, ns, 1, 1))
+      if (tile_wgs(128, 128, false, nblk * 128, ns, 1, 1) < kFewWgs)
         CHECK((gemm_t<CT, 128, 32, false>(c, "residues/w", A, B, E, nblk * 128, ns, naux, 1)));
       else
         CHECK((gemm_t<CT, 128, 128, false>(c, "residues/w", A, B, E, nblk * 128, ns, naux, 1)));
@@ -552,11 +552,11 @@ int stage_sigma_qs(qsgw_ctx* c, int64_t nbf, int64_t nocc, int64_t ns, const dou
   if (wh) {
     // pole weights already applied by the residue epilogue
     Strided<true> A{wh, nbf * ns, 1, 0, nbf};
-    CHECK((gemm_shape<double, false>(c, c->tiles.shape[TU_SIGMA], "sigma_qs", A, B, E, nbf, nbf,
+    CHECK((gemm_table<double, false>(c, TU_SIGMA, "sigma_qs", A, B, E, nbf, nbf,
                                      nbf * ns, 1, sp)));
   } else {
     PoleScaledResidueOp A{w, eps, Omega, nbf, nocc, ns, eta};
-    CHECK((gemm_shape<double, false>(c, c->tiles.shape[TU_SIGMA], "sigma_qs", A, B, E, nbf, nbf,
+    CHECK((gemm_table<double, false>(c, TU_SIGMA, "sigma_qs", A, B, E, nbf, nbf,
                                      nbf * ns, 1, sp)));
   }
   SPAN_CLOSE(spn);
@@ -595,7 +595,7 @@ int stage_jk_mo(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc, const doub
   CHECK(ws_get(c, W_PART, (size_t)(sp.nz * nn), Kpart));
   OccRowsOp A{B_mo, nbf, nocc};
   EpiStore E{*Kpart, nbf, 0, nn, 1.0};
-  CHECK((gemm_shape<double, true>(c, c->tiles.shape[TU_EXCHANGE], "exchange_mo", A, A, E, nbf, nbf,
+  CHECK((gemm_table<double, true>(c, TU_EXCHANGE, "exchange_mo", A, A, E, nbf, nbf,
                                   naux * nocc, 1, sp)));
   *nz = sp.nz;
   return QSGW_OK;
@@ -1419,7 +1419,7 @@ int qsgw_gw_unrestricted(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc_a,
   {
     EpiCasida E{M, delta, ntr};
     Strided<false> A{Bt, 1, ntr, 0, ntr};
-    CHECK((gemm_shape<double, true>(c, c->tiles.shape[TU_CASIDA], "gw_unrestricted/casida", A, A,
+    CHECK((gemm_table<double, true>(c, TU_CASIDA, "gw_unrestricted/casida", A, A,
                                     E, ntr, ntr, naux, 1)));
   }
   CHECK(spn.close());
@@ -1511,7 +1511,7 @@ int qsgw_fock_unrestricted(qsgw_ctx* c, int64_t nbf, int64_t naux, int64_t nocc_
     {
       OccRowsOp A{Bs[sp], nbf, no[sp]};
       EpiStore E{Kpart, nbf, 0, nn, 1.0};
-      CHECK((gemm_shape<double, true>(c, c->tiles.shape[TU_EXCHANGE], "fock_u/exchange", A, A, E,
+      CHECK((gemm_table<double, true>(c, TU_EXCHANGE, "fock_u/exchange", A, A, E,
                                       nbf, nbf, naux * no[sp], 1, spl)));
     }
     CHECK(congruence_t(c, nbf, Cs[sp], h, tmp, hmo));
@@ -1628,7 +1628,6 @@ int qsgw_set_tiles(qsgw_ctx* c, const char* spec) {
   if (!c) return QSGW_ERR_INVALID_ARG;
   Tiles t;  // defaults
   if (spec && *spec) {
-    t.chosen = true;
     static const char* names[TU_COUNT] = {"mo1", "mo2", "casida", "rho", "sigma", "exchange"};
     static const bool square[TU_COUNT] = {false, true, true, false, false, true};
     std::string all(spec);
