@@ -214,7 +214,8 @@ __global__ void k_fock_assemble(const double* hmo, const double* J, const double
   double k = 0.0;
   for (int64_t z = 0; z < nz; ++z) k += Kpart[z * nn + idx];
   const double h = 0.5 * (hmo[m * n + c] + hmo[c * n + m]);
-  F[idx] = h + J[idx] - k + V[idx];
+  const int64_t lo = m >= c ? idx : c * n + m;
+  F[idx] = h + J[lo] - k + V[lo];
 }
 
 __global__ void k_hf_core_mo(const double* eps, const double* J, const double* Kpart, int64_t nz,

@@ -469,7 +469,9 @@ __global__ void k_occ_trace(const double* bmo, int64_t naux, int64_t nbf, int64_
 // P in [g pg, (g + 1) pg) of c_P bmo[P][e], then k_sum_slices over g.
 __global__ void k_hartree_part(const double* bmo, const double* c, int64_t naux, int64_t nn,
                                int64_t pg, double* out);
-// F[m][n] = sym(hmo)[m][n] + J[m][n] - sum_z Kpart[z][m][n] + V[m][n]
+// F[m][n] = sym(hmo)[m][n] + J[m][n] - sum_z Kpart[z][m][n] + V[m][n], J and V by
+// their lower triangles (a caller's potential need not be symmetric, and one
+// eigensolver reads a triangle of F, the other all of it)
 __global__ void k_fock_assemble(const double* hmo, const double* J, const double* Kpart, int64_t nz,
                                 const double* V, int64_t n, double* F);
 // X = diag(eps) - J + sum_z Kpart   (HF core in the MO basis)

@@ -235,3 +235,31 @@ def test_unrestricted_two_stage_projection_matches_oracle(q, nbf, naux, na, nb):
         for V, R in ((host(Va), V_ref[0]), (host(Vb), V_ref[1])):
             np.testing.assert_array_equal(V, V.T)
             assert np.abs(V - R).max() <= 1e-10 * np.abs(R).max() + 1e-15
+
+
+@pytest.mark.parametrize("nbf", [24, 150])
+@pytest.mark.parametrize("solver", [0, 1])
+def test_fock_reads_the_potential_by_its_lower_triangle(q, nbf, solver):
+    """A potential with another upper triangle gives the same orbitals, whichever
+    solver takes the Fock matrix."""
+    print("fock, potential with a foreign upper triangle", nbf, solver, flush=True)
+    p = make_problem(nbf, 2 * nbf, nbf // 6, nbf, 0.99, 4)
+    rng = np.random.default_rng(nbf)
+    V = rng.standard_normal((nbf, nbf)) * 0.01
+    V = np.tril(V) + np.tril(V, -1).T
+    other = np.tril(V) + np.triu(rng.standard_normal((nbf, nbf)), 1)
+    c = q.Context()
+    try:
+        c.set_eigensolver(solver)
+        h = q.qsgw_hf_core(c, dev(p.B_ao), dev(p.C0), dev(p.eps0), p.nocc)
+        B = dev(O.mo_transform(p.B_ao, p.C0))
+        out = []
+        for W in (V, other):
+            ea, eb, Ca, Cb = dev(0 * p.eps0), dev(0 * p.eps0), dev(p.C0), dev(p.C0)
+            q.qsgw_fock_unrestricted(c, B, B, h, dev(W), dev(W), p.nocc, p.nocc, ea, eb, Ca, Cb)
+            torch.cuda.synchronize()
+            out.append((ea, eb, Ca, Cb))
+        for a, b in zip(*out):
+            assert torch.equal(a, b)
+    finally:
+        c.close()
