@@ -30,7 +30,6 @@
 // All arrays are column-major; a symmetric row-major matrix is its own
 // column-major view.  Everything runs in FP64.
 #include "internal.hpp"
-#include "poles.hpp"
 #include "wave.hpp"
 #include "wy.hpp"
 
@@ -308,13 +307,7 @@ __device__ __forceinline__ void panel_columns(d16 (&P)[4], double* A, int64_t ld
     lds_barrier();
     auto dot = [&](int c) { return (sm.sum[0][c] + sm.sum[1][c]) + (sm.sum[2][c] + sm.sum[3][c]); };
     const double alpha = sm.row[j], sig = dot(j);
-    double t = 0.0, beta = alpha, scale = 0.0;
-    if (!(sig <= kTinySquare)) {
-      const double n2 = fma(alpha, alpha, sig), r = fast_rsqrt(n2);
-      beta = -copysign(n2 * r, alpha);
-      t = fma(fabs(alpha), r, 1.0);
-      scale = fast_rcp(alpha - beta);
-    }
+    const auto [t, beta, scale] = reflector(alpha, sig);
     // w_c = P[j][c] + scale dots[c] (w = v^T P[:, c]), P -= tau v w^T; row j has v = 1
     d16 v;
 #pragma unroll
@@ -927,13 +920,7 @@ __global__ __launch_bounds__(256, 2) void k_bulge_chase(const double* __restrict
     // ---- reflector of the column (row r0 at lane s; rows past the matrix are zero) ----
     const double alpha = read_lane(x, s);
     const double sig = wave_total(lane != s ? x * x : 0.0);
-    double tau = 0.0, beta = alpha, scale = 0.0;
-    if (!(sig <= kTinySquare)) {
-      const double n2 = fma(alpha, alpha, sig), r = fast_rsqrt(n2);
-      beta = -copysign(n2 * r, alpha);
-      tau = fma(fabs(alpha), r, 1.0);
-      scale = fast_rcp(alpha - beta);
-    }
+    const auto [tau, beta, scale] = reflector(alpha, sig);
     const double v = lane == s ? 1.0 : x * scale;
     if (wave == 0) {
       publish(V2 + (f + k) * b + ((lane - s) & W), v);

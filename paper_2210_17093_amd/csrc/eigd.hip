@@ -24,7 +24,6 @@
 // order reversed).  A root's vector is zh / (d - lambda) there, a deflated one keeps
 // its half's sign.
 #include "internal.hpp"
-#include "poles.hpp"
 #include "wave.hpp"
 #include "wy.hpp"
 
@@ -256,17 +255,7 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
 #pragma unroll
     for (int q = 0; q < NW; ++q) sig += sm.red[0][rg][q];
     const double alpha = sm.al[0][rg];
-    // beta = -sign(alpha) r, tau = (beta - alpha) / beta = 1 + |alpha| / r,
-    // 1 / (alpha - beta) = sign(alpha) / (|alpha| + r)
-    double tau = 0.0, beta = alpha, scale = 0.0;
-    if (!(sig <= kTinySquare)) {
-      const double x = alpha * alpha + sig;
-      const double ir = fast_rsqrt(x), nr = x * ir;
-      const double r = fma(fma(-nr, nr, x), 0.5 * ir, nr);
-      beta = -copysign(r, alpha);
-      tau = fma(fabs(alpha), ir, 1.0);
-      scale = copysign(fast_rcp(fabs(alpha) + r), alpha);
-    }
+    const auto [tau, beta, scale] = reflector(alpha, sig);
 #pragma unroll
     for (int u = 0; u < CU; ++u) {
       const int c = tc + TC * u;

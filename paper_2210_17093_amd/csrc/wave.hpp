@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "poles.hpp"
+
 namespace qsgw {
 
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
@@ -47,6 +49,27 @@ __device__ __forceinline__ double fast_rsqrt(double x) {
   double y = __builtin_amdgcn_rsq(x);
   y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
   return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+// Householder reflector H = I - tau v v^T of a column (alpha, rest) with the rest's
+// sum of squares sig: H (alpha, rest) = (beta, 0), v = (1, scale rest).  The norm
+// r is corrected to its last bit, as beta goes into the reduced matrix:
+//   beta = -sign(alpha) r, tau = (beta - alpha) / beta = 1 + |alpha| / r,
+//   scale = 1 / (alpha - beta) = sign(alpha) / (|alpha| + r).
+// sig up to kTinySquare counts as zero (H = I); a NaN passes through.
+struct Reflector {
+  double tau, beta, scale;
+};
+__device__ __forceinline__ Reflector reflector(double alpha, double sig) {
+  Reflector h{0.0, alpha, 0.0};
+  if (!(sig <= kTinySquare)) {
+    const double x = fma(alpha, alpha, sig);
+    const double ir = fast_rsqrt(x), nr = x * ir;
+    const double r = fma(fma(-nr, nr, x), 0.5 * ir, nr);
+    h.beta = -copysign(r, alpha);
+    h.tau = fma(fabs(alpha), ir, 1.0);
+    h.scale = copysign(fast_rcp(fabs(alpha) + r), alpha);
+  }
+  return h;
 }
 // Workgroup barrier for LDS traffic alone: global stores stay in flight (the
 // row that one team member publishes would otherwise hold up its y by a
