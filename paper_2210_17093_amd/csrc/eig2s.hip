@@ -994,12 +994,12 @@ __global__ __launch_bounds__(256, 2) void k_bulge_chase(const double* __restrict
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const double zu = read_lane(z, (u & 3) + 16 * ((u >> 2) & 1) + 32 * (u >> 3));
-        O[u] = fma(-t2, zu, fma(-t1, read_lane(vpa, c0 + u), O[u]));
+        O[u] -= fma(t2, zu, t1 * read_lane(vpa, c0 + u));
       }
     }
 #pragma unroll
     for (int u = 0; u < 16; ++u)
-      D[u] = fma(-w, read_lane(va, c0 + u), fma(-v, read_lane(w, c0 + u), D[u]));
+      D[u] -= fma(w, read_lane(va, c0 + u), v * read_lane(w, c0 + u));
     // column s of D becomes O's last one; the next sweep's column and row to LDS
     O[s & 15] = wave == s >> 4 ? D[s & 15] : O[s & 15];
     if (lane == s) {

@@ -287,8 +287,7 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
         double t = 0.0;
 #pragma unroll
         for (int u = 0; u < CU; ++u) {
-          a[l][u] = fma(-bv, wp[u], a[l][u]);
-          a[l][u] = fma(-bw, vp[u], a[l][u]);
+          a[l][u] -= fma(bv, wp[u], bw * vp[u]);
           t = fma(a[l][u], v[u], t);
         }
         s4[q] = t;
