@@ -405,7 +405,7 @@ struct TeamShape {
 };
 constexpr TeamShape kTeamShapes[] = {
     {128, 128}, {64, 256}, {16, 512}, {64, 512}, {16, 1024}, {40, 1024}, {12, 1536},
-    {28, 1536}, {8, 2048}, {20, 2048}, {12, 2560}, {12, 3072}, {16, 2048}, {12, 2048},
+    {28, 1536}, {8, 2048}, {20, 2048}, {12, 2560}, {12, 3072},
 };
 __global__ __launch_bounds__(kTeamThreads, 2) void k_tri_team(const EigDev* __restrict__ P,
                                                               const TeamWg* __restrict__ wg,
@@ -426,9 +426,7 @@ __global__ __launch_bounds__(kTeamThreads, 2) void k_tri_team(const EigDev* __re
     case 8: tri_team<512, 4, 8>(p, t.g, sm, err); break;
     case 9: tri_team<512, 4, 20>(p, t.g, sm, err); break;
     case 10: tri_team<512, 5, 12>(p, t.g, sm, err); break;
-    case 11: tri_team<512, 6, 12>(p, t.g, sm, err); break;
-    case 12: tri_team<512, 4, 16>(p, t.g, sm, err); break;
-    default: tri_team<512, 4, 12>(p, t.g, sm, err); break;
+    default: tri_team<512, 6, 12>(p, t.g, sm, err); break;
   }
 }
 
