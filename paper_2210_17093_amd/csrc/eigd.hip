@@ -46,7 +46,7 @@ struct EigDev {
   double* vec;         // merge vectors, kVec x n
   int* idx;            // merge index maps, kIdx x n
   double *G, *T;       // Gram matrices and T factors [blocks][128][128]
-  double* scale;       // kScale words, see below
+  double* scale;       // kScale words of the plan's, see below
   int64_t ld;
   int n, team, cfg, pad;
 };
@@ -430,11 +430,10 @@ __global__ __launch_bounds__(kTeamThreads, 2) void k_tri_team(const EigDev* __re
   }
 }
 
-__global__ void k_eig_init(const EigDev* __restrict__ P, int* err, int64_t n) {
+__global__ void k_eig_init(double* scale, int* err, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  err[i] = 0;
-  P[i].scale[S_RANGE] = P[i].scale[S_MAX] = 0.0;
+  if (i < n * kScale) scale[i] = 0.0;
+  if (i < n) err[i] = 0;
 }
 
 // kEmpty into the exchange slots of every problem (blockIdx.y) solved by more
@@ -1414,6 +1413,7 @@ struct EigPlan {
   std::vector<char> img;  // host image of the device tables (alive until the run's last wait)
   char* dev = nullptr;
   int* err = nullptr;
+  double* scale = nullptr;
   size_t probs = 0, base = 0, tblocks = 0;
   unsigned count = 0, nbase = 0, ntb = 0;
   bool clear = false;
@@ -1513,17 +1513,9 @@ static void plan_merges(EigPlan* pl, const std::vector<EigDev>& P) {
 
 // Error flags and range words cleared.
 static int init_plan(qsgw_ctx* c, const EigPlan* pl) {
-  hipLaunchKernelGGL(k_eig_init, dim3(blocks_for(pl->count)), dim3(256), 0, c->stream,
-                     reinterpret_cast<const EigDev*>(pl->dev + pl->probs), pl->err,
-                     (int64_t)pl->count);
+  hipLaunchKernelGGL(k_eig_init, dim3(blocks_for((int64_t)pl->count * kScale)), dim3(256), 0,
+                     c->stream, pl->scale, pl->err, (int64_t)pl->count);
   return launch_check(c, "k_eig_init");
-}
-
-// The plan's tables to the device.
-static int upload_plan(qsgw_ctx* c, const EigPlan* pl) {
-  HIP_TRY(c, hipMemcpyAsync(pl->dev, pl->img.data(), pl->img.size(), hipMemcpyHostToDevice,
-                            c->stream));
-  return init_plan(c, pl);
 }
 
 int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, int set) {
@@ -1551,6 +1543,9 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
   CHECK(ws_get(c, W_EIGD_I + 3 * set, ni, &I));
   pl->err = I;
   I += count;
+  pl->scale = D;
+  D += kScale * count;
+  CHECK(init_plan(c, pl));
   for (int64_t i = 0; i < count; ++i) {
     const int64_t n = prob[i].n, nb = (n - 1 + kBk - 1) / kBk;
     EigDev& p = P[(size_t)i];
@@ -1572,8 +1567,7 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
     p.G = D;
     p.T = D + nb * kBk * kBk;
     D += 2 * nb * kBk * kBk;
-    p.scale = D;
-    D += kScale;
+    p.scale = pl->scale + kScale * i;
     p.idx = I;
     I += kIdx * n;
     pl->clear = pl->clear || p.team > 1;
@@ -1656,7 +1650,9 @@ int eig_plan(qsgw_ctx* c, EigPlan* pl, const EigProblem* prob, int64_t count, in
     pl->steps.push_back(st);
   }
   CHECK(ws_get(c, W_EIGD_T + 3 * set, pl->img.size() + 256, &pl->dev));
-  return upload_plan(c, pl);
+  HIP_TRY(c, hipMemcpyAsync(pl->dev, pl->img.data(), pl->img.size(), hipMemcpyHostToDevice,
+                            c->stream));
+  return QSGW_OK;
 }
 
 template <class J>
@@ -1795,6 +1791,8 @@ int eig_tridiag(qsgw_ctx* c, int64_t n, double* d, double* e, double* E, const c
   CHECK(ws_get(c, W_EIGD_F, (size_t)(2 * n * n + kVec * n + kScale), &D));
   CHECK(ws_get(c, W_EIGD_I, (size_t)(1 + kIdx * n), &I));
   pl.err = I;
+  pl.scale = D + 2 * n * n + kVec * n;
+  CHECK(init_plan(c, &pl));
   EigDev p{};
   p.n = (int)n;
   p.ev = p.d = d;
@@ -1803,13 +1801,14 @@ int eig_tridiag(qsgw_ctx* c, int64_t n, double* d, double* e, double* E, const c
   p.B = D;
   p.U = D + n * n;
   p.vec = D + 2 * n * n;
-  p.scale = p.vec + kVec * n;
+  p.scale = pl.scale;
   p.idx = I + 1;
   const std::vector<EigDev> P(1, p);
   pl.probs = put(pl.img, P);
   plan_merges(&pl, P);
   CHECK(ws_get(c, W_EIGD_T, pl.img.size() + 256, &pl.dev));
-  CHECK(upload_plan(c, &pl));
+  HIP_TRY(c, hipMemcpyAsync(pl.dev, pl.img.data(), pl.img.size(), hipMemcpyHostToDevice,
+                            c->stream));
   CHECK(run_merges(c, &pl, reinterpret_cast<const EigDev*>(pl.dev + pl.probs)));
   int64_t at = 0;
   return eig_check(c, &pl, what, &at);

@@ -595,9 +595,13 @@ inline bool eig_two_stage_for(const qsgw_ctx* c, int64_t n, bool fp64) {
 inline bool eig_team_for(qsgw_ctx* c, int64_t n, bool fp64) {
   return fp64 && c->eig_solver != QSGW_EIG_ROCSOLVER && eig_team_fits(c, n);
 }
+// One problem up to this order goes to rocSOLVER: its few launches are done before
+// a plan is on the device (a whole qsgw_rpa_solve of order 1 takes 75 us with
+// dsyevd and 108 with the team solver, 3: 150 and 166, 4: 174 and 182, 5: 194 and 185).
+constexpr int64_t kEigTeamMin = 5;
 inline int eig_dense(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
                      bool fp64) {
-  if (eig_team_for(c, n, fp64)) return eig_team(c, n, A, evals, what);
+  if (n >= kEigTeamMin && eig_team_for(c, n, fp64)) return eig_team(c, n, A, evals, what);
   return syevd(c, n, A, evals, what);
 }
 inline int eig_casida(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what,
