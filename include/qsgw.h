@@ -36,7 +36,8 @@
  *     for NaN and infinity on the device (one pass over each input, then one
  *     read-back, so the call synchronizes its stream once before its work
  *     is queued) and returns QSGW_ERR_NONFINITE naming the array; nothing
- *     else runs then.
+ *     else runs then.  A Fock matrix that overflows on the way is
+ *     QSGW_ERR_NONFINITE too, a Casida matrix QSGW_ERR_SOLVER.
  *   - One context per host thread.  Calls on one context must not overlap.
  */
 #ifndef QSGW_H
@@ -137,7 +138,8 @@ int qsgw_rpa_build(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc, const
  * qsgw_rpa_solve; the reduced-precision iterations take dsyevd, as their
  * trajectories hang on the last bits of the eigenvectors); above it the
  * two-stage solver, in the reduced precisions from n = 8192 on and dsyevd
- * below (as up to n = 3072 where the device takes no cooperative launches).
+ * below (as up to n = 4, and up to n = 3072 where the device takes no
+ * cooperative launches).
  * The Fock eigensolves and both eigensolves of the batched path take the
  * one-stage solver in FP64 up to n = 3072 and dsyevd otherwise. */
 #define QSGW_EIG_AUTO 0
@@ -338,6 +340,7 @@ int qsgw_gw_unrestricted(qsgw_ctx* ctx, int64_t nbf, int64_t naux, int64_t nocc_
  * h: [nbf][nbf] device (AO basis, orthonormal); V_a, V_b: [nbf][nbf] device, the
  *   spins' correlation potentials in their current MO bases (qsgw_gw_unrestricted);
  * eps_a, eps_b: [nbf] device out; C_a, C_b: [nbf][nbf] device in/out.
+ * V_a, V_b count by their lower triangles (row-major).
  * Errors: 0 < nocc_a, nocc_b < nbf violated, naux < 1, NULL pointers,
  * QSGW_ERR_SOLVER if the eigensolve fails.  Synchronizes the context stream; timed as
  * the fock stage of qsgw_last_stage_ms.

@@ -24,8 +24,8 @@
 //   4. back-transformations Z = Q1 Q2 E: the bulge-chasing reflectors in
 //      blocks of g consecutive sweeps at one step k (block (J, k) needs
 //      (J+1, k) and (J, k-1), so the blocks of one anti-diagonal are
-//      independent and touch disjoint rows), then the panel reflectors with
-//      rocSOLVER larfb (matrix products).
+//      independent and touch disjoint rows), then the panel reflectors as
+//      block reflectors by matrix products.
 //
 // All arrays are column-major; a symmetric row-major matrix is its own
 // column-major view.  Everything runs in FP64.
@@ -796,7 +796,7 @@ __global__ __launch_bounds__(256) void k_bulge(double* __restrict__ AB, int64_t 
 // band is read once, d and e leave from workgroup 0.
 // Bound by the instructions of a sweep (about 8,000 cycles a workgroup, of them
 // 1,300 waiting for the neighbours).  n = 10,400, kernel time: 20,795 launches
-// of k_bulge 228 ms, this one 34.4 ms; with the blocks in LDS 64 ms.
+// of k_bulge 228 ms, this one 34.9 ms; with the blocks in LDS 64 ms.
 struct alignas(16) BulgePos {
   double zero[kBand];
   double oc[kBand], row[kBand];         // the column to annihilate next, the window's first row of O

@@ -624,7 +624,7 @@ int tridiag_project_dc(qsgw_ctx* c, int64_t n, double* d, double* e, double* A, 
   run.info = reinterpret_cast<int*>(Iv);
   HIP_TRY(c, hipMemsetAsync(run.info, 0, (size_t)max_leaves * sizeof(int64_t), c->stream));
   if (depths == 0) {
-    // n <= dc_leaf: a single merge of two dstedc halves
+    // n <= dc_leaf: a single merge of two halves solved with their eigenvectors
     const DcLevel& L = run.lv[0];
     const int64_t n1 = n / 2, n2 = n - n1;
     double* scal = L.V + 13 * n;

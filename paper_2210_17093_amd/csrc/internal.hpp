@@ -545,11 +545,12 @@ int read_flag(qsgw_ctx* c, int* dflag, int* out) {
 }
 
 // The context's auxiliary streams.  Called before any cooperative launch too:
-// the first one makes the runtime take a hardware queue for itself, and the
-// streams created after that share the queues that are left (48 molecules in
-// reduced precision, whose dsyevd calls spread over these streams: 980 ms an
-// iteration pair with the streams created after a cooperative launch, 580 ms
-// before).
+// the first one makes the runtime take a hardware queue for itself, and where the
+// process has not used the others yet, the streams created after that share the
+// queues that are left (48 molecules in reduced precision, whose dsyevd calls
+// spread over these streams: 980 ms an iteration pair with the streams created
+// after a cooperative launch, 580 ms before, and 530 ms on a second context that
+// is created after the first one's launches).
 inline int aux_queues(qsgw_ctx* c) {
   for (int i = 0; i < qsgw_ctx::kAux; ++i)
     if (!c->aux[i]) HIP_TRY(c, hipStreamCreateWithFlags(&c->aux[i], hipStreamNonBlocking));
@@ -575,7 +576,7 @@ int syevd(qsgw_ctx* c, int64_t n, double* A, double* evals, const char* what) {
 }
 
 // Casida eigenproblems: the two-stage solver above the team solver's orders in
-// FP64 (order 3100: 37 ms, dsyevd 96; 5300: 89 and 239; 8100: 297 and 669),
+// FP64 (order 3100: 40 ms, dsyevd 95; 5300: 93 and 238; 8100: 298 and 667),
 // from kEigTwoStageMin on in the reduced precisions (see eig_dense)
 // (QSGW_EIG_AUTO).
 constexpr int64_t kEigTwoStageMin = 8192;
@@ -589,9 +590,10 @@ inline bool eig_two_stage_for(const qsgw_ctx* c, int64_t n, bool fp64) {
 // bits, and which way an entry close to a rounding boundary falls hangs on its
 // last FP64 bits: two solvers of equal accuracy give trajectories that part at
 // the level of these variants' own error (up to 2e-7 in the orbitals after two
-// iterations at 117 basis functions, against 1e-12 in FP64), so these variants
-// keep the solver their results were obtained with.  QSGW_EIG_ROCSOLVER asks for
-// rocSOLVER everywhere.
+// iterations at 117 basis functions, against 1e-12 in FP64).  Neither is the
+// better one by that, and dsyevd is the slower (two FP32 iterations with 61
+// functions 29 ms, 9 with the team solver); it stays here so that the results of
+// these variants do not move.  QSGW_EIG_ROCSOLVER asks for rocSOLVER everywhere.
 inline bool eig_team_for(qsgw_ctx* c, int64_t n, bool fp64) {
   return fp64 && c->eig_solver != QSGW_EIG_ROCSOLVER && eig_team_fits(c, n);
 }

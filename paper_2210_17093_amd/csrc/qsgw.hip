@@ -951,7 +951,7 @@ int iterate_impl(qsgw_ctx* c, const qsgw_problem* p, qsgw_state* st, const qsgw_
   float* rhoF32 = nullptr;
   unsigned long long* fprint = nullptr;
   // the two-stage solver hands the residues rho' of every excitation
-  // directly (projection), the rocSOLVER path the eigenvectors Z
+  // directly (projection), the other solvers the eigenvectors Z
   const bool fold = !qsmp2 && eig_two_stage_for(c, ntr, !fp32);
   if (!qsmp2) {  // (the qsMP2 potential replaces Casida, residues and the qsGW product)
     if (replay && (c->eig_ntr != ntr || c->eig_fold != fold))
