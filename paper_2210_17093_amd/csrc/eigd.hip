@@ -183,7 +183,9 @@ constexpr int kTeamSpinMax = 1 << 21;
 // The exchange has no flags: slot (j, i) = (y_i, A_j[j+1][i]) is written once,
 // each half by its owner, starts as kEmpty, and a reader polls the slots it needs.  Every group
 // computes the same scalars from the same values in the same order.
-// Row j of A takes v_j (every group has published y_j, so it has loaded its rows).
+// Row j of A takes v_j, once a whole workgroup has picked up y_j of every row: a
+// wave polls its own columns alone, and a workgroup that starts late (other work on
+// the device) may not have loaded its rows when another wave's slots are full.
 // Indices here run from the matrix's last row to its first (index i is row
 // n - 1 - i); T, the eigenvectors and the stored v are in the matrix's order.
 // That is the order in which dsyevd reduces an upper triangle, and with the
@@ -367,13 +369,6 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
         r[u] = in ? __builtin_bit_cast(double, u32x2{x[u][2], x[u][3]}) : 0.0;
       }
     }
-    if (j % G == g && rg == 0) {
-#pragma unroll
-      for (int u = 0; u < CU; ++u) {
-        const int c = tc + TC * u;
-        if (c < n) A[j * ld + (n - 1 - c)] = v[u];
-      }
-    }
     // ---- w and the next column ----
     double yv = 0.0;
 #pragma unroll
@@ -388,6 +383,15 @@ __device__ void tri_team(const EigDev& P, int g, TriSmem& sm, int* err) {
     yv = 0.0;
 #pragma unroll
     for (int q = 0; q < NW; ++q) yv += sm.red[1][rg][q];
+    // (only now, after the barrier, have this workgroup's waves together seen y_j
+    // of every row, and so each row's group has loaded it)
+    if (j % G == g && rg == 0) {
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int c = tc + TC * u;
+        if (c < n) A[j * ld + (n - 1 - c)] = v[u];
+      }
+    }
     const double kap = 0.5 * tau * tau * yv;
     const double w1 = tau * sm.al[1][rg] - kap;
 #pragma unroll
