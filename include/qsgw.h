@@ -496,8 +496,8 @@ int qsgw_iterate_unrestricted(qsgw_ctx* ctx, const qsgw_problem* prob, int64_t n
  * Every stage runs as one launch over all molecules: grouped matrix-core
  * GEMMs (a job table with one entry per molecule, each workgroup finding its
  * molecule by binary search) and segment kernels for the element-wise steps.
- * Each molecule's arithmetic is that of qsgw_iterate (same tile shapes, K
- * splits and epilogues).  In FP64 the Casida (and the Fock) eigensolves of
+ * Each molecule's arithmetic is that of qsgw_iterate (same K splits and
+ * epilogues, the tile table's shapes).  In FP64 the Casida (and the Fock) eigensolves of
  * every molecule run in the same launches of the one-stage solver (orders up
  * to 3072); larger ones, those of the reduced precisions and all of a context
  * set to QSGW_EIG_ROCSOLVER are rocSOLVER
