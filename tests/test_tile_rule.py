@@ -3,9 +3,11 @@ products choose (csrc/tiles.hpp compiled for the host), and, on the device, that
 a table which names no shape, or the default one written out and set again,
 launches the kernels of the default."""
 import ctypes as ct
+import json
 import os
 import shutil
 import subprocess
+import sys
 
 import pytest
 
@@ -66,33 +68,45 @@ def test_a_table_without_the_product_s_shape_chooses_as_the_default(lib, k, defa
             assert lib.table(k, other, tri, M, N, batch, nz) == other
 
 
+CHILD = """
+import json, sys
+sys.path[:0] = [sys.argv[1]]
+import torch
+import paper_2210_17093_amd.qsgw as q
+from qsgw_inputs import make_problem
+p = make_problem(60, 240, 10, 120, 0.99, 5)
+ctx = q.Context()
+B, e = torch.from_numpy(p.B_ao).cuda(), torch.from_numpy(p.eps0).cuda()
+ctx.set_tiles(None)
+default = ctx.get_tiles()
+out = {}
+for spec in ("", "dc_leaf=512", "persistent=1", "panel_coop=0", "mo1=64x64", default, "casida=64x64"):
+    ctx.set_tiles(spec)
+    q.qsgw_rpa_build(ctx, B, e, p.nocc)
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        q.qsgw_rpa_build(ctx, B, e, p.nocc)
+        torch.cuda.synchronize()
+    out["default table" if spec == default else spec] = sorted(
+        ev.name for ev in prof.events() if "gemm" in ev.name)
+print("KERNELS " + json.dumps(out), flush=True)
+"""
+
+
 @pytest.mark.gpu
 def test_launched_kernels_follow_the_table():
+    """(In a process of its own: the profiler stays loaded in the one that uses it.)"""
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("no HIP device")
-    import paper_2210_17093_amd.qsgw as q
-    from qsgw_inputs import make_problem
-    p = make_problem(60, 240, 10, 120, 0.99, 5)
-    ctx = q.Context()
-    B, e = torch.from_numpy(p.B_ao).cuda(), torch.from_numpy(p.eps0).cuda()
-    ctx.set_tiles(None)
-    default = ctx.get_tiles()
-
-    def kernels(spec):
-        ctx.set_tiles(spec)
-        q.qsgw_rpa_build(ctx, B, e, p.nocc)
-        torch.cuda.synchronize()
-        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
-            q.qsgw_rpa_build(ctx, B, e, p.nocc)
-            torch.cuda.synchronize()
-        return sorted(ev.name for ev in prof.events() if "gemm" in ev.name)
-
-    try:
-        want = kernels(None)
-        assert want, "no product seen"
-        for spec in ("dc_leaf=512", "persistent=1", "panel_coop=0", "mo1=64x64", default):
-            assert kernels(spec) == want, spec
-        assert kernels("casida=64x64") != want
-    finally:
-        ctx.close()
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-u", "-c", CHILD, root], cwd=root, timeout=100,
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    lines = [x for x in r.stdout.splitlines() if x.startswith("KERNELS ")]
+    assert lines, r.stdout[-2000:]
+    out = json.loads(lines[0][len("KERNELS "):])
+    other = out.pop("casida=64x64")
+    want = out.pop("")
+    assert want and other != want
+    for spec, got in out.items():
+        assert got == want, spec
